@@ -15,9 +15,12 @@ launch variant whose result agrees with the default, median of three rounds;
 each operator, as an operator is applied inside CG; --interleaved runs them
 step by step).  Per order each apply is bracketed by HIP events on the launch
 stream; the
-roofline fraction uses the algorithmic bytes of one apply,
-  8 N (x) + 8 N (y) + 4 E (p+1)^3 (restriction) + 48 E q^3 (geometric factors),
-over the measured duration, against 8 TB/s.  The CPU baseline times the FP64
+roofline fraction uses the algorithmic bytes of one apply over the measured
+duration, against 8 TB/s:
+  8 N (x) + 8 N (y) + the vertices (factors evaluated in the kernel), or
+  8 N + 8 N + 4 E (p+1)^3 (restriction) + 48 E q^3 (stored factors),
+as the launch variant reads them, next to the FP64 rate against 78.6 TFLOP/s;
+the larger fraction names the bound.  The CPU baseline times the FP64
 oracle (dense, no sum factorization) on a bounded sample on the host cores.
 
 The same run times a 1 GiB device copy and reports each order's fraction of
@@ -61,15 +64,20 @@ def alg_flops(E: int, p: int, q: int, kind: str = "diffusion", colloc: bool = Fa
     interp = 0 if colloc else 4 * (Q * P ** 3 + Q * Q * P * P + Q ** 3 * P)
     if kind == "mass":
         return E * (interp + Q ** 3)
-    # in-kernel factors: 3 adjugate rows (27), detJ (5), 6 products (30), scaling (8) per point,
-    # and 3 Q^2 Jacobian columns (36 each) per element
-    geo = (70 * Q ** 3 + 108 * Q ** 2) if otf else 0
+    # in-kernel factors: columns (12), cross products (27), detJ (5), reciprocal (8), scaling and
+    # sums (20) per point beyond the 3x3 product, and five columns (36) per z-line
+    geo = (72 * Q ** 3 + 36 * Q ** 2) if otf else 0
     return E * (interp + 12 * Q ** 4 + 15 * Q ** 3 + geo)
 
 
-def alg_bytes_otf(N: int, E: int, ne: int, p: int) -> int:
-    """In-kernel factors: x, y, offsets and the vertex coordinates (each vertex read once)."""
-    return 8 * N * 2 + 4 * E * (p + 1) ** 3 + 24 * (ne + 1) ** 3
+def alg_bytes_otf(N: int, ne: int) -> int:
+    """In-kernel factors: x, y and the vertex coordinates (each vertex read once)."""
+    return 8 * N * 2 + 24 * (ne + 1) ** 3
+
+
+def in_kernel_factors(kind: str, variant: int, otf: bool = False) -> bool:
+    """Launch variants that evaluate the geometric factors in the kernel (k_line, Gauss points)."""
+    return otf or (kind == "mass" and variant < 5) or (kind == "diffusion" and 9 <= variant <= 14)
 
 
 def cpu_baseline(p: int, budget_s: float = 12.0) -> dict:
@@ -210,9 +218,10 @@ def main():
     for p in orders:
         t_ms = float(np.mean([a.elapsed_time(b) for a, b in evs[p]]))
         m = meta[p]
-        byts = (alg_bytes_otf(m["N"], m["E"], m["ne"], p) if args.otf else
+        geo = in_kernel_factors(args.kind, m["epb"][0], args.otf)
+        byts = (alg_bytes_otf(m["N"], m["ne"]) if geo else
                 alg_bytes(m["N"], m["E"], p, m["q"], g=6 if args.kind == "diffusion" else 1))
-        fl = alg_flops(m["E"], p, m["q"], args.kind, otf=args.otf)
+        fl = alg_flops(m["E"], p, m["q"], args.kind, otf=geo)
         gbs = byts / (t_ms / 1e3) / 1e9
         per_p.append({"p": p, "elements_per_dim": m["ne"], "dofs": m["N"], "ms": round(t_ms, 4),
                       "gdofs": round(m["N"] / (t_ms / 1e3) / 1e9, 3), "alg_bytes": byts,
@@ -231,19 +240,16 @@ def main():
     from paper_2109_05072_amd.prof_summary import read_traffic
     lg = dom["launch"]
     if args.kind == "diffusion":
-        tag = "otf " if args.otf else ""
         traffic = read_traffic(os.path.join(ROOT, "profiles", f"bp3{'_otf' if args.otf else ''}_apply_traffic.txt"))
-        gf = 9 <= lg["variant"] <= 14
-        kname = "k_apply_gf" if gf else "k_apply"
+        kname = "k_line" if in_kernel_factors(args.kind, lg["variant"], args.otf) else "k_apply"
         late = LATE_FACTOR_SLOTS.get((dom["p"] + 2, lg["variant"]))
         pre = PREFETCH_SLOTS.get((dom["p"] + 2, lg["variant"]))
-        suffix = (" late-factors" if lg["variant"] == 14 else
-                  f" late{late}{f' pre{pre}' if pre else ''}" if late and not args.otf else "")
-        dom_name = (f"{kname} p={dom['p']} q={dom['p'] + 2} diffusion {tag}double G={lg['elements_per_group']} "
+        suffix = f" late{late}{f' pre{pre}' if pre else ''}" if late and kname == "k_apply" else ""
+        dom_name = (f"{kname} p={dom['p']} q={dom['p'] + 2} diffusion double G={lg['elements_per_group']} "
                     f"NT={lg['threads_per_group']}{suffix}")
     else:
         traffic = read_traffic(os.path.join(ROOT, "profiles", "bp1_apply_traffic.txt"))
-        dom_name = (f"k_mass p={dom['p']} q={dom['p'] + 2} double G={lg['elements_per_group']} "
+        dom_name = (f"k_line p={dom['p']} q={dom['p'] + 2} mass double G={lg['elements_per_group']} "
                     f"NT={lg['threads_per_group']}")
     out = {
         "metric": METRIC, "value": round(value, 3), "unit": "GDOF/s", "n_gpus": 1,
@@ -263,7 +269,7 @@ def main():
                       "frac": dom["hbm_frac"], "traffic": traffic.get(dom_name),
                       "alg_bytes_per_launch": dom["alg_bytes"], "measured_copy_gbs": round(copy_gbs, 1),
                       "frac_of_copy": dom["copy_frac"]}
-                     if not args.otf or dom["hbm_frac"] >= dom["fp64_alu_frac"] else
+                     if dom["hbm_frac"] >= dom["fp64_alu_frac"] else
                      {"bound": "alu", "kernel": dom_name, "achieved": dom["alg_tflops"],
                       "peak": FP64_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": dom["fp64_alu_frac"],
                       "traffic": traffic.get(dom_name), "alg_bytes_per_launch": dom["alg_bytes"],
@@ -447,9 +453,10 @@ def per_order_sweep(orders, dofs: float, steps: int = 5, tune: bool = True) -> l
             e1.record()
         torch.cuda.synchronize()
         ms = float(np.median([a.elapsed_time(b) for a, b in ev]))
-        byts = alg_bytes(op.n_nodes, op.n_elem, p, p + 2)
-        gbs = byts / (ms / 1e3) / 1e9
         cfg = op.get_config()
+        byts = (alg_bytes_otf(op.n_nodes, ne) if in_kernel_factors("diffusion", cfg[0]) else
+                alg_bytes(op.n_nodes, op.n_elem, p, p + 2))
+        gbs = byts / (ms / 1e3) / 1e9
         r = {"p": p, "elements_per_dim": ne, "dofs": op.n_nodes, "ms": round(ms, 4),
              "gdofs": round(op.n_nodes / (ms / 1e3) / 1e9, 3), "alg_bytes": byts, "alg_gbs": round(gbs, 1),
              "hbm_frac": round(gbs / HBM_PEAK_GBS, 4),

@@ -92,7 +92,12 @@ enum { MFHEX_PRECOND_NONE = 0, MFHEX_PRECOND_JACOBI = 1, MFHEX_PRECOND_MG = 2 };
  *   set by mfhex_set_kappa multiplies the geometric factors.
  *   vertex_xyz: HOST array [(nex+1)(ney+1)(nez+1)][3] of FP64 vertex
  *   coordinates, x fastest; each hexahedron is the trilinear image of
- *   [-1,1]^3 through its 8 vertices.  Copied into the workspace by create. */
+ *   [-1,1]^3 through its 8 vertices.  Copied into the workspace by create.
+ * Unless MFHEX_FLAG_OTF drops it, create stores the six factors per point;
+ * the multi-vector launches, the coefficient gradient, the diagonal and the
+ * stored-factor launch variants read them.  The default single-vector launch
+ * evaluates the factors from the trilinear map instead (equal up to
+ * rounding; mfhex_set_config). */
 typedef struct {
     int32_t nex, ney, nez;
     int32_t p, q, quad, kind, ncomp, dirichlet, variable_kappa;
@@ -319,10 +324,11 @@ int mfhex_get_config(mfhex_op op, int prec, int nrhs, int32_t *variant, int32_t 
                      int32_t *threads_per_group, int32_t *groups_per_block);
 
 /* Force the launch configuration for (prec, nrhs): variant 0 .. 16 (5 .. 8
- * carry 2, 4, 8, 16 vectors of a multi-vector together; 9 .. 14 are the
- * factored-gradient diffusion kernel for Gauss points, which forms the
- * gradient with the basis derivative at the points in three contraction
- * stages instead of six; 15 and 16 carry 4 and 8 vectors with the gradient
+ * carry 2, 4, 8, 16 vectors of a multi-vector together; 9 .. 14 for diffusion
+ * with Gauss points, and 0 .. 4 for collocated or OTF diffusion and for mass
+ * with Gauss points, are the line-fused kernel, which evaluates the factors
+ * from the element's trilinear map; 0 .. 4 of diffusion with Gauss points
+ * read the stored factors; 15 and 16 carry 4 and 8 vectors with the gradient
  * contractions on the FP64 matrix cores, collocated FP64 diffusion only) and
  * pipeline depth
  * groups_per_block (0: the operator's default, measured per order for mass

@@ -35,7 +35,6 @@
 #include <type_traits>
 
 #include "diag_kernels.hpp"
-#include "geom.hpp"
 #include "mfhex_internal.h"
 
 namespace mfhex {
@@ -71,6 +70,12 @@ __device__ __forceinline__ void group_sync()
         __syncthreads();
     }
 }
+
+}  // namespace mfhex
+
+#include "line_kernels.hpp"
+
+namespace mfhex {
 
 // Contract axis AX of the G element arrays (extents E0 x E1 x E2 before the
 // contraction) from NI = E_AX to NO entries: dst[..o..] = sum_i M[o][i]
@@ -545,20 +550,12 @@ __device__ __forceinline__ void contract_halves(const T *src, T *dst, const T *_
 // y += A x  (diffusion), or y += B^T (w detJ f) for the load vector.
 // VC vectors of the multi-vector travel together (virtual elements g*VC + vc).
 // ---------------------------------------------------------------------------
-//
-// OTF (diffusion, FP64, constant coefficient): no stored factors.  Along a
-// trilinear map dx/dr depends on (s, t) only, dx/ds on (r, t) and dx/dt on
-// (r, s), so each element's Jacobian is fully described by three tables of
-// Q^2 columns, built once per element group in LDS from its 8 vertices; each
-// point then reads its three columns and forms w adj(J) adj(J)^T / detJ in
-// registers (the same expressions as the set-up kernel), instead of reading
-// six factors per point from HBM.
-template <int P, int Q, bool COLLOC, int MODE, bool VARK, typename T, int G, int NT, int VC, bool OTF, bool DET,
+template <int P, int Q, bool COLLOC, int MODE, bool VARK, typename T, int G, int NT, int VC, bool DET,
           bool STAGE = false, int LATE = 0, bool MX = false, int PRE = 0>
 __global__ void __launch_bounds__(NT)
-k_apply(const T *__restrict__ bas, const int nex, const int ney, const int nvec, const int32_t *__restrict__ offsets,
+k_apply(const T *__restrict__ bas, const int nex, const int nvec, const int32_t *__restrict__ offsets,
         const T *__restrict__ qdata, const double *__restrict__ kappa, const double *__restrict__ wdet,
-        const double *__restrict__ vert, const T *__restrict__ x, T *__restrict__ y, T *__restrict__ ebuf)
+        const T *__restrict__ x, T *__restrict__ y, T *__restrict__ ebuf)
 {
     constexpr int Q2 = Q * Q, Q3 = Q2 * Q;
     constexpr int NPT = G * Q3, RQ = (NPT + NT - 1) / NT;
@@ -566,17 +563,12 @@ k_apply(const T *__restrict__ bas, const int nex, const int ney, const int nvec,
     constexpr bool SPLIT = split_stages(Q, MODE, G, NT, VC);
     constexpr int NT2 = NT / 2;
     static_assert(MODE != kMass, "the mass operator runs in k_mass");
-    static_assert(!OTF || (MODE == kDiff && !VARK && VC == 1 && sizeof(T) == 8), "in-kernel factors: FP64 diffusion");
     using L = Lds<Q>;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     T *const s0 = reinterpret_cast<T *>(smem_raw);
     T *const s1 = s0 + GV * L::BUF;
     T *const s2 = s1 + GV * L::BUF;
     T *const s3 = s2 + GV * L::BUF;  // split stages only
-    // OTF: element vertices [G][8][3], 1D rule x [Q], w [Q] (one contiguous run), Jacobian columns [G][3][Q^2][3]
-    double *const sV = reinterpret_cast<double *>(SPLIT ? s3 + GV * L::BUF : s2 + GV * L::BUF);
-    double *const sR = sV + G * 24;
-    double *const sJ = sR + 2 * Q;
     // staged scatter of multi-vector chunks: element values [P^3][SC - VC], then offsets [P^3]
     constexpr int P3 = P * P * P;
     static_assert(!STAGE || (staged_scatter(MODE, VC, sizeof(T)) && !DET), "staged scatter: multi-vector diffusion");
@@ -589,36 +581,19 @@ k_apply(const T *__restrict__ bas, const int nex, const int ney, const int nvec,
     const int64_t e0 = gpos.e0;
     const int nvalid = gpos.nvalid;
     // MX: the collocated gradient and its transpose on the matrix cores (fragments of D and D^T)
-    static_assert(!MX || (COLLOC && MODE == kDiff && !SPLIT && !OTF && sizeof(T) == 8), "matrix-core stages");
+    static_assert(!MX || (COLLOC && MODE == kDiff && !SPLIT && sizeof(T) == 8), "matrix-core stages");
     double mxd[MX ? mx_steps(Q) : 1], mxt[MX ? mx_steps(Q) : 1];
     if constexpr (MX) {
         mx_fragments<Q, -1>(reinterpret_cast<const double *>(bas) + basis_df(P, Q), mxd, tid & 63);
         mx_fragments<Q, -1>(reinterpret_cast<const double *>(bas) + basis_dtf(P, Q), mxt, tid & 63);
     }
     if constexpr (STAGE) {
-        static_assert(G == 1 && !SPLIT && !OTF, "staged scatter: one element, plain stages");
+        static_assert(G == 1 && !SPLIT, "staged scatter: one element, plain stages");
         for (int t = tid; t < P3; t += NT) soff[t] = __builtin_nontemporal_load(&offsets[e0 * P3 + t]);
     }
 
     int32_t off[NodeIO<P, G, NT, VC>::NR];
     load_offsets<P, G, NT, VC>(off, offsets, e0, nvalid, tid);
-
-    // OTF: the group's vertex coordinates, issued now, stored to LDS after the gather is issued
-    constexpr int VR = OTF ? (24 * G + 2 * Q + NT - 1) / NT : 1;
-    double vtx[VR];
-    if constexpr (OTF) {
-#pragma unroll
-        for (int r = 0; r < VR; ++r) {
-            const int t = tid + r * NT;
-            if (t < 24 * G) {
-                const int g = t / 24, v = (t % 24) / 3, d = t % 3;
-                const int64_t e = g < nvalid ? e0 + g : e0;
-                vtx[r] = vert[3 * elem_vertex(e, nex, ney, v) + d];
-            } else if (t < 24 * G + 2 * Q) {
-                vtx[r] = bas[basis_xq(P, Q) + (t - 24 * G)];  // x [Q] then w [Q], contiguous
-            }
-        }
-    }
 
     // This lane's geometric factors, loaded once per element group and issued
     // first, so their HBM latency overlaps the gather and the forward
@@ -626,9 +601,9 @@ k_apply(const T *__restrict__ bas, const int nex, const int ney, const int nvec,
     // the pointwise stage instead, LATE points at a time, which keeps their
     // registers free through the contractions; with PRE > 0 the lane's first PRE points are still
     // prefetched and only the rest load late).
-    static_assert(LATE == 0 || (VC == 1 && !OTF && MODE == kDiff), "late factor loads: one-vector diffusion");
+    static_assert(LATE == 0 || (VC == 1 && MODE == kDiff), "late factor loads: one-vector diffusion");
     static_assert(PRE == 0 || (LATE > 0 && PRE < RQ), "partial prefetch: some points late");
-    constexpr int NQD = MODE == kDiff && !OTF && (LATE == 0 || PRE > 0) ? kQdDiff : 0;
+    constexpr int NQD = MODE == kDiff && (LATE == 0 || PRE > 0) ? kQdDiff : 0;
     constexpr int KP = LATE == 0 ? RQ : PRE;  // points whose factors are prefetched
     T qv[KP > 0 ? KP : 1][NQD > 0 ? NQD : 1];
     if constexpr (NQD > 0) {
@@ -653,7 +628,7 @@ k_apply(const T *__restrict__ bas, const int nex, const int ney, const int nvec,
     // chunk's right after the previous chunk is in LDS, so their memory latency overlaps that
     // chunk's contractions.  (One-vector groups keep no such registers: at q = 10 they would cost
     // a wavefront per SIMD.)
-    constexpr bool PREFETCH = VC > 1 && MODE != kRhs && !OTF;
+    constexpr bool PREFETCH = VC > 1 && MODE != kRhs;
     T xn[PREFETCH ? NodeIO<P, G, NT, VC>::NR : 1];
     if constexpr (PREFETCH) gather_load<P, G, NT, VC>(xn, off, x, nvec, 0, tid);
 
@@ -673,30 +648,7 @@ k_apply(const T *__restrict__ bas, const int nex, const int ney, const int nvec,
             }
             group_sync<NT>();
         } else {
-            if constexpr (OTF) {
-                T xv[NodeIO<P, G, NT, VC>::NR];
-                gather_load<P, G, NT, VC>(xv, off, x, nvec, v0, tid);
-                if (v0 == 0) {
-                    // vertices and rule into LDS, then the Jacobian-column tables (the x loads stay in flight)
-#pragma unroll
-                    for (int r = 0; r < VR; ++r)
-                        if (tid + r * NT < 24 * G + 2 * Q) sV[tid + r * NT] = vtx[r];
-                    group_sync<NT>();
-                    for (int t = tid; t < G * 3 * Q2; t += NT) {
-                        const int g = t / (3 * Q2), dir = (t / Q2) % 3, uw = t % Q2;
-                        const double u = sR[uw % Q], w = sR[uw / Q];
-                        const double *Xg = sV + g * 24;
-                        auto X = [&](int v, int d) { return Xg[3 * v + d]; };
-                        double j[3];
-                        if (dir == 0) jacobian_col<0>(X, u, w, j);
-                        else if (dir == 1) jacobian_col<1>(X, u, w, j);
-                        else jacobian_col<2>(X, u, w, j);
-#pragma unroll
-                        for (int d = 0; d < 3; ++d) sJ[3 * t + d] = j[d];
-                    }
-                }
-                gather_store<P, Q, G, NT, VC>(SPLIT && COLLOC ? s3 : s0, xv, off, nvec, v0, nvalid, tid);
-            } else if constexpr (PREFETCH) {
+            if constexpr (PREFETCH) {
                 gather_store<P, Q, G, NT, VC>(s0, xn, off, nvec, v0, nvalid, tid);
                 if (v0 + VC < nvec) gather_load<P, G, NT, VC>(xn, off, x, nvec, v0 + VC, tid);
             } else {
@@ -761,16 +713,6 @@ k_apply(const T *__restrict__ bas, const int nex, const int ney, const int nvec,
                                 for (int m = 0; m < kQdDiff; ++m) gl[m] *= kap;
                             }
                             gm = gl;
-                        }
-                        double gotf[kQdDiff];
-                        if constexpr (OTF) {
-                            // columns dx/dr at (b, c), dx/ds at (a, c), dx/dt at (a, b) of element g
-                            const double *Jg = sJ + g * 9 * Q2;
-                            const double *jr = Jg + 3 * (b + Q * c), *js = Jg + 3 * (Q2 + a + Q * c),
-                                         *jt = Jg + 3 * (2 * Q2 + a + Q * b);
-                            const double wq = sR[Q + a] * sR[Q + b] * sR[Q + c];
-                            diffusion_factors(jr, js, jt, wq, gotf);
-                            gm = gotf;
                         }
 #pragma unroll
                         for (int vc = 0; vc < VC; ++vc) {
@@ -1033,380 +975,6 @@ k_kgrad(const double *__restrict__ bas, const int64_t nelem, const int32_t *__re
 }
 
 // ---------------------------------------------------------------------------
-// y += A x (diffusion, Gauss points, q = p+2) with the gradient factored
-// through the basis derivative at the points, G[a][i] = l_i'(x_a):
-//   u_r = (G (x) B (x) B) u,  u_s = (B (x) G (x) B) u,  u_t = (B (x) B (x) G) u
-// (x fastest in the Kronecker products), and back
-//   y = (G^T B^T B^T) v_r + (B^T G^T B^T) v_s + (B^T B^T G^T) v_t.
-// Sharing the partial products, the whole operator is six contraction
-// stages instead of twelve: z (B u and G u), y (B and G of the first, B of
-// the second), x (G, B, B), then the pointwise factors, and x (G^T, B^T,
-// B^T), y (B^T + G^T, B^T), z (B^T + G^T).  Each stage reads every line it
-// owns once from LDS and forms two or three contractions from it, so there
-// are half as many stage barriers and about 40% less LDS traffic, at the
-// cost of about 20% more multiply-adds (G is Q x P where the collocated
-// derivative D is Q x Q, but it is applied to P-long lines).  Same element
-// groups, restriction, even-odd folding and factor prefetch as k_apply.
-// ---------------------------------------------------------------------------
-
-// One line of NI values, folded: e_i = v_i + v_{NI-1-i}, d_i = v_i - v_{NI-1-i} (i < NI/2), e_{NI/2} = v_mid.
-template <int NI, typename T>
-struct FLine {
-    static constexpr int H = NI / 2, MID = NI & 1;
-    T e[H + MID];
-    T d[H > 0 ? H : 1];
-};
-
-template <int NI, int ST, typename T>
-__device__ __forceinline__ void fold_line(const T *src, int base, FLine<NI, T> &f)
-{
-    constexpr int H = NI / 2;
-    T v[NI];
-#pragma unroll
-    for (int i = 0; i < NI; ++i) v[i] = src[base + i * ST];
-#pragma unroll
-    for (int i = 0; i < H; ++i) {
-        f.e[i] = v[i] + v[NI - 1 - i];
-        f.d[i] = v[i] - v[NI - 1 - i];
-    }
-    if constexpr (NI & 1) f.e[H] = v[H];
-}
-
-// Even and odd half-sums of one folded row against a folded line: out_o = E + O and
-// out_{NO-1-o} = SYM (E - O).
-template <int NI, typename T>
-__device__ __forceinline__ void fdot(const T *__restrict__ row, const FLine<NI, T> &f, T &E, T &O)
-{
-    constexpr int H = NI / 2;
-    E = T(0);
-    O = T(0);
-#pragma unroll
-    for (int i = 0; i < H; ++i) {
-        E += row[i] * f.e[i];
-        O += row[H + i] * f.d[i];
-    }
-    if constexpr (NI & 1) E += row[2 * H] * f.e[H];
-}
-
-// Lines along axis AX of G element arrays with extents (E0, E1, E2) (same lane-to-line order as contract()).
-template <int AX, int E0, int E1, int E2, int G, int NT, int Q>
-struct LineSet {
-    using L = Lds<Q>;
-    static constexpr int NI = AX == 0 ? E0 : AX == 1 ? E1 : E2;
-    static constexpr int NA = AX == 0 ? E1 : E0;
-    static constexpr int NB = AX == 2 ? E1 : E2;
-    static constexpr int SA = AX == 0 ? L::PITCH : 1;
-    static constexpr int SB = AX == 2 ? L::PITCH : L::PLANE;
-    static constexpr int ST = AX == 0 ? 1 : AX == 1 ? L::PITCH : L::PLANE;
-    static constexpr int NPEN = G * NA * NB;
-    static constexpr int R = (NPEN + NT - 1) / NT;
-    __device__ static __forceinline__ int base(int id)
-    {
-        const int a = id % NA, t = id / NA, b = t % NB, g = t / NB;
-        return g * L::BUF + a * SA + b * SB;
-    }
-};
-
-// Forward z: A (nodes) -> A = B_z u, Bb = G_z u.
-template <int P, int Q, int G, int NT, typename T>
-__device__ __forceinline__ void gf_z(T *A, T *Bb, const T *__restrict__ bas, int tid)
-{
-    using LS = LineSet<2, P, P, P, G, NT, Q>;
-    constexpr int NOH = (Q + 1) / 2, UR = 2;
-    FLine<P, T> f[LS::R];
-    int base[LS::R];
-#pragma unroll
-    for (int r = 0; r < LS::R; ++r) {
-        const int id = tid + r * NT;
-        base[r] = id < LS::NPEN ? LS::base(id) : -1;
-        if (base[r] >= 0) fold_line<P, LS::ST>(A, base[r], f[r]);
-    }
-    const T *bf = bas + basis_bf(P, Q), *gf = bas + basis_gf(P, Q);
-#pragma unroll UR
-    for (int o = 0; o < NOH; ++o) {
-        const int om = Q - 1 - o;
-#pragma unroll
-        for (int r = 0; r < LS::R; ++r) {
-            if (base[r] < 0) continue;
-            T E, O;
-            fdot<P>(bf + o * P, f[r], E, O);
-            A[base[r] + o * LS::ST] = E + O;
-            if (om != o) A[base[r] + om * LS::ST] = E - O;
-            fdot<P>(gf + o * P, f[r], E, O);
-            Bb[base[r] + o * LS::ST] = E + O;
-            if (om != o) Bb[base[r] + om * LS::ST] = O - E;
-        }
-    }
-}
-
-// Forward y: A (B_z u), Bb (G_z u) -> A = B_y A, C = G_y A, Bb = B_y Bb.
-template <int P, int Q, int G, int NT, typename T>
-__device__ __forceinline__ void gf_y(T *A, T *Bb, T *C, const T *__restrict__ bas, int tid)
-{
-    using LS = LineSet<1, P, P, Q, G, NT, Q>;
-    constexpr int NOH = (Q + 1) / 2, UR = 2;
-    FLine<P, T> fa[LS::R], fb[LS::R];
-    int base[LS::R];
-#pragma unroll
-    for (int r = 0; r < LS::R; ++r) {
-        const int id = tid + r * NT;
-        base[r] = id < LS::NPEN ? LS::base(id) : -1;
-        if (base[r] >= 0) {
-            fold_line<P, LS::ST>(A, base[r], fa[r]);
-            fold_line<P, LS::ST>(Bb, base[r], fb[r]);
-        }
-    }
-    const T *bf = bas + basis_bf(P, Q), *gf = bas + basis_gf(P, Q);
-#pragma unroll UR
-    for (int o = 0; o < NOH; ++o) {
-        const int om = Q - 1 - o;
-#pragma unroll
-        for (int r = 0; r < LS::R; ++r) {
-            if (base[r] < 0) continue;
-            T E, O;
-            fdot<P>(bf + o * P, fa[r], E, O);
-            A[base[r] + o * LS::ST] = E + O;
-            if (om != o) A[base[r] + om * LS::ST] = E - O;
-            fdot<P>(gf + o * P, fa[r], E, O);
-            C[base[r] + o * LS::ST] = E + O;
-            if (om != o) C[base[r] + om * LS::ST] = O - E;
-            fdot<P>(bf + o * P, fb[r], E, O);
-            Bb[base[r] + o * LS::ST] = E + O;
-            if (om != o) Bb[base[r] + om * LS::ST] = E - O;
-        }
-    }
-}
-
-// Forward x: A, C, Bb -> A = G_x A (d/dr), C = B_x C (d/ds), Bb = B_x Bb (d/dt), all at the points.
-template <int P, int Q, int G, int NT, typename T>
-__device__ __forceinline__ void gf_x(T *A, T *Bb, T *C, const T *__restrict__ bas, int tid)
-{
-    using LS = LineSet<0, P, Q, Q, G, NT, Q>;
-    constexpr int NOH = (Q + 1) / 2, UR = 1;
-    FLine<P, T> fa[LS::R], fb[LS::R], fc[LS::R];
-    int base[LS::R];
-#pragma unroll
-    for (int r = 0; r < LS::R; ++r) {
-        const int id = tid + r * NT;
-        base[r] = id < LS::NPEN ? LS::base(id) : -1;
-        if (base[r] >= 0) {
-            fold_line<P, LS::ST>(A, base[r], fa[r]);
-            fold_line<P, LS::ST>(Bb, base[r], fb[r]);
-            fold_line<P, LS::ST>(C, base[r], fc[r]);
-        }
-    }
-    const T *bf = bas + basis_bf(P, Q), *gf = bas + basis_gf(P, Q);
-#pragma unroll UR
-    for (int o = 0; o < NOH; ++o) {
-        const int om = Q - 1 - o;
-#pragma unroll
-        for (int r = 0; r < LS::R; ++r) {
-            if (base[r] < 0) continue;
-            T E, O;
-            fdot<P>(gf + o * P, fa[r], E, O);
-            A[base[r] + o] = E + O;
-            if (om != o) A[base[r] + om] = O - E;
-            fdot<P>(bf + o * P, fc[r], E, O);
-            C[base[r] + o] = E + O;
-            if (om != o) C[base[r] + om] = E - O;
-            fdot<P>(bf + o * P, fb[r], E, O);
-            Bb[base[r] + o] = E + O;
-            if (om != o) Bb[base[r] + om] = E - O;
-        }
-    }
-}
-
-// Transposed x: A (v_r), C (v_s), Bb (v_t) at the points -> A = G_x^T A, C = B_x^T C, Bb = B_x^T Bb.
-template <int P, int Q, int G, int NT, typename T>
-__device__ __forceinline__ void gf_xt(T *A, T *Bb, T *C, const T *__restrict__ bas, int tid)
-{
-    using LS = LineSet<0, Q, Q, Q, G, NT, Q>;
-    constexpr int NOH = (P + 1) / 2, UR = 1;
-    FLine<Q, T> fa[LS::R], fb[LS::R], fc[LS::R];
-    int base[LS::R];
-#pragma unroll
-    for (int r = 0; r < LS::R; ++r) {
-        const int id = tid + r * NT;
-        base[r] = id < LS::NPEN ? LS::base(id) : -1;
-        if (base[r] >= 0) {
-            fold_line<Q, LS::ST>(A, base[r], fa[r]);
-            fold_line<Q, LS::ST>(Bb, base[r], fb[r]);
-            fold_line<Q, LS::ST>(C, base[r], fc[r]);
-        }
-    }
-    const T *btf = bas + basis_btf(P, Q), *gtf = bas + basis_gtf(P, Q);
-#pragma unroll UR
-    for (int o = 0; o < NOH; ++o) {
-        const int om = P - 1 - o;
-#pragma unroll
-        for (int r = 0; r < LS::R; ++r) {
-            if (base[r] < 0) continue;
-            T E, O;
-            fdot<Q>(gtf + o * Q, fa[r], E, O);
-            A[base[r] + o] = E + O;
-            if (om != o) A[base[r] + om] = O - E;
-            fdot<Q>(btf + o * Q, fc[r], E, O);
-            C[base[r] + o] = E + O;
-            if (om != o) C[base[r] + om] = E - O;
-            fdot<Q>(btf + o * Q, fb[r], E, O);
-            Bb[base[r] + o] = E + O;
-            if (om != o) Bb[base[r] + om] = E - O;
-        }
-    }
-}
-
-// Transposed y: A, C, Bb (nodes along x, points along y and z) -> A = B_y^T A + G_y^T C, Bb = B_y^T Bb.
-template <int P, int Q, int G, int NT, typename T>
-__device__ __forceinline__ void gf_yt(T *A, T *Bb, const T *C, const T *__restrict__ bas, int tid)
-{
-    using LS = LineSet<1, P, Q, Q, G, NT, Q>;
-    constexpr int NOH = (P + 1) / 2, UR = 1;
-    FLine<Q, T> fa[LS::R], fb[LS::R], fc[LS::R];
-    int base[LS::R];
-#pragma unroll
-    for (int r = 0; r < LS::R; ++r) {
-        const int id = tid + r * NT;
-        base[r] = id < LS::NPEN ? LS::base(id) : -1;
-        if (base[r] >= 0) {
-            fold_line<Q, LS::ST>(A, base[r], fa[r]);
-            fold_line<Q, LS::ST>(Bb, base[r], fb[r]);
-            fold_line<Q, LS::ST>(C, base[r], fc[r]);
-        }
-    }
-    const T *btf = bas + basis_btf(P, Q), *gtf = bas + basis_gtf(P, Q);
-#pragma unroll UR
-    for (int o = 0; o < NOH; ++o) {
-        const int om = P - 1 - o;
-#pragma unroll
-        for (int r = 0; r < LS::R; ++r) {
-            if (base[r] < 0) continue;
-            T E1, O1, E2, O2;
-            fdot<Q>(btf + o * Q, fa[r], E1, O1);
-            fdot<Q>(gtf + o * Q, fc[r], E2, O2);
-            A[base[r] + o * LS::ST] = (E1 + O1) + (E2 + O2);
-            if (om != o) A[base[r] + om * LS::ST] = (E1 - O1) + (O2 - E2);
-            fdot<Q>(btf + o * Q, fb[r], E1, O1);
-            Bb[base[r] + o * LS::ST] = E1 + O1;
-            if (om != o) Bb[base[r] + om * LS::ST] = E1 - O1;
-        }
-    }
-}
-
-// Transposed z: A, Bb (nodes along x and y, points along z) -> A = B_z^T A + G_z^T Bb (element values).
-template <int P, int Q, int G, int NT, typename T>
-__device__ __forceinline__ void gf_zt(T *A, const T *Bb, const T *__restrict__ bas, int tid)
-{
-    using LS = LineSet<2, P, P, Q, G, NT, Q>;
-    constexpr int NOH = (P + 1) / 2, UR = 2;
-    FLine<Q, T> fa[LS::R], fb[LS::R];
-    int base[LS::R];
-#pragma unroll
-    for (int r = 0; r < LS::R; ++r) {
-        const int id = tid + r * NT;
-        base[r] = id < LS::NPEN ? LS::base(id) : -1;
-        if (base[r] >= 0) {
-            fold_line<Q, LS::ST>(A, base[r], fa[r]);
-            fold_line<Q, LS::ST>(Bb, base[r], fb[r]);
-        }
-    }
-    const T *btf = bas + basis_btf(P, Q), *gtf = bas + basis_gtf(P, Q);
-#pragma unroll UR
-    for (int o = 0; o < NOH; ++o) {
-        const int om = P - 1 - o;
-#pragma unroll
-        for (int r = 0; r < LS::R; ++r) {
-            if (base[r] < 0) continue;
-            T E1, O1, E2, O2;
-            fdot<Q>(btf + o * Q, fa[r], E1, O1);
-            fdot<Q>(gtf + o * Q, fb[r], E2, O2);
-            A[base[r] + o * LS::ST] = (E1 + O1) + (E2 + O2);
-            if (om != o) A[base[r] + om * LS::ST] = (E1 - O1) + (O2 - E2);
-        }
-    }
-}
-
-// PF: the lane's geometric factors are loaded at the start of the element group (as in k_apply);
-// otherwise in the pointwise stage, keeping their registers free through the forward stages.
-template <int P, int Q, bool VARK, typename T, int G, int NT, bool PF, bool DET>
-__global__ void __launch_bounds__(NT)
-k_apply_gf(const T *__restrict__ bas, const int nex, const int nvec, const int32_t *__restrict__ offsets,
-           const T *__restrict__ qdata, const double *__restrict__ kappa, const T *__restrict__ x, T *__restrict__ y,
-           T *__restrict__ ebuf)
-{
-    constexpr int Q2 = Q * Q, Q3 = Q2 * Q;
-    constexpr int NPT = G * Q3, RQ = (NPT + NT - 1) / NT;
-    using L = Lds<Q>;
-    extern __shared__ __align__(16) unsigned char smem_raw[];
-    T *const A = reinterpret_cast<T *>(smem_raw);
-    T *const Bb = A + G * L::BUF;
-    T *const C = Bb + G * L::BUF;
-    const int tid = threadIdx.x;
-    const GroupPos gpos = group_pos<G>(xcd_block(blockIdx.x, gridDim.x), nex);
-    const int64_t e0 = gpos.e0;
-    const int nvalid = gpos.nvalid;
-
-    int32_t off[NodeIO<P, G, NT, 1>::NR];
-    load_offsets<P, G, NT, 1>(off, offsets, e0, nvalid, tid);
-
-    // factors of the points of this lane (elements past the end of the row read the first element's)
-    auto load_factors = [&](T (&qv)[RQ][kQdDiff]) {
-#pragma unroll
-        for (int k = 0; k < RQ; ++k) {
-            const int id = tid + k * NT < NPT ? tid + k * NT : NPT - 1;
-            const int g = id / Q3, pt = id - g * Q3;
-            const int64_t e = g < nvalid ? e0 + g : e0;
-            const T *qd = qdata + e * (kQdDiff * Q3) + pt;
-#pragma unroll
-            for (int m = 0; m < kQdDiff; ++m) qv[k][m] = __builtin_nontemporal_load(&qd[m * Q3]);
-            if constexpr (VARK) {
-                const T kap = T(kappa[e * Q3 + pt]);
-#pragma unroll
-                for (int m = 0; m < kQdDiff; ++m) qv[k][m] *= kap;
-            }
-        }
-    };
-    T qv[RQ][kQdDiff];
-    if constexpr (PF) load_factors(qv);
-
-    for (int v0 = 0; v0 < nvec; ++v0) {
-        gather<P, Q, G, NT, 1, T>(A, off, x, nvec, v0, nvalid, tid);
-        group_sync<NT>();
-        gf_z<P, Q, G, NT, T>(A, Bb, bas, tid);
-        group_sync<NT>();
-        gf_y<P, Q, G, NT, T>(A, Bb, C, bas, tid);
-        if constexpr (!PF) {
-            if (v0 == 0) load_factors(qv);
-        }
-        group_sync<NT>();
-        gf_x<P, Q, G, NT, T>(A, Bb, C, bas, tid);
-        group_sync<NT>();
-#pragma unroll
-        for (int k = 0; k < RQ; ++k) {
-            const int id = tid + k * NT;
-            if (id < NPT) {
-                const int g = id / Q3, pt = id - g * Q3;
-                const int a = pt % Q, b = (pt / Q) % Q, c = pt / Q2;
-                const int ls = g * L::BUF + a + L::PITCH * b + L::PLANE * c;
-                const T *gm = qv[k];
-                const T ur = A[ls], us = C[ls], ut = Bb[ls];
-                A[ls] = gm[0] * ur + gm[5] * us + gm[4] * ut;
-                C[ls] = gm[5] * ur + gm[1] * us + gm[3] * ut;
-                Bb[ls] = gm[4] * ur + gm[3] * us + gm[2] * ut;
-            }
-        }
-        group_sync<NT>();
-        gf_xt<P, Q, G, NT, T>(A, Bb, C, bas, tid);
-        group_sync<NT>();
-        gf_yt<P, Q, G, NT, T>(A, Bb, C, bas, tid);
-        group_sync<NT>();
-        gf_zt<P, Q, G, NT, T>(A, Bb, bas, tid);
-        group_sync<NT>();
-        scatter_add<P, Q, G, NT, 1, DET, T>(A, off, y, nvec, v0, nvalid, tid, ebuf, e0);
-        group_sync<NT>();
-    }
-}
-
-// ---------------------------------------------------------------------------
 // Host launchers for one (P, Q) pair.
 // ---------------------------------------------------------------------------
 template <typename K>
@@ -1417,16 +985,66 @@ static hipError_t prepare_lds(K kernel, size_t lds)
     return hipSuccess;
 }
 
-template <int P, int Q, bool COLLOC, int MODE, bool VARK, typename T, int V, bool OTF, bool DET>
-static hipError_t launch_apply_v(const ApplyLaunch &a)
+// Elements a thread group marches through: a pipeline depth that was asked for (mass); else at most the default
+// depth (mass) or 8, and no more than leave four
+// rounds of resident groups on the chip (16384 wavefronts), since a march trades parallelism for carried faces.
+// (p = 3, 5, 7 at 1e7 nodes: 2, 4 and 8 within 3%, 16 up to 10% slower.)
+static int line_march(const ApplyLaunch &a, int64_t columns, int nt)
+{
+    const int64_t cap = a.mode == kMass ? a.chain : 8;
+    int64_t m = columns * a.v.ney * (nt / 64) / 16384;
+    m = m < cap && (a.mode != kMass || a.auto_chain) ? m : cap;
+    m = m < a.v.ney ? m : a.v.ney;
+    return (int)(m < 1 ? 1 : m);
+}
+
+// The line-fused kernel.
+template <int P, int Q, bool COLLOC, int MODE, bool VARK, typename T, int V, bool DET>
+static hipError_t launch_line_v(const ApplyLaunch &a)
+{
+    constexpr int G = kLineG[Q - 2][line_slot(V)], NT = line_nt(Q, G);
+    constexpr size_t lds = line_lds<P, Q, T>(MODE, G);
+    static_assert(lds <= kMaxLds, "LDS of a line-fused group");
+    LineArgs<T> k{};
+    k.bas = static_cast<const T *>(a.basis_dev);
+    k.bas64 = a.basis64;
+    k.vert = a.vert;
+    k.kappa = a.v.kappa;
+    k.x = static_cast<const T *>(a.x);
+    k.y = static_cast<T *>(a.y);
+    k.ebuf = static_cast<T *>(a.ebuf);
+    k.nex = a.v.nex;
+    k.ney = a.v.ney;
+    k.nez = a.v.nez;
+    k.dirichlet = a.dirichlet;
+    k.nvec = a.nvec;
+    k.ngx = (a.v.nex + G - 1) / G;
+    k.march = line_march(a, (int64_t)k.ngx * a.v.nez * a.nvec, NT);
+    k.nych = (a.v.ney + k.march - 1) / k.march;
+    const int64_t nblk = (int64_t)k.ngx * k.nych * a.v.nez;
+    auto go = [&](auto kern) {
+        const hipError_t e = prepare_lds(kern, lds);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(kern, dim3((unsigned)nblk, (unsigned)a.nvec), dim3(NT), lds, a.stream, k);
+        return hipGetLastError();
+    };
+    // byte offsets inside a slab of P planes of nodes: 32 bits unless the slab is that large
+    const int64_t slab = (int64_t)P * (a.v.nex * (P - 1) + 1) * (a.v.ney * (int64_t)(P - 1) + 1) * a.nvec * (int64_t)sizeof(T);
+    if (slab < (int64_t)1 << 31) return go(k_line<P, Q, COLLOC, MODE, VARK, T, G, NT, DET, uint32_t>);
+    return go(k_line<P, Q, COLLOC, MODE, VARK, T, G, NT, DET, int64_t>);
+}
+
+// The element-at-a-time kernels with stored factors (k_apply, k_mass).
+template <int P, int Q, bool COLLOC, int MODE, bool VARK, typename T, int V, bool DET>
+static hipError_t launch_element_v(const ApplyLaunch &a)
 {
     constexpr int G = variant_g(Q, V, MODE), NT = variant_nt(Q, V), VC = variant_vc(V);
-    constexpr size_t lds = apply_lds(P, Q, MODE, sizeof(T), V, OTF);
+    constexpr size_t lds = apply_lds(P, Q, MODE, sizeof(T), V);
     // matrix-core gradient: collocated FP64 diffusion with stored factors
     constexpr bool MX = variant_mx(V);
-    constexpr bool mx_ok = COLLOC && MODE == kDiff && sizeof(T) == 8 && !OTF && !VARK;
+    constexpr bool mx_ok = COLLOC && MODE == kDiff && sizeof(T) == 8 && !VARK;
     // chunked multi-vector variants exist for the plain mass / diffusion operators only
-    if constexpr ((VC > 1 && (MODE == kRhs || VARK || OTF)) || lds > kMaxLds || (MX && !mx_ok)) {
+    if constexpr ((VC > 1 && (MODE == kRhs || VARK)) || lds > kMaxLds || (MX && !mx_ok)) {
         (void)a;
         return hipErrorInvalidValue;
     } else if constexpr (MODE == kMass) {
@@ -1446,63 +1064,43 @@ static hipError_t launch_apply_v(const ApplyLaunch &a)
             const hipError_t e = prepare_lds(kern, lds_bytes);
             if (e != hipSuccess) return e;
             hipLaunchKernelGGL(kern, dim3((unsigned)nblk), dim3(NT), lds_bytes, a.stream,
-                               static_cast<const T *>(a.basis_dev), a.v.nex, a.v.ney, a.nvec, a.v.offsets,
-                               static_cast<const T *>(a.v.qdata), a.v.kappa, a.wdet, a.vert,
+                               static_cast<const T *>(a.basis_dev), a.v.nex, a.nvec, a.v.offsets,
+                               static_cast<const T *>(a.v.qdata), a.v.kappa, a.wdet,
                                static_cast<const T *>(a.x), static_cast<T *>(a.y), static_cast<T *>(a.ebuf));
             return hipGetLastError();
         };
         // several chunks per launch: staged scatter in runs of at least 64 bytes per node
-        if constexpr (staged_scatter(MODE, VC, sizeof(T)) && !DET && !VARK && !OTF) {
-            constexpr size_t lds_st = apply_lds(P, Q, MODE, sizeof(T), V, OTF, true);
+        if constexpr (staged_scatter(MODE, VC, sizeof(T)) && !DET && !VARK) {
+            constexpr size_t lds_st = apply_lds(P, Q, MODE, sizeof(T), V, true);
             if constexpr (lds_st <= kMaxLds) {
                 if (a.nvec > VC)
-                    return go(k_apply<P, Q, COLLOC, MODE, VARK, T, G, NT, VC, OTF, DET, true, 0, MX>, lds_st);
+                    return go(k_apply<P, Q, COLLOC, MODE, VARK, T, G, NT, VC, DET, true, 0, MX>, lds_st);
             }
         }
-        constexpr int LATE = MODE == kDiff && VC == 1 && !OTF ? variant_late(Q, V) : 0;
+        constexpr int LATE = MODE == kDiff && VC == 1 ? variant_late(Q, V) : 0;
         constexpr int PRE = LATE > 0 ? variant_pre(Q, V) : 0;
-        return go(k_apply<P, Q, COLLOC, MODE, VARK, T, G, NT, VC, OTF, DET, false, LATE, MX, PRE>, lds);
+        return go(k_apply<P, Q, COLLOC, MODE, VARK, T, G, NT, VC, DET, false, LATE, MX, PRE>, lds);
     }
 }
 
 template <int P, int Q, bool COLLOC, int MODE, bool VARK, typename T, int V, bool OTF, bool DET>
-static hipError_t launch_apply_gfv(const ApplyLaunch &a)
+static hipError_t launch_apply_v(const ApplyLaunch &a)
 {
-    // the factored-gradient kernel: diffusion with Gauss points (not collocated), stored factors
-    if constexpr (MODE != kDiff || COLLOC || OTF) {
-        (void)a;
-        return hipErrorInvalidValue;
-    } else {
-        constexpr int G = variant_g(Q, V, MODE), NT = variant_nt(Q, V);
-        constexpr bool PF = gf_prefetch(V);
-        constexpr size_t lds = apply_lds(P, Q, MODE, sizeof(T), V, OTF);
-        if constexpr (lds > kMaxLds) {
-            (void)a;
-            return hipErrorInvalidValue;
-        } else {
-            const int64_t nblk = (int64_t)a.v.ney * a.v.nez * ((a.v.nex + G - 1) / G);
-            auto kern = k_apply_gf<P, Q, VARK, T, G, NT, PF, DET>;
-            const hipError_t e = prepare_lds(kern, lds);
-            if (e != hipSuccess) return e;
-            hipLaunchKernelGGL(kern, dim3((unsigned)nblk), dim3(NT), lds, a.stream,
-                               static_cast<const T *>(a.basis_dev), a.v.nex, a.nvec, a.v.offsets,
-                               static_cast<const T *>(a.v.qdata), a.v.kappa, static_cast<const T *>(a.x),
-                               static_cast<T *>(a.y), static_cast<T *>(a.ebuf));
-            return hipGetLastError();
-        }
-    }
+    if constexpr (line_variant(MODE, COLLOC, OTF, V)) return launch_line_v<P, Q, COLLOC, MODE, VARK, T, V, DET>(a);
+    else if constexpr (variant_gf(V) || OTF) return hipErrorInvalidValue;
+    else return launch_element_v<P, Q, COLLOC, MODE, VARK, T, V, DET>(a);
 }
 
 template <int P, int Q, bool COLLOC, int MODE, bool VARK, typename T, bool OTF, bool DET>
 static hipError_t launch_apply_vd(const ApplyLaunch &a)
 {
     switch (a.variant) {
-    case 9: return launch_apply_gfv<P, Q, COLLOC, MODE, VARK, T, 9, OTF, DET>(a);
-    case 10: return launch_apply_gfv<P, Q, COLLOC, MODE, VARK, T, 10, OTF, DET>(a);
-    case 11: return launch_apply_gfv<P, Q, COLLOC, MODE, VARK, T, 11, OTF, DET>(a);
-    case 12: return launch_apply_gfv<P, Q, COLLOC, MODE, VARK, T, 12, OTF, DET>(a);
-    case 13: return launch_apply_gfv<P, Q, COLLOC, MODE, VARK, T, 13, OTF, DET>(a);
-    case 14: return launch_apply_gfv<P, Q, COLLOC, MODE, VARK, T, 14, OTF, DET>(a);
+    case 9: return launch_apply_v<P, Q, COLLOC, MODE, VARK, T, 9, OTF, DET>(a);
+    case 10: return launch_apply_v<P, Q, COLLOC, MODE, VARK, T, 10, OTF, DET>(a);
+    case 11: return launch_apply_v<P, Q, COLLOC, MODE, VARK, T, 11, OTF, DET>(a);
+    case 12: return launch_apply_v<P, Q, COLLOC, MODE, VARK, T, 12, OTF, DET>(a);
+    case 13: return launch_apply_v<P, Q, COLLOC, MODE, VARK, T, 13, OTF, DET>(a);
+    case 14: return launch_apply_v<P, Q, COLLOC, MODE, VARK, T, 14, OTF, DET>(a);
     case 8: return launch_apply_v<P, Q, COLLOC, MODE, VARK, T, 8, OTF, DET>(a);
     case 0: return launch_apply_v<P, Q, COLLOC, MODE, VARK, T, 0, OTF, DET>(a);
     case 1: return launch_apply_v<P, Q, COLLOC, MODE, VARK, T, 1, OTF, DET>(a);

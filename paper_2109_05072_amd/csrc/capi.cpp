@@ -161,11 +161,12 @@ bool valid_variant(const mfhex_op_s &op, int prec, int variant)
     if (variant_vc(variant) > 1 && op.d.variable_kappa) return false;
     const bool otf = (op.d.flags & MFHEX_FLAG_OTF) != 0;
     if (otf && variant_vc(variant) > 1) return false;  // in-kernel factors: single-vector variants
-    // the factored-gradient kernel: diffusion with Gauss points and stored factors
+    // the line-fused diffusion variants of operators whose 0 .. 4 read stored factors
     if (variant_gf(variant) && (mode_of(op) != kDiff || op.basis.colloc || otf)) return false;
     // the matrix-core gradient: collocated FP64 diffusion with stored factors
     if (variant_mx(variant) && (mode_of(op) != kDiff || !op.basis.colloc || otf || prec != MFHEX_F64)) return false;
-    return apply_lds(op.P, op.Q, mode_of(op), prec == MFHEX_F32 ? 4 : 8, variant, otf) <= kMaxLds;
+    if (line_variant(mode_of(op), op.basis.colloc, otf, variant)) return true;
+    return apply_lds(op.P, op.Q, mode_of(op), prec == MFHEX_F32 ? 4 : 8, variant) <= kMaxLds;
 }
 
 int default_variant(const mfhex_op_s &op, int prec, int nvec)
@@ -174,10 +175,25 @@ int default_variant(const mfhex_op_s &op, int prec, int nvec)
     // several: the largest chunk that fits the LDS budget and does not exceed
     // the vector count
     if (nvec <= 1) {
-        const int v = (mode_of(op) == kMass            ? kDefVariantMass
-                       : prec == MFHEX_F32 ? kDefVariantDiff32
-                                           : kDefVariantDiff)[op.Q - 2];
-        return valid_variant(op, prec, v) ? v : 0;
+        const int mode = mode_of(op);
+        const bool otf = (op.d.flags & MFHEX_FLAG_OTF) != 0, coll = op.basis.colloc;
+        if (mode == kMass && coll) {
+            const int v = kDefVariantMassColl[op.Q - 2];
+            return valid_variant(op, prec, v) ? v : 0;
+        }
+        int slot = 0;
+        if (prec == MFHEX_F32 && mode == kDiff) {
+            slot = (coll ? kLineSlot32Coll : kLineSlot32Gauss)[op.Q - 2];
+        } else {
+            const int *cost = (mode == kMass ? kLineCostMass : coll ? kLineCostColl : kLineCostDiff)[op.Q - 2];
+            int64_t best = INT64_MAX;
+            for (int i = 0; i < 5; ++i) {
+                const int G = kLineG[op.Q - 2][i];
+                const int64_t t = (int64_t)cost[i] * ((op.d.nex + G - 1) / G) * G;
+                if (t < best) best = t, slot = i;
+            }
+        }
+        return line_variant(mode, coll, otf, slot) ? slot : 9 + slot;
     }
     // (with the scatter staging that several chunks need, the chunk must still leave room for two
     // thread groups per compute unit)
@@ -185,7 +201,7 @@ int default_variant(const mfhex_op_s &op, int prec, int nvec)
     for (int v = 8; v >= 5; --v) {  // the multi-vector chunk variants
         if (variant_vc(v) > nvec || !valid_variant(op, prec, v)) continue;
         const bool stage = nvec > variant_vc(v);
-        if (apply_lds(op.P, op.Q, mode_of(op), eb, v, false, stage) <= kLdsTwoGroups) return v;
+        if (apply_lds(op.P, op.Q, mode_of(op), eb, v, stage) <= kLdsTwoGroups) return v;
     }
     for (int v = 8; v >= 5; --v)
         if (variant_vc(v) <= nvec && valid_variant(op, prec, v)) return v;
@@ -194,7 +210,10 @@ int default_variant(const mfhex_op_s &op, int prec, int nvec)
 
 // Pipeline depth: the mass kernel chains the measured best number of element
 // groups per thread group; the diffusion kernel takes one.
-int default_chain(const mfhex_op_s &op) { return mode_of(op) == kMass ? kDefChainMass[op.Q - 2] : 1; }
+int default_chain(const mfhex_op_s &op)
+{
+    return mode_of(op) != kMass ? 1 : (op.basis.colloc ? kDefChainMassColl : kDefChainMass)[op.Q - 2];
+}
 
 LaunchCfg config_for(const mfhex_op_s &op, int prec, int nvec)
 {
@@ -301,12 +320,15 @@ int apply_impl(mfhex_op op, int prec, int nrhs, const void *x, void *y, hipStrea
     a.P = op->P;
     a.colloc = op->basis.colloc;
     a.basis_dev = prec == MFHEX_F32 ? (const void *)op->basis32 : (const void *)op->basis64;
+    a.basis64 = op->basis64;
+    a.dirichlet = op->d.dirichlet;
     a.prec = prec;
     a.mode = mode_of(*op);
     a.vark = op->d.variable_kappa;
     a.nvec = nvec;
     a.variant = var;
     a.chain = nchain;
+    a.auto_chain = chain <= 0 && op->config.find({prec, nvec}) == op->config.end();
     a.otf = (op->d.flags & MFHEX_FLAG_OTF) != 0;
     a.vert = op->vert;
     a.x = x;
@@ -605,8 +627,10 @@ int mfhex_get_config(mfhex_op op, int prec, int nrhs, int32_t *variant, int32_t 
     if (!op || nrhs < 1) return fail(MFHEX_ERR_ARG, "bad argument");
     const LaunchCfg c = config_for(*op, prec, nrhs * op->d.ncomp);
     if (variant) *variant = c.variant;
-    if (elems_per_group) *elems_per_group = variant_g(op->Q, c.variant, mode_of(*op));
-    if (threads_per_group) *threads_per_group = variant_nt(op->Q, c.variant);
+    const bool line = line_variant(mode_of(*op), op->basis.colloc, (op->d.flags & MFHEX_FLAG_OTF) != 0, c.variant);
+    const int g = line ? kLineG[op->Q - 2][line_slot(c.variant)] : variant_g(op->Q, c.variant, mode_of(*op));
+    if (elems_per_group) *elems_per_group = g;
+    if (threads_per_group) *threads_per_group = line ? line_nt(op->Q, g) : variant_nt(op->Q, c.variant);
     if (groups_per_block) *groups_per_block = c.chain;
     return MFHEX_OK;
 }

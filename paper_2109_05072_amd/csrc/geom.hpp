@@ -51,6 +51,25 @@ __device__ __forceinline__ void map_point(const Elem8 &el, double r, double s, d
     }
 }
 
+// Trilinear coefficients of one element, [m - 1][component], m = 1..7 the exponents (r, s, t) as bits:
+// x(r, s, t) = sum_m c_m r^(m&1) s^(m>>1&1) t^(m>>2) + constant.
+constexpr int kTriCoef = 21;
+
+// Coefficient m of one component: X is the component at the corner (0, 0, 0) of the lower y-plane, offsets y0 and
+// y1 lead to the two y-planes, 3 to the next corner in x and sz in z.  Edge vectors along the lowest axis of m
+// first (differences of near-equal positions lose nothing), then their signed average.
+__device__ __forceinline__ double tri_coef(const double *X, int y0, int y1, int sz, int m)
+{
+    const bool mx = m & 1, my = m & 2, mz = m & 4;
+    // the axis, then the other two axes with their signs on the low corner
+    const int step = mx ? 3 : my ? y1 - y0 : sz;
+    const int u = mx ? y1 - y0 : 3, v = mx || my ? sz : y1 - y0;
+    const double su = (mx ? my : mx) ? -1.0 : 1.0, sv = (mx || my ? mz : my) ? -1.0 : 1.0;
+    const double *b = X + y0;
+    const double e0 = b[step] - b[0], e1 = b[u + step] - b[u], e2 = b[v + step] - b[v], e3 = b[u + v + step] - b[u + v];
+    return 0.125 * ((e3 + su * e2) + sv * (e1 + su * e0));
+}
+
 // One Jacobian column: DIR 0: dx/dr at (s, t) = (u, w); DIR 1: dx/ds at (r, t);
 // DIR 2: dx/dt at (r, s).  X(v) returns coordinate d of corner v.
 template <int DIR, typename VX>

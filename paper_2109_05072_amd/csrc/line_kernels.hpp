@@ -1,0 +1,668 @@
+// Line-fused operator kernel: the whole element operator in five register stages.
+//
+// Every stage owns whole lines of an element in registers and does all the
+// work that needs only that line before it goes back to LDS:
+//   Y    gather an y-line of nodes straight from x; B and D^B along y
+//        (D^B = l_i'(x_a), the basis derivative at the points)
+//   X    B and D^B along x
+//   Z    B and D^B along z: the reference gradient of a z-line of points is
+//        now in registers; the pointwise factors act there, and the transposed
+//        z contraction follows from the same registers
+//   X^T, Y^T  the transposed contractions; the element values of an y-line of
+//        nodes leave Y^T in registers, straight into the scatter
+// With Gauss-Lobatto points at the nodes B is the identity: Y forms d/ds, X
+// d/dr, Z d/dt, then the same way back.  The mass operator carries one array
+// through the same stages.  Four barriers an element instead of thirteen and
+// 15-17 LDS accesses a point instead of about 26 (Gauss).
+//
+// Pointwise stage: no stored factors.  The map is trilinear, so along a z-line (r, s fixed) the
+// Jacobian columns are j_r, j_s linear in t and j_t constant: a lane forms them
+// once per line from the element's seven trilinear coefficients and evaluates
+// v = (w / detJ) adj(J) adj(J)^T u from cross products, about 55 FP64
+// operations a point in place of 48 bytes of HBM (in FP64 also when x and y
+// are FP32: the same result as factors rounded to FP32, or closer).
+//
+// A thread group owns G elements consecutive in x and marches along y: the
+// y-face shared by consecutive elements is carried in registers (one load and
+// one atomic fewer per line), the next element's x lines and vertices load
+// behind the transposed stages.  Node numbers and Dirichlet masks follow from
+// the position in the structured mesh, so no restriction offsets are read.
+//
+// Measured on MI355X, about 1e7 nodes, FP64, us an apply with its output fill, stored-factor kernel
+// (k_apply / k_mass, the best variant) -> this kernel: BP3 p = 1..8 2610 -> 1636, 720 -> 457, 474 -> 285,
+// 383 -> 248, 334 -> 228, 287 -> 194, 294 -> 191, 270 -> 203; BP1 p = 3..8 198 -> 138, 200 -> 122,
+// 152 -> 127, 168 -> 115, 166 -> 119, 160 -> 126.  HBM traffic is within 1.45 of x and y (p = 3: 90 MB
+// read, 135 MB written); the FP64 pipes are busy 61% of the time (p = 3) and bound it: about 109 FP64
+// operations a point at p = 3, 55 of them geometry.  (Coefficients read from a table of 168 bytes an
+// element instead of formed from the vertices: 253 us at p = 3; not kept, the workspace has no room.)
+#pragma once
+
+#include "geom.hpp"
+#include "mfhex_internal.h"
+
+namespace mfhex {
+
+// The 1D matrices are read through the scalar cache: constant address space, uniform addresses.
+template <typename T>
+using cptr = const __attribute__((address_space(4))) T *;
+
+template <typename T>
+using gptr = __attribute__((address_space(1))) T *;
+__device__ __forceinline__ void global_add(gptr<double> p, double v) { __builtin_amdgcn_global_atomic_fadd_f64(p, v); }
+__device__ __forceinline__ void global_add(gptr<float> p, float v) { __builtin_amdgcn_global_atomic_fadd_f32(p, v); }
+
+// Keeps the loads of one stage from being hoisted out of the march (there are more coefficients
+// than scalar registers).
+template <typename T>
+__device__ __forceinline__ cptr<T> opaque(cptr<T> p)
+{
+    asm volatile("" : "+s"(p));
+    return p;
+}
+
+// Orders the coefficient loads of a row behind a value of an earlier row, so that at most two rows are in flight:
+// issued all at once they would not fit the scalar registers (used where the matrices exceed them).
+template <typename T>
+__device__ __forceinline__ cptr<T> after(cptr<T> p, const T &v)
+{
+    asm volatile("" : "+s"(p) : "v"(v));
+    return p;
+}
+constexpr bool rows_in_flight(int NI, int NO, int bytes) { return 2 * ((NO + 1) / 2) * NI * bytes > 256; }
+
+// A line of N values, folded: e_i = v_i + v_{N-1-i}, d_i = v_i - v_{N-1-i} (i < N/2), e_{N/2} = the middle value.
+template <int N, typename T>
+struct Folded {
+    static constexpr int H = N / 2, MID = N & 1;
+    T e[H + MID];
+    T d[H > 0 ? H : 1];
+    __device__ __forceinline__ void set(const T (&v)[N])
+    {
+#pragma unroll
+        for (int i = 0; i < H; ++i) {
+            e[i] = v[i] + v[N - 1 - i];
+            d[i] = v[i] - v[N - 1 - i];
+        }
+        if constexpr (MID) e[H] = v[H];
+    }
+};
+
+// Output pair (o, NO-1-o) of a contraction of a folded line; SYM +1: M[NO-1-o][NI-1-i] = M[o][i], -1: = -M[o][i].
+template <int NI, int NO, int SYM, typename T>
+__device__ __forceinline__ void line_pair(cptr<T> M, const Folded<NI, T> &f, int o, T &lo, T &hi)
+{
+    constexpr int H = NI / 2;
+    const cptr<T> row = M + o * NI;
+    T E = T(0), O = T(0);
+    const bool middle = 2 * o + 1 == NO;  // one output: only its even (SYM +1) or odd (-1) half is non-zero
+#pragma unroll
+    for (int i = 0; i < H; ++i) {
+        if (!middle || SYM > 0) E += row[i] * f.e[i];
+        if (!middle || SYM < 0) O += row[H + i] * f.d[i];
+    }
+    if constexpr (NI & 1)
+        if (!middle || SYM > 0) E += row[2 * H] * f.e[H];
+    lo = E + O;
+    hi = SYM > 0 ? E - O : O - E;
+}
+
+// All output pairs of a contraction: put(o, lo, hi).
+template <int NI, int NO, int SYM, typename T, typename Put>
+__device__ __forceinline__ void line_all(cptr<T> M, const Folded<NI, T> &f, Put put)
+{
+    constexpr bool TIE = rows_in_flight(NI, NO, sizeof(T));
+    if (TIE) M = after<T>(M, f.e[0]);
+    cptr<T> cur = M, next = M;
+#pragma unroll
+    for (int o = 0; o < (NO + 1) / 2; ++o) {
+        T lo, hi;
+        line_pair<NI, NO, SYM>(cur, f, o, lo, hi);
+        cur = next;
+        if (TIE) next = after<T>(M, lo);
+        put(o, lo, hi);
+    }
+}
+
+// Transposed contraction of a line of NO values with the same folded rows, accumulated over several matrices:
+// out_i = S_i + D_i, out_{NI-1-i} = S_i - D_i.
+template <int NI, typename T>
+struct TransAcc {
+    static constexpr int H = NI / 2, MID = NI & 1;
+    T S[H + MID], D[H > 0 ? H : 1];
+    __device__ __forceinline__ void zero()
+    {
+#pragma unroll
+        for (int i = 0; i < H + MID; ++i) S[i] = T(0);
+#pragma unroll
+        for (int i = 0; i < H; ++i) D[i] = T(0);
+    }
+    template <int NO, int SYM>
+    __device__ __forceinline__ void add(cptr<T> M, const T (&w)[NO])
+    {
+        constexpr bool TIE = rows_in_flight(NI, NO, sizeof(T));
+        if (TIE) M = after<T>(M, w[0]);
+        cptr<T> cur = M, next = M;
+#pragma unroll
+        for (int o = 0; o < NO / 2; ++o) {
+            const T e = w[o] + w[NO - 1 - o], d = w[o] - w[NO - 1 - o];
+            const T s = SYM > 0 ? e : d, t = SYM > 0 ? d : e;
+            const cptr<T> row = cur + o * NI;
+#pragma unroll
+            for (int i = 0; i < H; ++i) {
+                S[i] += row[i] * s;
+                D[i] += row[H + i] * t;
+            }
+            if constexpr (MID) S[H] += row[2 * H] * s;
+            cur = next;
+            if (TIE) {
+                // (every accumulator: a chain of one of them alone could run ahead of the others)
+#pragma unroll
+                for (int i = 0; i < H; ++i) asm volatile("" : "+v"(S[i]), "+v"(D[i]));
+                next = after<T>(M, S[0]);
+            }
+        }
+        if constexpr (NO & 1) {
+            const T m = w[NO / 2];
+            const cptr<T> row = cur + (NO / 2) * NI;
+#pragma unroll
+            for (int i = 0; i < H; ++i) {
+                if (SYM > 0) S[i] += row[i] * m;
+                else D[i] += row[H + i] * m;
+            }
+            if constexpr (MID && SYM > 0) S[H] += row[2 * H] * m;
+        }
+    }
+    __device__ __forceinline__ T out(int i) const
+    {
+        return MID && i == H ? S[H] : i < H ? S[i] + D[i] : S[NI - 1 - i] - D[NI - 1 - i];
+    }
+};
+
+template <int N, int ST, typename T>
+__device__ __forceinline__ void line_read(const T *src, T (&v)[N])
+{
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] = src[i * ST];
+}
+
+// Jacobian columns along the z-line (r, s): jr = jr0 + t jr1, js = js0 + t js1, jt constant.
+struct ZLineGeom {
+    double jr0[3], jr1[3], js0[3], js1[3], jt[3];
+
+    __device__ __forceinline__ void set(const double *c, double r, double s)
+    {
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            jr0[d] = c[d] + s * c[6 + d];          // r, rs
+            jr1[d] = c[12 + d] + s * c[18 + d];    // rt, rst
+            js0[d] = c[3 + d] + r * c[6 + d];      // s, rs
+            js1[d] = c[15 + d] + r * c[18 + d];    // st, rst
+            jt[d] = c[9 + d] + r * c[12 + d] + s * js1[d];
+            // one component's coefficients in registers at a time
+            asm volatile("" : "+v"(jr0[d]), "+v"(jr1[d]), "+v"(js0[d]), "+v"(js1[d]), "+v"(jt[d]), "+v"(r));
+        }
+    }
+    // pins the evaluation order: nothing that uses the columns moves above this point
+    __device__ __forceinline__ void pin()
+    {
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            asm volatile("" : "+v"(jr0[d]), "+v"(jr1[d]), "+v"(js0[d]), "+v"(js1[d]), "+v"(jt[d]));
+        }
+    }
+    __device__ __forceinline__ void columns(double t, double jr[3], double js[3]) const
+    {
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            jr[d] = jr0[d] + t * jr1[d];
+            js[d] = js0[d] + t * js1[d];
+        }
+    }
+    // detJ along the line: d[0] + t (d[1] + t d[2])
+    __device__ __forceinline__ void det_poly(double d[3]) const
+    {
+        double a[3], b[3];
+        cross(jr0, js0, a);
+        d[0] = dot3(jt, a);
+        cross(jr1, js1, a);
+        d[2] = dot3(jt, a);
+        cross(jr0, js1, a);
+        cross(jr1, js0, b);
+        d[1] = dot3(jt, a) + dot3(jt, b);
+    }
+};
+
+// 1 / d by the hardware estimate and two Newton steps (relative error about one unit in the last place).
+__device__ __forceinline__ double fast_rcp(double d)
+{
+    double y = __builtin_amdgcn_rcp(d);
+    y = fma(fma(-d, y, 1.0), y, y);
+    return fma(fma(-d, y, 1.0), y, y);
+}
+
+// v = w adj(J) adj(J)^T u / detJ at parameter t of the line.  With the adjugate rows js x jt, jt x jr and jr x js,
+//   q = adj(J)^T u = jt x (us jr - ur js) + ut (jr x js),
+//   v = (js . (jt x q), -jr . (jt x q), (jr x js) . q) w / detJ,
+// which needs no more than the columns and one cross product at a time in registers.
+__device__ __forceinline__ void apply_geom(const ZLineGeom &g, double t, double w, double &ur, double &us, double &ut)
+{
+    double jr[3], js[3], r2[3], h[3], q[3];
+    g.columns(t, jr, js);
+    cross(jr, js, r2);
+    const double f = w * fast_rcp(dot3(g.jt, r2));
+#pragma unroll
+    for (int d = 0; d < 3; ++d) h[d] = us * jr[d] - ur * js[d];
+    cross(g.jt, h, q);
+#pragma unroll
+    for (int d = 0; d < 3; ++d) q[d] = f * (q[d] + ut * r2[d]);
+    cross(g.jt, q, h);
+    ur = dot3(js, h);
+    us = -dot3(jr, h);
+    ut = dot3(r2, q);
+}
+
+// LDS of one element: arrays [k][b][a] of P planes of Q rows of PITCH entries.
+template <int P, int Q>
+struct LineLds {
+    static constexpr int PITCH = (Q % 2 == 0) ? Q + 1 : Q;
+    static constexpr int PLANE = PITCH * Q;
+    static constexpr int ELEM = P * PLANE;
+};
+constexpr int line_arrays(int mode) { return mode == kMass ? 1 : 3; }
+template <int P, int Q, typename T>
+constexpr size_t line_lds(int mode, int G)
+{
+    return (size_t)line_arrays(mode) * G * LineLds<P, Q>::ELEM * sizeof(T) + ((size_t)G * kTriCoef + 2 * Q + 12 * (G + 1)) * 8;
+}
+
+// Wavefronts per SIMD that the registers are allocated for: the pointwise stage holds the gradient of a z-line
+// (6 Q registers), the columns (30) and one point's work (about 30); four wavefronts (128 registers) fit it up to
+// q = 6 without spills, three (168) above.  (Two at q = 5: 283 against 277 us at p = 3, 1e7 nodes.)
+constexpr int line_waves(int Q, int mode) { return mode == kDiff && Q > 6 ? 3 : 4; }
+
+template <typename T>
+struct LineArgs {
+    const T *bas;
+    const double *bas64;
+    const double *vert, *kappa;
+    const T *x;
+    T *y, *ebuf;
+    int nex, ney, nez, dirichlet, nvec;
+    int ngx, nych, march;  // element groups per row, y-chunks per column, elements per march
+};
+
+// Marching position of a thread group.
+struct LinePos {
+    int ex0, nvalid, ey0, ey1, ez;
+};
+template <int G, typename A>
+__device__ __forceinline__ LinePos line_pos_of(const A &a, unsigned bid, unsigned nb)
+{
+    // XCD x (blocks are dealt round-robin) takes the x-th contiguous range of the groups
+    const unsigned xcd = bid % kNumXcd, nq = nb / kNumXcd, nr = nb % kNumXcd;
+    const unsigned b = xcd * nq + (xcd < nr ? xcd : nr) + bid / kNumXcd;
+    LinePos q;
+    const int gx = (int)(b % (unsigned)a.ngx);
+    const unsigned r = b / (unsigned)a.ngx;
+    q.ex0 = gx * G;
+    q.nvalid = a.nex - q.ex0 < G ? a.nex - q.ex0 : G;
+    q.ey0 = (int)(r % (unsigned)a.nych) * a.march;
+    q.ey1 = q.ey0 + a.march < a.ney ? q.ey0 + a.march : a.ney;
+    q.ez = (int)(r / (unsigned)a.nych);
+    return q;
+}
+
+template <int P, int Q, bool COLLOC, int MODE, bool VARK, typename T, int G, int NT, bool DET, typename OFF>
+__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(line_waves(Q, MODE))))
+k_line(const LineArgs<T> a)
+{
+    static_assert(!(COLLOC && MODE == kMass), "the collocated mass operator has no contractions");
+    using L = LineLds<P, Q>;
+    constexpr int p = P - 1, W = G * p + 1, Q2 = Q * Q, Q3 = Q2 * Q, P3 = P * P * P;
+    constexpr int SX = 1, SY = L::PITCH, SZ = L::PLANE;
+    constexpr int NOH = (Q + 1) / 2;
+    static_assert(G * Q2 <= NT, "one line per lane");
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    T *const A = reinterpret_cast<T *>(smem_raw);
+    T *const Bb = MODE == kMass ? A : A + G * L::ELEM;
+    T *const C = MODE == kMass ? A : Bb + G * L::ELEM;
+    double *const sC = reinterpret_cast<double *>(A + line_arrays(MODE) * G * L::ELEM);
+    const int tid = threadIdx.x;
+    const LinePos pos = line_pos_of<G>(a, blockIdx.x, gridDim.x);
+    const int vec = blockIdx.y;
+    const cptr<T> bas = (cptr<T>)(uintptr_t)a.bas;
+    const int nx = a.nex * p + 1, ny = a.ney * p + 1, nz = a.nez * p + 1;
+
+    // Lane roles, packed into three registers for the whole march (an inactive role has its bit clear):
+    //   X line (row b, plane k) and Z line (a, b): LDS positions; Y line: node column X, plane k
+    static_assert(G * L::ELEM < 1 << 14, "positions in 14 bits");
+    constexpr uint32_t kAct = 1u << 14, kDual = 1u << 15;
+    uint32_t rxz, ry, rz;
+    int X, ky;
+    {
+        ky = tid / W;
+        X = tid - ky * W;
+        int g = 0, i = X;
+        if constexpr (G > 1) {
+            g = X / p;
+            if (g > pos.nvalid - 1) g = pos.nvalid - 1;
+            i = X - g * p;
+        }
+        ry = 0;
+        if (tid < W * P && X <= pos.nvalid * p)
+            ry = (uint32_t)(g * L::ELEM + ky * SZ + i) | kAct | (G > 1 && i == 0 && g > 0 ? kDual : 0u);  // dual: face shared with g-1
+        const int bx = tid % Q, kx = (tid / Q) % P, gx = tid / (Q * P);
+        rxz = 0;
+        if (tid < G * P * Q && gx < pos.nvalid) rxz = (uint32_t)(gx * L::ELEM + kx * SZ + bx * SY) | kAct;
+        const int az = tid % Q, bz = (tid / Q) % Q, gz = tid / Q2;
+        if (tid < G * Q2 && gz < pos.nvalid) rxz |= ((uint32_t)(gz * L::ELEM + bz * SY + az) | kAct) << 16;
+        rz = (uint32_t)az | (uint32_t)bz << 4 | (uint32_t)gz << 8;
+    }
+    const auto at = [](uint32_t r) { return (int)(r & (kAct - 1)); };
+    // the group's first node is uniform; a lane adds its own offset (OFF: 32 bits where a slab of P planes allows)
+    const int64_t stride = (int64_t)nx * a.nvec;
+    const int64_t node0 = (((int64_t)pos.ez * p * ny + (int64_t)pos.ey0 * p) * nx + (int64_t)pos.ex0 * p) * a.nvec + vec;
+    const T *xb = a.x + node0;
+    T *yb = DET ? nullptr : a.y + node0;
+    const int I = pos.ex0 * p + X, K = pos.ez * p + ky;
+    const bool io = (ry & kAct) && !(a.dirichlet && (I == 0 || I == nx - 1 || K == 0 || K == nz - 1));
+    const OFF lane0 = ((OFF)ky * (OFF)ny * (OFF)nx + (OFF)X) * (OFF)a.nvec;
+
+    T xv[P], carry = T(0);
+#pragma unroll
+    for (int j = 0; j < P; ++j) xv[j] = io ? (xb + j * stride)[lane0] : T(0);
+
+    // Vertices: two y-planes of 2 (G + 1) vertices in LDS, used in turn; a march loads one plane per element.  The
+    // elements' trilinear coefficients are formed from them in the X stage.
+    constexpr int VP = 6 * (G + 1), RV = (VP + NT - 1) / NT, RC = (G * kTriCoef + NT - 1) / NT;
+    double *const sV = sC + G * kTriCoef + 2 * Q;
+    double vtx[RV];
+    auto vtx_load = [&](int vy) {
+#pragma unroll
+        for (int r = 0; r < RV; ++r) {
+            const int t = tid + r * NT, z = t / (VP / 2), c = t - z * (VP / 2);
+            if (t < VP && c < 3 * (pos.nvalid + 1))
+                vtx[r] = a.vert[3 * (pos.ex0 + (int64_t)(a.nex + 1) * (vy + (int64_t)(a.ney + 1) * (pos.ez + z))) + c];
+        }
+    };
+    auto vtx_store = [&](int vy) {
+#pragma unroll
+        for (int r = 0; r < RV; ++r)
+            if (tid + r * NT < VP) sV[(vy & 1) * VP + tid + r * NT] = vtx[r];
+    };
+    vtx_load(pos.ey0);
+    vtx_store(pos.ey0);
+    vtx_load(pos.ey0 + 1);
+    // points, then weights (contiguous in the basis block)
+    double *const sR = sC + G * kTriCoef;
+    if (tid < 2 * Q) sR[tid] = a.bas64[basis_xq(P, Q) + tid];
+    for (int ey = pos.ey0; ey < pos.ey1; ++ey) {
+        const bool more = ey + 1 < pos.ey1;
+        cptr<T> Bf, Gf;
+        auto matrices = [&]() {
+            const cptr<T> b = opaque<T>(bas);
+            Bf = b + basis_bf(P, Q);
+            Gf = b + (COLLOC ? basis_df(P, Q) : basis_gf(P, Q));
+        };
+        matrices();
+        // --- Y -----------------------------------------------------------------------------
+        vtx_store(ey + 1);
+        if (ry & kAct) {
+            const int ly = at(ry), ly2 = ly - L::ELEM + p;
+            T v[P];
+#pragma unroll
+            for (int j = 0; j < P; ++j) v[j] = xv[j];
+            if (a.dirichlet) {
+                if (ey == 0) v[0] = T(0);
+                if (ey == a.ney - 1) v[P - 1] = T(0);
+            }
+            Folded<P, T> f;
+            f.set(v);
+            auto put = [&](T *arr, int o, T lo, T hi) {
+                arr[ly + o * SY] = lo;
+                if (2 * o + 1 != Q) arr[ly + (Q - 1 - o) * SY] = hi;
+                if (ry & kDual) {
+                    arr[ly2 + o * SY] = lo;
+                    if (2 * o + 1 != Q) arr[ly2 + (Q - 1 - o) * SY] = hi;
+                }
+            };
+            if constexpr (COLLOC) {
+#pragma unroll
+                for (int o = 0; o < NOH; ++o) put(A, o, v[o], v[P - 1 - o]);
+            } else {
+                line_all<P, Q, 1>(Bf, f, [&](int o, T lo, T hi) { put(A, o, lo, hi); });
+            }
+            if constexpr (MODE == kDiff) line_all<P, Q, -1>(Gf, f, [&](int o, T lo, T hi) { put(Bb, o, lo, hi); });
+        }
+        group_sync<NT>();
+        // --- X -----------------------------------------------------------------------------
+#pragma unroll
+        for (int r = 0; r < RC; ++r) {
+            int t = tid + r * NT;
+            asm volatile("" : "+v"(t));  // (addresses not kept through the other stages)
+            if (t < pos.nvalid * kTriCoef) {
+                const int g = t / kTriCoef, c = t - g * kTriCoef, m = c / 3;
+                sC[t] = tri_coef(sV + 3 * g + (c - 3 * m), (ey & 1) * VP, VP - (ey & 1) * VP, VP / 2, m + 1);
+            }
+        }
+        if (rxz & kAct) {
+            const int lx = at(rxz);
+            matrices();
+            T v[P];
+            Folded<P, T> f;
+            auto put = [&](T *arr, int o, T lo, T hi) {
+                arr[lx + o * SX] = lo;
+                if (2 * o + 1 != Q) arr[lx + (Q - 1 - o) * SX] = hi;
+            };
+            line_read<P, SX>(A + lx, v);
+            f.set(v);
+            if constexpr (MODE == kDiff) line_all<P, Q, -1>(Gf, f, [&](int o, T lo, T hi) { put(C, o, lo, hi); });
+            if constexpr (!COLLOC) {
+                line_all<P, Q, 1>(Bf, f, [&](int o, T lo, T hi) { put(A, o, lo, hi); });
+                if constexpr (MODE == kDiff) {
+                    line_read<P, SX>(Bb + lx, v);
+                    f.set(v);
+                    line_all<P, Q, 1>(Bf, f, [&](int o, T lo, T hi) { put(Bb, o, lo, hi); });
+                }
+            }
+        }
+        group_sync<NT>();
+        // --- Z -----------------------------------------------------------------------------
+        if (rxz >> 16 & kAct) {
+            const int lz = at(rxz >> 16), az = rz & 15, bz = rz >> 4 & 15, gz = rz >> 8;
+            const cptr<double> xq = (cptr<double>)(uintptr_t)a.bas64 + basis_xq(P, Q);
+            const cptr<double> wq = (cptr<double>)(uintptr_t)a.bas64 + basis_wq(P, Q);
+            matrices();
+            T v[P];
+            Folded<P, T> f;
+            T ur[Q], us[Q], ut[Q];
+            auto pair_to = [&](T (&u)[Q], int o, T lo, T hi) {
+                u[o] = lo;
+                if (2 * o + 1 != Q) u[Q - 1 - o] = hi;
+            };
+            line_read<P, SZ>(A + lz, v);
+            f.set(v);
+            if constexpr (MODE == kMass) {
+                line_all<P, Q, 1>(Bf, f, [&](int o, T lo, T hi) { pair_to(ut, o, lo, hi); });
+                ZLineGeom g;
+                g.set(sC + gz * kTriCoef, sR[az], sR[bz]);
+                const double wz = sR[Q + az] * sR[Q + bz];
+                double d[3];
+                g.det_poly(d);
+#pragma unroll
+                for (int c = 0; c < Q; ++c) ut[c] *= T((wz * wq[c]) * (d[0] + xq[c] * (d[1] + xq[c] * d[2])));
+                TransAcc<P, T> t;
+                t.zero();
+                t.template add<Q, 1>(Bf, ut);
+#pragma unroll
+                for (int k = 0; k < P; ++k) A[lz + k * SZ] = t.out(k);
+            } else {
+                line_all<P, Q, -1>(Gf, f, [&](int o, T lo, T hi) { pair_to(ut, o, lo, hi); });
+                if constexpr (COLLOC) {
+                    line_read<Q, SZ>(Bb + lz, us);
+                    line_read<Q, SZ>(C + lz, ur);
+                } else {
+                    line_read<P, SZ>(Bb + lz, v);
+                    f.set(v);
+                    line_all<P, Q, 1>(Bf, f, [&](int o, T lo, T hi) { pair_to(us, o, lo, hi); });
+                    line_read<P, SZ>(C + lz, v);
+                    f.set(v);
+                    line_all<P, Q, 1>(Bf, f, [&](int o, T lo, T hi) { pair_to(ur, o, lo, hi); });
+                }
+                const double *kp = nullptr;
+                if constexpr (VARK)
+                    kp = a.kappa + (pos.ex0 + gz + (int64_t)a.nex * (ey + (int64_t)a.ney * pos.ez)) * Q3 + bz * Q + az;
+                ZLineGeom g;
+                g.set(sC + gz * kTriCoef, sR[az], sR[bz]);
+                const double wz = sR[Q + az] * sR[Q + bz];
+#pragma unroll
+                for (int c = 0; c < Q; ++c) {
+                    // one point at a time: evaluated together the points' temporaries would spill
+                    g.pin();
+                    double w = wz * wq[c];
+                    if constexpr (VARK) w *= kp[c * Q2];
+                    double r = ur[c], s = us[c], t = ut[c];
+                    apply_geom(g, xq[c], w, r, s, t);
+                    ur[c] = T(r);
+                    us[c] = T(s);
+                    ut[c] = T(t);
+                    asm volatile("" : "+v"(ur[c]), "+v"(us[c]), "+v"(ut[c]));
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                matrices();
+                TransAcc<P, T> t;
+                t.zero();
+                t.template add<Q, -1>(Gf, ut);
+#pragma unroll
+                for (int k = 0; k < P; ++k) A[lz + k * SZ] = t.out(k);
+                if constexpr (COLLOC) {
+#pragma unroll
+                    for (int k = 0; k < P; ++k) {
+                        Bb[lz + k * SZ] = us[k];
+                        C[lz + k * SZ] = ur[k];
+                    }
+                } else {
+                    t.zero();
+                    t.template add<Q, 1>(Bf, us);
+#pragma unroll
+                    for (int k = 0; k < P; ++k) Bb[lz + k * SZ] = t.out(k);
+                    t.zero();
+                    t.template add<Q, 1>(Bf, ur);
+#pragma unroll
+                    for (int k = 0; k < P; ++k) C[lz + k * SZ] = t.out(k);
+                }
+            }
+        }
+        // the next element's inputs travel behind the transposed stages
+        if (more) {
+            xv[0] = xv[P - 1];
+            xb += p * stride;
+            if (io) {
+                gptr<const T> row = (gptr<const T>)xb;
+#pragma unroll
+                for (int j = 1; j < P; ++j) {
+                    row += stride;
+                    asm volatile("" : "+s"(row));
+                    xv[j] = row[lane0];
+                }
+            }
+            vtx_load(ey + 2);
+        }
+        group_sync<NT>();
+        // --- X^T ---------------------------------------------------------------------------
+        if (rxz & kAct) {
+            const int lx = at(rxz);
+            matrices();
+            T w[Q];
+            TransAcc<P, T> t;
+            t.zero();
+            if constexpr (COLLOC) {
+                line_read<Q, SX>(C + lx, w);
+                t.template add<Q, -1>(Gf, w);
+#pragma unroll
+                for (int i = 0; i < P; ++i) A[lx + i] += t.out(i);
+            } else {
+                line_read<Q, SX>(A + lx, w);
+                t.template add<Q, 1>(Bf, w);
+                if constexpr (MODE == kDiff) {
+                    line_read<Q, SX>(C + lx, w);
+                    t.template add<Q, -1>(Gf, w);
+                }
+#pragma unroll
+                for (int i = 0; i < P; ++i) A[lx + i] = t.out(i);
+                if constexpr (MODE == kDiff) {
+                    line_read<Q, SX>(Bb + lx, w);
+                    t.zero();
+                    t.template add<Q, 1>(Bf, w);
+#pragma unroll
+                    for (int i = 0; i < P; ++i) Bb[lx + i] = t.out(i);
+                }
+            }
+        }
+        group_sync<NT>();
+        // --- Y^T and scatter ---------------------------------------------------------------
+        auto transposed_y = [&](int base, bool two, int base2, T (&out)[P]) {
+            // a column shared by two elements of the group: both elements' lines summed first (the
+            // contraction is linear)
+            matrices();
+            T w[Q];
+            TransAcc<P, T> t;
+            t.zero();
+            auto get = [&](const T *arr) {
+                line_read<Q, SY>(arr + base, w);
+                if (two) {
+#pragma unroll
+                    for (int b = 0; b < Q; ++b) w[b] += arr[base2 + b * SY];
+                }
+            };
+            if constexpr (COLLOC) {
+                get(Bb);
+                t.template add<Q, -1>(Gf, w);
+                get(A);
+#pragma unroll
+                for (int j = 0; j < P; ++j) out[j] = t.out(j) + w[j];
+            } else {
+                get(A);
+                t.template add<Q, 1>(Bf, w);
+                if constexpr (MODE == kDiff) {
+                    get(Bb);
+                    t.template add<Q, -1>(Gf, w);
+                }
+#pragma unroll
+                for (int j = 0; j < P; ++j) out[j] = t.out(j);
+            }
+        };
+        if constexpr (DET) {
+            // element values as they are: one line per element column
+            const int i = tid % P, k = (tid / P) % P, g = tid / (P * P);
+            if (tid < G * P * P && g < pos.nvalid) {
+                T out[P];
+                transposed_y(g * L::ELEM + k * SZ + i, false, 0, out);
+                const int64_t e = pos.ex0 + g + (int64_t)a.nex * (ey + (int64_t)a.ney * pos.ez);
+                T *eb = a.ebuf + (e * P3 + i + P * P * k) * a.nvec + vec;
+#pragma unroll
+                for (int j = 0; j < P; ++j) eb[j * P * a.nvec] = out[j];
+            }
+        } else if (io) {
+            T out[P];
+            transposed_y(at(ry), ry & kDual, at(ry) - L::ELEM + p, out);
+            out[0] += carry;
+            carry = out[P - 1];
+            const bool m0 = a.dirichlet && ey == 0, m1 = a.dirichlet && ey == a.ney - 1;
+            // one row address at a time in scalar registers
+            gptr<T> row = (gptr<T>)yb;
+            if (!m0) global_add(row + lane0, out[0]);
+#pragma unroll
+            for (int j = 1; j < P - 1; ++j) {
+                row += stride;
+                asm volatile("" : "+s"(row) : "v"(out[j]));
+                global_add(row + lane0, out[j]);
+            }
+            if (!more && !m1) global_add(row + stride + lane0, out[P - 1]);
+        }
+        yb += p * stride;
+        if (more) group_sync<NT>();
+    }
+}
+
+}  // namespace mfhex

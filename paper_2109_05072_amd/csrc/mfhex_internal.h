@@ -58,14 +58,17 @@ struct ApplyLaunch {
     OpView v;
     int P, colloc;
     const void *basis_dev; // device basis block (B, B^T, D, D^T) in the apply precision
+    const double *basis64; // the same block in FP64
+    int dirichlet;
     int prec;             // MFHEX_F64 / MFHEX_F32
     int mode;             // kMass / kDiff / kRhs
     int vark;             // multiply the factors by kappa
     int nvec;
     int variant;          // launch variant (elements and threads per group)
     int chain;            // mass: element groups per thread group (software pipeline depth), >= 1
+    bool auto_chain;      // the depth is the operator's default, not one that was asked for
     int otf;              // diffusion FP64: geometric factors evaluated in the kernel from the vertices
-    const double *vert;   // device vertex coordinates [(nex+1)(ney+1)(nez+1)][3] (otf)
+    const double *vert;   // device vertex coordinates [(nex+1)(ney+1)(nez+1)][3] (line-fused kernels)
     const void *x;        // input (for kRhs: the per-point f, FP64)
     void *y;              // output (accumulated)
     const double *wdet;   // kRhs: w*detJ per point
@@ -112,15 +115,14 @@ constexpr bool split_stages(int Q, int mode, int G, int NT, int VC)
     return mode == 1 && VC == 1 && NT >= 256 && 2 * G * Q * Q <= NT;
 }
 
-// Launch variants of the fused kernels for q points per direction: G
-// elements per thread group of NT threads; variant 0 is the default.
-// Variants 0..4 carry one vector at a time through the element (rows: Q = 2
-// .. 10; variant 0 is the measured best on MI355X for one vector); variants
-// 5..8 carry a chunk of VC = 2, 4, 8, 16 vectors of a multi-vector together
-// (one element per group), sharing the geometric factors and reading /
-// writing each node's chunk as one contiguous run.  Variants 9..14 are the
-// factored-gradient kernel (below); 15 and 16 are chunks of 4 and 8 vectors
-// whose collocated gradient contractions run on the FP64 matrix cores.
+// Launch variants of the fused kernels for q points per direction: G elements per thread group of NT
+// threads.  Which kernel a number stands for depends on the operator (line_variant below): the line-fused
+// kernel takes 9 .. 14 of diffusion with Gauss points, and 0 .. 4 of collocated or in-kernel-factor
+// diffusion and of mass with Gauss points.  Variants 0 .. 4 of the other operators carry one vector at a
+// time through the element with stored factors (rows: Q = 2 .. 10); 5 .. 8 carry a chunk of VC = 2, 4, 8,
+// 16 vectors of a multi-vector together (one element per group), sharing the geometric factors and reading
+// / writing each node's chunk as one contiguous run; 15 and 16 are chunks of 4 and 8 vectors whose
+// collocated gradient contractions run on the FP64 matrix cores.
 constexpr int kNumVariants = 17;
 // At q = 6 and 7 variant 4 fills the lanes: every contraction of the diffusion
 // kernel runs over G q^2 lines (q^2 = 36, 49), so 7 and 5 elements per
@@ -134,7 +136,7 @@ constexpr int kNumVariants = 17;
 // wavefronts fit on a SIMD (q = 7..9, two points at a time: 64-72 registers instead of 120-142)
 // while the loads' latency is no longer hidden by the contractions.  At q = 10 this was 6% faster
 // on one box and 5% slower on another against variant 0 with 128 threads.  With 256 threads
-// (split stages) the late loads are the q = 9 and 10 defaults: 68 and 81 registers instead of 101
+// (split stages) the late loads are the fastest stored-factor launches at q = 9 and 10: 68 and 81 registers instead of 101
 // and 126, so that five to six groups fit per CU (at q = 10 with the unpadded row pitch, which
 // puts the four arrays of a group in 32 KB); same-box A/B, one element per group: q = 9 6%
 // faster than the best prefetching variant, q = 10 11%.
@@ -158,41 +160,36 @@ constexpr int variant_vc(int v)
 {
     return v == 15 ? 4 : v == 16 ? 8 : v < 5 || v >= 9 ? 1 : v == 5 ? 2 : v == 6 ? 4 : v == 7 ? 8 : 16;
 }
-// Variants 9 .. 14: the factored-gradient diffusion kernel (Gauss points, one vector at a time;
-// k_apply_gf): 9 .. 13 take the (elements, threads) pairs below per q and load the geometric
-// factors at the start of the element group; 14 is variant 9 loading them in the middle of the
-// forward stages (fewer registers held through the first contractions).
-constexpr int kGfG[9][5] = {{16, 8, 32, 16, 8}, {16, 8, 32, 16, 8}, {8, 4, 16, 8, 4}, {8, 4, 2, 8, 4},
-                            {4, 2, 8, 4, 2},    {2, 1, 4, 2, 1},    {1, 2, 4, 1, 2}, {1, 1, 2, 2, 1},
-                            {1, 1, 2, 2, 1}};
-constexpr int kGfNT[9][5] = {{128, 64, 256, 256, 128}, {128, 64, 256, 256, 128}, {128, 64, 256, 256, 128},
-                             {256, 128, 64, 128, 64},  {128, 64, 256, 256, 128}, {128, 64, 256, 64, 128},
-                             {64, 128, 256, 128, 64},  {128, 64, 256, 128, 256}, {128, 64, 256, 128, 256}};
+// The line-fused kernel (k_line, line_kernels.hpp): variants 9 .. 14 of the diffusion operator with
+// Gauss points, and variants 0 .. 4 of the collocated diffusion, the in-kernel-factor (OTF) and the
+// mass operator with Gauss points.  G q^2 lines in the widest stage, one per lane, so the slots take
+// the (elements, threads) pairs that leave few lanes idle.
+constexpr int kLineG[9][5] = {{16, 32, 8, 64, 4}, {7, 14, 28, 4, 2}, {4, 8, 16, 2, 1}, {5, 10, 2, 4, 1}, {7, 3, 5, 1, 2},
+                              {5, 1, 2, 4, 3},    {2, 1, 4, 3, 1},   {3, 1, 2, 1, 3},  {1, 3, 2, 1, 2}};
+constexpr int line_nt(int Q, int G) { return (G * Q * Q + 63) / 64 * 64; }
+constexpr int line_slot(int v) { return v < 5 ? v : v == 14 ? 0 : v - 9; }
+constexpr bool line_variant(int mode, bool colloc, bool otf, int v)
+{
+    return mode == 0 ? v < 5 && !colloc : mode == 1 && (colloc || otf ? v < 5 : v >= 9 && v <= 14);
+}
 constexpr bool variant_gf(int v) { return v >= 9 && v <= 14; }
-constexpr bool gf_prefetch(int v) { return v != 14; }
-constexpr int gf_slot(int v) { return v == 14 ? 0 : v - 9; }
 // The mass operator keeps one LDS array per element instead of three and has
 // far less work per element, so at low order its single-vector variants
 // carry more elements per group.
 constexpr int mass_group_scale(int Q) { return Q <= 4 ? 4 : Q <= 6 ? 2 : 1; }
 constexpr int variant_g(int Q, int v, int mode = 1)
 {
-    return variant_gf(v) ? kGfG[Q - 2][gf_slot(v)] : v < 5 ? kVarG[Q - 2][v] * (mode == 1 ? 1 : mass_group_scale(Q)) : 1;
+    return v < 5 ? kVarG[Q - 2][v] * (mode == 1 ? 1 : mass_group_scale(Q)) : 1;
 }
 constexpr int variant_nt(int Q, int v)
 {
-    return variant_gf(v) ? kGfNT[Q - 2][gf_slot(v)]
-           : v < 5       ? kVarNT[Q - 2][v]
-                         : (Q * Q * variant_vc(v) <= 64 ? 64 : Q * Q * variant_vc(v) <= 128 ? 128 : 256);
+    return v < 5 ? kVarNT[Q - 2][v]
+                 : (Q * Q * variant_vc(v) <= 64 ? 64 : Q * Q * variant_vc(v) <= 128 ? 128 : 256);
 }
 // Dynamic LDS bytes of one group of the fused apply.
-// In-kernel geometric factors: per element its 8 vertices (24 doubles) and
-// the three Jacobian-column tables (3 x Q^2 columns of 3), plus the 1D rule.
-constexpr int otf_lds_doubles(int Q, int G) { return G * (24 + 9 * Q * Q) + 2 * Q; }
-
 constexpr bool variant_split(int Q, int v, int mode)
 {
-    return !variant_gf(v) && split_stages(Q, mode, variant_g(Q, v, mode), variant_nt(Q, v), variant_vc(v));
+    return split_stages(Q, mode, variant_g(Q, v, mode), variant_nt(Q, v), variant_vc(v));
 }
 // Multi-vector chunks of the diffusion kernel add their results to y in runs of at least 64 bytes
 // per node (8 FP64 or 16 FP32 vectors) when a launch has more vectors than one chunk: y is
@@ -205,12 +202,11 @@ constexpr bool staged_scatter(int mode, int vc, int elem_bytes)
 {
     return mode == 1 && vc > 1 && scatter_run(vc, elem_bytes) > vc;
 }
-constexpr size_t apply_lds(int P, int Q, int mode, int elem_bytes, int v, bool otf = false, bool stage = false)
+constexpr size_t apply_lds(int P, int Q, int mode, int elem_bytes, int v, bool stage = false)
 {
     const int vc = variant_vc(v);
     const size_t p3 = (size_t)P * P * P;
     return (size_t)variant_g(Q, v, mode) * vc * apply_nbuf(mode, variant_split(Q, v, mode)) * lds_buf(Q) * elem_bytes +
-           (otf ? (size_t)otf_lds_doubles(Q, variant_g(Q, v, mode)) * 8 : 0) +
            (stage && staged_scatter(mode, vc, elem_bytes) ? p3 * (scatter_run(vc, elem_bytes) - vc) * elem_bytes + p3 * 4
                                                           : 0);
 }
@@ -220,20 +216,28 @@ constexpr size_t apply_lds(int P, int Q, int mode, int elem_bytes, int v, bool o
 constexpr size_t kMaxLds = 98304;
 constexpr size_t kLdsTwoGroups = 81920;  // at most this much LDS leaves room for two thread groups per CU
 
-// Single-vector launch defaults per q (index q-2): the variant and, for the
-// mass operator, the pipeline depth measured fastest (median of interleaved
-// timings at about 1e7 DOFs on perturbed box meshes, Gauss q = p+2); orders
-// not measured there keep variant 0.
-constexpr int kDefVariantDiff[9] = {0, 0, 0, 4, 4, 4, 0, 4, 3};
-// FP32 diffusion (the operator inside mixed-precision CG): half the register and LDS footprint
-// favours two-element groups at q = 8 (20-27% faster than the FP64 choice at 1e7 and 3e7 nodes);
-// the lane-filling groups of q = 6 and 7 are 6% and 6-12% faster than the earlier two-element
-// choices; at q = 9 the best choice changes with the mesh size; q = 9 and 10 keep the one-element
-// groups that prefetch their factors (the late-factor groups that are the FP64 defaults there
-// were measured in FP64 only).
-constexpr int kDefVariantDiff32[9] = {0, 0, 0, 4, 4, 4, 3, 1, 0};
-constexpr int kDefVariantMass[9] = {0, 0, 0, 3, 3, 1, 3, 0, 4};
-constexpr int kDefChainMass[9] = {2, 2, 2, 4, 2, 4, 4, 4, 2};
+// Single-vector launch defaults of the line-fused kernel per q (index q-2).  Measured time of every
+// slot in percent of the best, at about 1e7 nodes and with the idle elements of ragged x rows taken
+// out; the default is the slot with the smallest time x idle share on the operator's own row length
+// (a row of nex elements takes ceil(nex / G) groups of G).  At p = 5 (G = 5: 201 us for whole rows,
+// G = 1: 242) a row of 6 elements is 17% faster with G = 1.
+constexpr int kLineCostDiff[9][5] = {{100, 100, 130, 100, 250}, {103, 101, 100, 162, 306}, {108, 102, 100, 169, 310},
+                                     {100, 101, 120, 117, 194}, {100, 111, 102, 132, 126}, {100, 121, 122, 109, 113},
+                                     {106, 110, 100, 104, 109}, {100, 139, 114, 139, 100}, {107, 148, 100, 107, 100}};
+constexpr int kLineCostColl[9][5] = {{102, 102, 137, 100, 245}, {100, 107, 105, 148, 259}, {100, 115, 116, 143, 232},
+                                     {105, 100, 136, 115, 192}, {100, 111, 114, 188, 150}, {100, 162, 129, 115, 122},
+                                     {108, 137, 113, 100, 137}, {117, 130, 100, 130, 117}, {107, 148, 100, 107, 100}};
+constexpr int kLineCostMass[9][5] = {{107, 101, 100, 157, 277}, {107, 101, 100, 157, 277}, {114, 103, 100, 178, 308},
+                                     {112, 100, 167, 124, 255}, {100, 126, 106, 198, 138}, {100, 175, 133, 105, 106},
+                                     {120, 152, 100, 111, 152}, {100, 146, 113, 146, 100}, {129, 100, 101, 129, 101}};
+// FP32: the measured best slot, Gauss and collocated (p = 1..8, 1e7 nodes: 1583 -> 1079, 384 -> 342, 287 -> 223,
+// 213 -> 182, 193 -> 155, 168 -> 130, 165 -> 128, 169 -> 155 us against the stored-factor kernel).
+constexpr int kLineSlot32Gauss[9] = {0, 0, 0, 0, 0, 0, 0, 0, 2};
+constexpr int kLineSlot32Coll[9] = {0, 1, 0, 1, 0, 3, 2, 2, 2};
+// Mass: pipeline depth (elements a group marches through); collocated mass (k_mass): variant and depth.
+constexpr int kDefChainMass[9] = {8, 8, 8, 8, 4, 2, 4, 4, 2};
+constexpr int kDefVariantMassColl[9] = {0, 0, 0, 3, 3, 1, 3, 0, 4};
+constexpr int kDefChainMassColl[9] = {2, 2, 2, 4, 2, 4, 4, 4, 2};
 // Device basis block (elements): B [Q][P], B^T [P][Q], D [Q][Q], D^T [Q][Q],
 // then the folded (even-odd) forms of the same four matrices: for a matrix M
 // with NO rows and NI columns, row o < ceil(NO/2) holds

@@ -26,7 +26,7 @@ import sys
 from collections import defaultdict
 
 HERE = os.path.dirname(os.path.abspath(__file__))
-KERNEL_SOURCES = ("csrc/apply_kernels.hpp", "csrc/mfhex_internal.h", "csrc/geom.hpp", "csrc/diag_kernels.hpp")
+KERNEL_SOURCES = ("csrc/apply_kernels.hpp", "csrc/line_kernels.hpp", "csrc/mfhex_internal.h", "csrc/geom.hpp", "csrc/diag_kernels.hpp")
 TET_SOURCES = ("csrc/tet_kernels.hip", "csrc/tet.h")
 PROBE_SOURCES = ("probe/hbm_stream.hip", "probe/fp64_rate.hip")
 COPY_BYTES = 1 << 30
@@ -42,27 +42,25 @@ def kernel_source_hash(sources=KERNEL_SOURCES) -> str:
 
 def _short(name: str) -> str:
     m = re.match(r"void mfhex::k_apply<(\d+), (\d+), (\w+), (\d), (\w+), (\w+), (\d+), (\d+)(?:, (\d+))?"
-                 r"(?:, (true|false))?(?:, (true|false))?(?:, (true|false))?(?:, (\d+))?(?:, (true|false))?"
+                 r"(?:, (true|false))?(?:, (true|false))?(?:, (\d+))?(?:, (true|false))?"
                  r"(?:, (\d+))?>", name)
     if m:
-        P, Q, colloc, mode, vark, T, G, NT, VC, otf, det, stage, late, mx, pre = m.groups()
+        P, Q, colloc, mode, vark, T, G, NT, VC, det, stage, late, mx, pre = m.groups()
         kind = {"0": "mass", "1": "diffusion", "2": "rhs"}[mode]
         vc = f" VC={VC}" if VC and VC != "1" else ""
-        geo = " otf" if otf == "true" else ""
         dt = " det" if det == "true" else ""
         st = " staged" if stage == "true" else ""
         lt = f" late{late}" if late and late != "0" else ""
         lt += f" pre{pre}" if pre and pre != "0" else ""
         mc = " mfma" if mx == "true" else ""
-        return (f"k_apply p={int(P) - 1} q={Q} {kind}{' kappa' if vark == 'true' else ''}{geo} {T} G={G} NT={NT}"
+        return (f"k_apply p={int(P) - 1} q={Q} {kind}{' kappa' if vark == 'true' else ''} {T} G={G} NT={NT}"
                 f"{vc}{dt}{st}{lt}{mc}")
-    m = re.match(r"void mfhex::k_apply_gf<(\d+), (\d+), (\w+), (\w+), (\d+), (\d+), (\w+)(?:, (true|false))?>", name)
+    m = re.match(r"void mfhex::k_line<(\d+), (\d+), (\w+), (\d), (\w+), (\w+), (\d+), (\d+), (\w+), ([\w ]+)>", name)
     if m:
-        P, Q, vark, T, G, NT, pf, det = m.groups()
-        late = "" if pf == "true" else " late-factors"
-        dt = " det" if det == "true" else ""
-        return (f"k_apply_gf p={int(P) - 1} q={Q} diffusion{' kappa' if vark == 'true' else ''} {T} G={G} NT={NT}"
-                f"{late}{dt}")
+        P, Q, colloc, mode, vark, T, G, NT, det, off = m.groups()
+        kind = {"0": "mass", "1": "diffusion"}[mode]
+        return (f"k_line p={int(P) - 1} q={Q} {kind}{' kappa' if vark == 'true' else ''} {T} G={G} NT={NT}"
+                f"{' det' if det == 'true' else ''}{'' if off == 'unsigned int' else ' wide'}")
     m = re.match(r"void mfhex::k_mass<(\d+), (\d+), (\w+), (\w+), (\d+), (\d+), (\d+)(?:, (true|false))?>", name)
     if m:
         P, Q, colloc, T, G, NT, VC, det = m.groups()
@@ -121,7 +119,7 @@ def traffic_summary(fetch_dir: str, write_dir: str, command: str) -> str:
            f"scale fetch x{f_scale:.4f}, write x{w_scale:.4f}",
            f"{'kernel':<60} {'fetch_KiB':>12} {'write_KiB':>12} {'traffic_bytes':>15} {'avg_us':>9}"]
     for k in fe:
-        if ("k_apply" not in k and "k_mass" not in k) or k not in wr:
+        if not any(n in k for n in ("k_apply", "k_mass", "k_line")) or k not in wr:
             continue
         f = sum(fe[k]) / len(fe[k])
         w = sum(wr[k]) / len(wr[k])
@@ -195,7 +193,7 @@ def counter_summary(dirs, command: str, sources=KERNEL_SOURCES) -> str:
     per = {}
     for k in vals:
         sk = _short(k)
-        if sk.startswith("k_apply") or sk.startswith("k_mass") or sk.startswith("k_tet"):
+        if sk.startswith(("k_apply", "k_mass", "k_line", "k_tet")):
             per[sk] = {c: sum(v) / len(v) for c, v in vals[k].items()}
     header = [f"# rocprofv3 counters per dispatch (mean over dispatches)", f"# command: {command}",
               f"# kernel source hash: {kernel_source_hash(sources)}", _TABLE_NOTE]
@@ -231,7 +229,7 @@ def read_traffic(path: str):
         return {}
     res = {}
     for line in txt.splitlines():
-        if line.startswith("k_apply") or line.startswith("k_mass"):
+        if line.startswith(("k_apply", "k_mass", "k_line")):
             parts = line.split()
             name = " ".join(parts[:-4])
             res[name] = float(parts[-2])
