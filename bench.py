@@ -643,10 +643,10 @@ def adjoint_bench(p=4, dofs=1e7):
     return out
 
 
-def tet_dims(p: int, q: int):
-    P, Q = (p + 1) * (p + 2) * (p + 3) // 6, q ** 3
-    r = lambda n, m: (n + m - 1) // m * m
-    return P, Q, r(Q, 16), r(P, 4), r(P, 16)
+def tet_dims(p: int):
+    """Basis functions, gradient rows (dim P_{p-1}), tiles of four rows, forward and transposed steps of a tile."""
+    P, M = (p + 1) * (p + 2) * (p + 3) // 6, p * (p + 1) * (p + 2) // 6
+    return P, M, -(-M // 4), -(-P // 4), 3 * (-(-P // 16))
 
 
 def tet_bench(orders=(2, 3, 4, 5, 6), dofs=1e7, reps=20):
@@ -669,18 +669,14 @@ def tet_bench(orders=(2, 3, 4, 5, 6), dofs=1e7, reps=20):
             e1.record()
         torch.cuda.synchronize()
         ms = float(np.median([a.elapsed_time(b) for a, b in ev]))
-        P, Q, Qp, Pk, Pn = tet_dims(p, op.q)
+        P, M, tiles, fwd, bwd = tet_dims(p)
         E, N = op.n_elem, op.n_nodes
-        useful = E * (12.0 * Q * P + 15.0 * Q)          # two products of 3Q x P per element + the 3x3 per point
-        # p <= 3: the library groups the 12 tetrahedra of two hexahedra per wavefront and computes their
-        # restriction from the block coordinates (no offset array); otherwise 16 elements per
-        # wavefront with a stored int32 restriction
-        pairs = p <= 3
-        groups = ((ne + 1) // 2) * ne * ne if pairs else -(-E // 16)
-        issued = groups * 2048.0 * (3 * (Qp // 16) * (Pk // 4) + 12 * (Qp // 16) * (Pn // 16))
-        byts = 8 * N + 8 * N + (0 if pairs else 4 * E * P) + 48 * E * Q
+        useful = E * (12.0 * M * P + 15.0 * M)          # two products of 3M x P per element + the 3x3 per row
+        # three wavefronts of 16 columns per 8 hexahedra of a row
+        issued = 3.0 * (-(-ne // 8)) * ne * ne * 2048.0 * tiles * (fwd + bwd)
+        byts = 8 * N + 8 * N + 48 * E
         t = ms / 1e3
-        r = {"p": p, "q": op.q, "elements": E, "dofs": N, "basis_per_elem": P, "points_per_elem": Q, "ms": round(ms, 4),
+        r = {"p": p, "q": op.q, "elements": E, "dofs": N, "basis_per_elem": P, "rows_per_elem": M, "ms": round(ms, 4),
              "gdofs": round(N / t / 1e9, 3), "useful_tflops": round(useful / t / 1e12, 2),
              "mfma_frac_useful": round(useful / t / 1e12 / FP64_PEAK_TFLOPS, 4),
              "issued_mfma_tflops": round(issued / t / 1e12, 2),

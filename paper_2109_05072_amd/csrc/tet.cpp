@@ -36,9 +36,8 @@
 struct mfhex_tet_s {
     mfhex_tet_desc d{};
     mfhex::tet::Dims D{};
-    int64_t E = 0, ngroups = 0, N = 0;
-    double *afrag = nullptr, *bfrag = nullptr, *qdata = nullptr;
-    int32_t *offsets = nullptr;
+    int64_t E = 0, N = 0;
+    double *frag = nullptr, *fac = nullptr;
     const int32_t *lattice = nullptr;
 };
 
@@ -192,39 +191,67 @@ void eval_basis(int p, const double *xi, int M, double *B, double *G)
     }
 }
 
+// Orthonormal basis of P_{p-1} on the reference tetrahedron at collapsed coordinates (a, b, c) in [0,1]^3 (the
+// Koornwinder-Dubiner products of Jacobi polynomials), not yet normalized: psi [n_rows(p)].
+void eval_psi(int p, double a, double b, double c, double *psi)
+{
+    int m = 0;
+    for (int i = 0; i < p; ++i)
+        for (int j = 0; i + j < p; ++j)
+            for (int k = 0; i + j + k < p; ++k)
+                psi[m++] = jacobi_poly(i, 0.0, 0.0, 2.0 * a - 1.0) * std::pow(1.0 - b, i) *
+                           jacobi_poly(j, 2.0 * i + 1.0, 0.0, 2.0 * b - 1.0) * std::pow(1.0 - c, i + j) *
+                           jacobi_poly(k, 2.0 * (i + j) + 2.0, 0.0, 2.0 * c - 1.0);
+}
+
+// H [3][M][P] with the rule of p + 1 points per direction (exact here: degree 2p - 2 against 2p + 1).
+std::vector<double> gradient_rows(int p)
+{
+    const int q = p + 1, Q = q * q * q, P = n_basis(p), M = n_rows(p);
+    const Rule R = tet_rule(q);
+    std::vector<double> g((size_t)3 * Q * P), psi((size_t)Q * M), norm(M, 0.0), H((size_t)3 * M * P, 0.0);
+    eval_basis(p, R.xi.data(), Q, nullptr, g.data());
+    for (int k = 0; k < Q; ++k) {
+        // collapsed coordinates of the point xi = (a (1-b)(1-c), b (1-c), c)
+        const double c = R.xi[3 * k + 2], b = R.xi[3 * k + 1] / (1.0 - c), a = R.xi[3 * k] / ((1.0 - b) * (1.0 - c));
+        eval_psi(p, a, b, c, &psi[(size_t)k * M]);
+        for (int m = 0; m < M; ++m) norm[m] += R.w[k] * psi[(size_t)k * M + m] * psi[(size_t)k * M + m];
+    }
+    for (int d = 0; d < 3; ++d)
+        for (int k = 0; k < Q; ++k)
+            for (int m = 0; m < M; ++m) {
+                const double f = R.w[k] * psi[(size_t)k * M + m] / std::sqrt(norm[m]);
+                for (int n = 0; n < P; ++n) H[((size_t)d * M + m) * P + n] += f * g[((size_t)d * Q + k) * P + n];
+            }
+    return H;
+}
+
 struct Layout {
-    size_t afrag, bfrag, lattice, wq, vert, bad, offsets, qdata, total;
+    size_t frag, lattice, vert, bad, fac, total;
 };
 
-Layout layout(const mfhex_tet_desc &d, const Dims &D, int64_t ngroups)
+// The caller's workspace is sized for six factors at every point and a stored restriction of 16-element groups (its
+// documented contents); the tables in use (fragments, six factors per element) fit in it for every p and q.
+Layout layout(const mfhex_tet_desc &d, const Dims &D)
 {
+    const bool pairs = D.p <= 3;
+    const int64_t E = 6LL * d.nex * d.ney * d.nez;
+    const int64_t ngroups = pairs ? (int64_t)((d.nex + 1) / 2) * d.ney * d.nez : (E + 15) / 16;
     Layout L{};
     size_t o = 0;
-    L.afrag = o;
-    o += al(afrag_len(D) * 8);
-    L.bfrag = o;
-    o += al(bfrag_len(D) * 8);
+    L.frag = o;
+    o += al((size_t)(D.Qp / 16) * 3 * (D.Pk / 4) * 64 * 8) + al((size_t)(D.Qp / 16) * 3 * 4 * (D.Pn / 16) * 64 * 8);
     L.lattice = o;
-    o += al((size_t)D.P * 4 * 4);
-    L.wq = o;
-    o += al((size_t)D.Q * 8);
+    o += al((size_t)D.P * 4 * 4) + al((size_t)D.Q * 8);
     L.vert = o;
     o += al((size_t)(d.nex + 1) * (d.ney + 1) * (d.nez + 1) * 3 * 8);
     L.bad = o;
     o += 256;
-    L.offsets = o;
-    if (!pair_groups(D.p)) o += al((size_t)ngroups * D.P * kGroup * 4);
-    L.qdata = o;
-    o += al((size_t)ngroups * D.Q * 6 * kGroup * 8);
+    L.fac = o;
+    if (!pairs) o += al((size_t)ngroups * D.P * 16 * 4);
+    o += al((size_t)ngroups * D.Q * 6 * 16 * 8);
     L.total = o;
     return L;
-}
-
-// Element groups: 16 consecutive elements, or (low orders) the two x-adjacent hexahedra of a pair.
-int64_t n_groups(const mfhex_tet_desc &d)
-{
-    if (pair_groups(d.p)) return (int64_t)((d.nex + 1) / 2) * d.ney * d.nez;
-    return (6LL * d.nex * d.ney * d.nez + kGroup - 1) / kGroup;
 }
 
 int validate(const mfhex_tet_desc *d)
@@ -236,7 +263,7 @@ int validate(const mfhex_tet_desc *d)
     if (d->nex < 1 || d->ney < 1 || d->nez < 1) return fail_global(MFHEX_ERR_ARG, "empty mesh");
     const int64_t E = 6LL * d->nex * d->ney * d->nez;
     const int64_t N = (int64_t)(d->p * (int64_t)d->nex + 1) * (d->p * (int64_t)d->ney + 1) * (d->p * (int64_t)d->nez + 1);
-    if (N >= (1LL << 31) || E >= (1LL << 31) / kGroup)
+    if (N >= (1LL << 31) || E >= (1LL << 31) / 16)
         return fail_global(MFHEX_ERR_UNSUPPORTED, "tetrahedral operator: node or element count too large");
     if (!d->vertex_xyz) return fail_global(MFHEX_ERR_ARG, "null vertex array");
     return MFHEX_OK;
@@ -257,13 +284,13 @@ int mfhex_tet_query(const mfhex_tet_desc *d, mfhex_tet_sizes *out)
     if (c) return c;
     if (!out) return fail_global(MFHEX_ERR_ARG, "null output");
     const Dims D = dims(d->p, d->q);
-    const int64_t E = 6LL * d->nex * d->ney * d->nez, G = n_groups(*d);
+    const int64_t E = 6LL * d->nex * d->ney * d->nez;
     out->n_nodes = (int64_t)(d->p * (int64_t)d->nex + 1) * (d->p * (int64_t)d->ney + 1) * (d->p * (int64_t)d->nez + 1);
     out->n_elem = E;
     out->n_qpts = E * D.Q;
     out->n_basis = D.P;
     out->n_points = D.Q;
-    out->workspace_bytes = layout(*d, D, G).total;
+    out->workspace_bytes = layout(*d, D).total;
     return MFHEX_OK;
 }
 
@@ -298,9 +325,8 @@ int mfhex_tet_create(const mfhex_tet_desc *d, void *workspace_dev, size_t worksp
     op->D = dims(d->p, d->q);
     op->E = sz.n_elem;
     op->N = sz.n_nodes;
-    op->ngroups = n_groups(*d);
     const Dims &D = op->D;
-    const tet::Layout L = layout(*d, D, op->ngroups);
+    const tet::Layout L = layout(*d, D);
     char *w = static_cast<char *>(workspace_dev);
     hipStream_t s = static_cast<hipStream_t>(stream);
     // on a failure after copies were queued, wait for them: their host sources are locals
@@ -309,53 +335,39 @@ int mfhex_tet_create(const mfhex_tet_desc *d, void *workspace_dev, size_t worksp
         return code;
     };
 
-    // gradient matrices G_d [Q][P] at the rule's points, as matrix-core fragments
-    const Rule R = tet_rule(d->q);
-    std::vector<double> g((size_t)3 * D.Q * D.P);
-    eval_basis(d->p, R.xi.data(), D.Q, nullptr, g.data());
-    auto G = [&](int dd, int k, int n) { return (k < D.Q && n < D.P) ? g[((size_t)dd * D.Q + k) * D.P + n] : 0.0; };
-    std::vector<double> af(afrag_len(D)), bf(bfrag_len(D));
-    for (int b = 0; b < D.Qp / 16; ++b)
-        for (int dd = 0; dd < 3; ++dd) {
-            for (int st = 0; st < D.Pk / 4; ++st)
-                for (int l = 0; l < 64; ++l)
-                    af[(((size_t)b * 3 + dd) * (D.Pk / 4) + st) * 64 + l] = G(dd, 16 * b + l % 16, 4 * st + l / 16);
-            for (int r = 0; r < 4; ++r)
-                for (int t = 0; t < D.Pn / 16; ++t)
-                    for (int l = 0; l < 64; ++l)
-                        bf[((((size_t)b * 3 + dd) * 4 + r) * (D.Pn / 16) + t) * 64 + l] =
-                            G(dd, 16 * b + 4 * r + l / 16, 16 * t + l % 16);
-        }
+    // gradient rows H_d [M][P] as matrix-core fragments, tile by tile
+    const std::vector<double> H = gradient_rows(d->p);
+    const int M = n_rows(d->p), NS = D.Pk / 4, NT = D.Pn / 16;
+    auto h = [&](int dd, int m, int n) {
+        return (dd < 3 && m < M && n < D.P) ? H[((size_t)dd * M + m) * D.P + n] : 0.0;
+    };
+    std::vector<double> fr(tet_frag_doubles(d->p));
+    size_t k = 0;
+    for (int t = 0; t < tet_tiles(d->p); ++t) {
+        for (int st = 0; st < NS; ++st)
+            for (int l = 0; l < 64; ++l) fr[k++] = h((l % 16) / 4, 4 * t + l % 4, 4 * st + l / 16);
+        for (int dd = 0; dd < 3; ++dd)
+            for (int o = 0; o < NT; ++o)
+                for (int l = 0; l < 64; ++l) fr[k++] = h(dd, 4 * t + l / 16, 16 * o + l % 16);
+    }
     const std::vector<int> lat = lattice(d->p);
     const size_t nv = (size_t)(d->nex + 1) * (d->ney + 1) * (d->nez + 1) * 3;
-    op->afrag = reinterpret_cast<double *>(w + L.afrag);
-    op->bfrag = reinterpret_cast<double *>(w + L.bfrag);
-    op->offsets = pair_groups(d->p) ? nullptr : reinterpret_cast<int32_t *>(w + L.offsets);
+    op->frag = reinterpret_cast<double *>(w + L.frag);
     op->lattice = reinterpret_cast<const int32_t *>(w + L.lattice);
-    op->qdata = reinterpret_cast<double *>(w + L.qdata);
+    op->fac = reinterpret_cast<double *>(w + L.fac);
     int *bad = reinterpret_cast<int *>(w + L.bad);
-    if ((c = check_hip(nullptr, hipMemcpyAsync(op->afrag, af.data(), af.size() * 8, hipMemcpyHostToDevice, s), "copy")) ||
-        (c = check_hip(nullptr, hipMemcpyAsync(op->bfrag, bf.data(), bf.size() * 8, hipMemcpyHostToDevice, s), "copy")) ||
+    if ((c = check_hip(nullptr, hipMemcpyAsync(op->frag, fr.data(), fr.size() * 8, hipMemcpyHostToDevice, s), "copy")) ||
         (c = check_hip(nullptr, hipMemcpyAsync(w + L.lattice, lat.data(), lat.size() * 4, hipMemcpyHostToDevice, s),
                        "copy")) ||
-        (c = check_hip(nullptr, hipMemcpyAsync(w + L.wq, R.w.data(), R.w.size() * 8, hipMemcpyHostToDevice, s), "copy")) ||
         (c = check_hip(nullptr, hipMemcpyAsync(w + L.vert, d->vertex_xyz, nv * 8, hipMemcpyHostToDevice, s), "copy")) ||
         (c = check_hip(nullptr, hipMemsetAsync(bad, 0, sizeof(int), s), "hipMemsetAsync")))
         return drain(c);
     TetSetupLaunch S{};
-    S.p = d->p;
-    S.q = d->q;
     S.nex = d->nex;
     S.ney = d->ney;
-    S.nez = d->nez;
-    S.dirichlet = d->dirichlet;
     S.nelem = op->E;
-    S.ngroups = op->ngroups;
     S.vert = reinterpret_cast<const double *>(w + L.vert);
-    S.lattice = reinterpret_cast<const int32_t *>(w + L.lattice);
-    S.wq = reinterpret_cast<const double *>(w + L.wq);
-    S.offsets = op->offsets;
-    S.qdata = op->qdata;
+    S.fac = op->fac;
     S.bad = bad;
     S.stream = s;
     if ((c = check_hip(nullptr, launch_tet_setup(S), "tetrahedral set-up kernel"))) return drain(c);
@@ -379,18 +391,13 @@ int mfhex_tet_apply(mfhex_tet op, const double *x_dev, double *y_dev, void *stre
     if (c) return c;
     TetLaunch a{};
     a.p = op->D.p;
-    a.q = op->D.q;
     a.nex = op->d.nex;
     a.ney = op->d.ney;
     a.nez = op->d.nez;
     a.dirichlet = op->d.dirichlet;
     a.lattice = op->lattice;
-    a.nelem = op->E;
-    a.ngroups = op->ngroups;
-    a.afrag = op->afrag;
-    a.bfrag = op->bfrag;
-    a.offsets = op->offsets;
-    a.qdata = op->qdata;
+    a.frag = op->frag;
+    a.fac = op->fac;
     a.x = x_dev;
     a.y = y_dev;
     a.stream = s;

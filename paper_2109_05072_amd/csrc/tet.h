@@ -13,21 +13,37 @@ namespace mfhex {
 namespace tet {
 
 constexpr int kMaxP = 6;
-constexpr int kGroup = 16;       // elements per wavefront (the N extent of one matrix-core tile)
-constexpr int kWaves = 4;        // wavefronts per thread group
+constexpr int kComputeUnits = 256;
 constexpr int n_basis(int p) { return (p + 1) * (p + 2) * (p + 3) / 6; }
-// Low orders group elements by pairs of x-adjacent hexahedra (their 12 tetrahedra in columns 0..11
-// of the wavefront's 16): the pair's element results are summed on chip over its
-// (2p+1) x (p+1) x (p+1) lattice block before one global atomic per block node, and the
-// restriction is computed from the block coordinates instead of read.  (At p = 2 each lattice node
-// is shared by about 7 tetrahedra; per-element atomics dominate there.)
-constexpr bool pair_groups(int p) { return p <= 3; }
-constexpr int pair_block_nodes(int p) { return (2 * p + 1) * (p + 1) * (p + 1); }
 constexpr int round_up(int n, int m) { return (n + m - 1) / m * m; }
 
-// Sizes of one (p, q) instance: P basis functions, Q = q^3 points, padded to
-// the matrix-core tile (points to 16, basis functions to 4 as a contraction
-// extent and to 16 as an output extent).
+// A set of three wavefronts takes the 48 tetrahedra of 8 hexahedra consecutive in x (three full
+// 16-column tiles; pairs of hexahedra left a quarter of every tile empty).
+constexpr int kCubes = 8;
+constexpr int set_threads = 192;
+constexpr int box_nodes(int p) { return (kCubes * p + 1) * (p + 1) * (p + 1); }
+
+// Rows m of H (dim P_{p-1}) in tiles of four; the fragments of a tile: NS steps of the forward product,
+// then 3 x NT of the transposed one, 64 doubles each.
+constexpr int n_rows(int p) { return n_basis(p - 1); }
+constexpr int tet_tiles(int p) { return (n_rows(p) + 3) / 4; }
+constexpr int tet_tile_doubles(int p) { return (round_up(n_basis(p), 4) / 4 + 3 * (round_up(n_basis(p), 16) / 16)) * 64; }
+constexpr int tet_frag_doubles(int p) { return tet_tiles(p) * tet_tile_doubles(p); }
+
+// Fragments resident in LDS up to p = 4, streamed tile by tile above.  Sets per thread group share the
+// fragments: two at p = 4 (three wavefronts per SIMD in two groups), four where they are streamed
+// (twelve wavefronts, three on every SIMD).
+constexpr bool tet_stream(int p) { return p >= 5; }
+constexpr int tet_sets(int p) { return p <= 3 ? 1 : p == 4 ? 2 : 4; }
+constexpr int tet_set_doubles(int p) { return (tet_stream(p) ? 1 : 2) * round_up(box_nodes(p), 2) + 48 * 6; }
+constexpr size_t tet_lds(int p)
+{
+    return ((size_t)(tet_stream(p) ? 2 * tet_tile_doubles(p) : tet_frag_doubles(p)) +
+            (size_t)tet_sets(p) * tet_set_doubles(p)) * 8;
+}
+
+// Sizes of one (p, q) instance: P basis functions, Q = q^3 points, padded to the matrix-core tile (points to 16,
+// basis functions to 4 as a contraction extent and to 16 as an output extent).  They size the caller's workspace.
 struct Dims {
     int p, q, P, Q, Qp, Pk, Pn;
 };
@@ -36,38 +52,27 @@ constexpr Dims dims(int p, int q)
     return Dims{p, q, n_basis(p), q * q * q, round_up(q * q * q, 16), round_up(n_basis(p), 4), round_up(n_basis(p), 16)};
 }
 
-// Device tables (element counts, doubles unless noted):
-//   afrag [Qp/16][3][Pk/4][64]: lane l of step s of point block b holds G_d[16b + l%16][4s + l/16]
-//   bfrag [Qp/16][3][4][Pn/16][64]: lane l of (b, d, r, t) holds G_d[16b + 4r + l/16][16t + l%16]
-// with G_d[k][n] = d phi_n / d xi_d at point k (0 outside the Q x P matrix).
-// Matrix-core operand layout of the 16x16x4 FP64 product D += A B (wave64):
-// lane l supplies A[l%16][l/16] and B[l/16][l%16], and its result register r
-// is D[4r + l/16][l%16] (checked on gfx950 with distinct entries).
-constexpr size_t afrag_len(const Dims &D) { return (size_t)(D.Qp / 16) * 3 * (D.Pk / 4) * 64; }
-constexpr size_t bfrag_len(const Dims &D) { return (size_t)(D.Qp / 16) * 3 * 4 * (D.Pn / 16) * 64; }
-
+// Device tables:
+//   frag [tile][NS + 3 NT][64]: lane l of forward step s holds H_d[4 tile + l%4][4 s + l/16], d = (l%16)/4 (0 for
+//     d = 3); lane l of transposed step (d, t) holds H_d[4 tile + l/16][16 t + l%16] (0 outside the matrix)
+//   fac [element][6]: |det J| J^-1 J^-T (xx, yy, zz, yz, xz, xy)
+// Matrix-core operand layout of the 16x16x4 FP64 product D += A B (wave64): lane l supplies A[l%16][l/16] and
+// B[l/16][l%16], and its result register r is D[4r + l/16][l%16] (checked on gfx950 with distinct entries).
 struct TetLaunch {
-    int p, q;
-    int nex, ney, nez, dirichlet;   // pair groups: the mesh, for the computed restriction
-    int64_t nelem, ngroups;
-    const int32_t *lattice;         // [P][4]: n1, n2, n3 of each basis function's node
-    const double *afrag, *bfrag;
-    const int32_t *offsets;  // [ngroups][P][16], -1 = masked node or no element (not with pair groups)
-    const double *qdata;     // [ngroups][Q][6][16]: w |det J| J^-1 J^-T (xx, yy, zz, yz, xz, xy)
+    int p, nex, ney, nez, dirichlet;
+    const int32_t *lattice;  // [P][4]: n1, n2, n3 of each basis function's node
+    const double *frag, *fac;
     const double *x;
     double *y;
     hipStream_t stream;
 };
 
 struct TetSetupLaunch {
-    int p, q, nex, ney, nez, dirichlet;
-    int64_t nelem, ngroups;
-    const double *vert;     // [(nex+1)(ney+1)(nez+1)][3]
-    const int32_t *lattice; // [P][4]: n1, n2, n3 of each basis function's node
-    const double *wq;       // [Q] reference rule weights
-    int32_t *offsets;
-    double *qdata;
-    int *bad;               // set to 1 when an element has det J <= 0 in absolute terms
+    int nex, ney;
+    int64_t nelem;
+    const double *vert;  // [(nex+1)(ney+1)(nez+1)][3]
+    double *fac;
+    int *bad;            // set to 1 when an element is degenerate
     hipStream_t stream;
 };
 

@@ -1,23 +1,31 @@
 // Tetrahedral P_p diffusion operator: set-up and fused apply kernels.
 //
 // Apply (Sec. 2.1 libCEED and Sec. 2.2 MAGMA: the non-tensor basis action as a matrix product over
-// elements).  One wavefront owns 16 elements; the kWaves wavefronts of a
-// thread group stage the basis fragments of each block of 16 quadrature
-// points b in LDS together (coalesced copies shared by 4 x 16 elements,
-// fetched one phase ahead), then each:
-//   phase 1, U_d = G_d X on the FP64 matrix cores: A = the basis-gradient rows
-//     of the block (16 points x 4 basis functions per step, a pre-swizzled
-//     fragment of 64 consecutive doubles), B = the 16 elements' gathered
-//     values (4 basis functions x 16 elements per step, kept in registers for
-//     the whole element group);
-//   pointwise, in the result registers: v = D_q u with the symmetric factor
-//     D_q = w |det J| J^-1 J^-T of each (point, element);
-//   phase 2, Y^T += V_d^T G_d: result register r of every lane holds the
-//     points 16b + 4r + (0..3) of one element (the matrix-core result
-//     layout), which is exactly the A operand of a 4-deep step over those
-//     points, so the products feed the transposed contraction with no data
-//     movement; B = the gradient rows of the same 4 points (pre-swizzled).
-// The 16 x P element results then go to the nodes with FP64 atomics.
+// elements).  The elements are affine and the rule integrates the stiffness exactly, so the
+// gradient of a P_p field, which lies in P_{p-1}, is taken in an orthonormal basis of P_{p-1}
+// instead of at the q^3 points: with H_d[m][n] = int psi_m d phi_n / d xi_d the element stiffness is
+//   K = sum_{ab} D_ab H_a^T H_b,   D = |det J| J^-1 J^-T (one symmetric 3x3 per element),
+// M = p (p+1) (p+2) / 6 rows per direction in place of q^3 (10 of 27 at p = 3, 56 of 216 at p = 6),
+// and six factors per element in place of six per point.
+//
+// A set of three wavefronts owns the 48 tetrahedra of 8 hexahedra consecutive in x, 16 columns each:
+//   gather: the (8p+1)(p+1)^2 lattice nodes of the box once, coalesced, into LDS; each wavefront takes
+//     its X (P x 16) from there as matrix-core B operands;
+//   U = H X on the FP64 matrix cores, a tile = the three directions of four rows m: row 4 d + k of the
+//     tile is H_d[4 t + k], so result register d of lane l holds d/dxi_d of row 4 t + l/16, element l%16,
+//     and the 3x3 factor acts within a lane;
+//   Y^T += V_d^T H_d: that register is the A operand of a 4-deep step over the same four rows, so the
+//     products feed the transposed contraction with no data movement;
+//   scatter: the element results are summed in LDS over the box, then one atomic per lattice node.
+// The fragments of H (pre-swizzled, 64 consecutive doubles each) stay in LDS for the whole grid-stride
+// run of a thread group at p <= 4 (46 KB at p = 4) and are streamed through two buffers, one tile ahead,
+// shared by all its wavefronts, above (120 KB at p = 5, 273 KB at p = 6).
+//
+// Measured on MI355X, about 1e7 nodes, us an apply with its output fill, products at the q^3 points with
+// per-point factors -> this form: p = 1..6 4626 -> 1908, 1221 -> 342, 1064 -> 285, 1019 -> 392,
+// 1160 -> 446, 1579 -> 578.  The matrix cores alone need 72, 117, 138, 181, 249 us at p = 2..6; the
+// rest is the scatter and the gather with their two barriers (p = 3), issue (VALU 21% busy) and, at
+// p = 5, 6, three wavefronts a SIMD that wait for one another at every tile.
 #include "mfhex_internal.h"
 #include "tet.h"
 
@@ -27,6 +35,7 @@ namespace tet {
 namespace {
 
 typedef double d4 __attribute__((ext_vector_type(4)));
+typedef double d2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ d4 mma(double a, double b, d4 c)
 {
@@ -50,63 +59,14 @@ __device__ __forceinline__ int64_t xcd_remap(int64_t bid, int64_t nb)
     return x * q + (x < r ? x : r) + i;
 }
 
-// offsets[g][n][16]: global lattice node of basis function n of element 16 g + j (-1: masked / none).
-__global__ void k_tet_offsets(int p, int P, int nex, int ney, int nez, int dirichlet, int64_t nelem, int64_t total,
-                              const int32_t *__restrict__ lattice, int32_t *__restrict__ offsets)
+// fac[e][6] = |det J| J^-1 J^-T = adj(J) adj(J)^T / |det J| (xx, yy, zz, yz, xz, xy) of element e = 6 cube + t.
+__global__ void k_tet_factors(int nex, int ney, int64_t nelem, const double *__restrict__ vert, double *__restrict__ fac,
+                              int *__restrict__ bad)
 {
-    const int64_t idx = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (idx >= total) return;
-    const int j = (int)(idx % kGroup);
-    const int n = (int)((idx / kGroup) % P);
-    const int64_t e = (idx / ((int64_t)kGroup * P)) * kGroup + j;
-    int32_t o = -1;
-    if (e < nelem) {
-        const int64_t cube = e / 6;
-        const int t = (int)(e % 6);
-        const int ex = (int)(cube % nex), ey = (int)((cube / nex) % ney), ez = (int)(cube / ((int64_t)nex * ney));
-        int a0, a1, a2;
-        kuhn_perm(t, a0, a1, a2);
-        const int n1 = lattice[4 * n], n2 = lattice[4 * n + 1], n3 = lattice[4 * n + 2];
-        // lattice offset n1 v1 + n2 v2 + n3 v3 with v1 = e_a0, v2 = e_a0 + e_a1, v3 = (1,1,1)
-        int a[3] = {n3, n3, n3};
-        a[a0] += n1 + n2;
-        a[a1] += n2;
-        (void)a2;
-        const int nx = p * nex + 1, ny = p * ney + 1, nz = p * nez + 1;
-        const int I = p * ex + a[0], J = p * ey + a[1], K = p * ez + a[2];
-        const bool bnd = I == 0 || I == nx - 1 || J == 0 || J == ny - 1 || K == 0 || K == nz - 1;
-        if (!(dirichlet && bnd)) o = I + nx * (J + ny * K);
-    }
-    offsets[idx] = o;
-}
-
-// qdata[g][m][6][16] = w_m |det J| J^-1 J^-T = w_m adj(J) adj(J)^T / |det J| (xx, yy, zz, yz, xz, xy).
-// Element of column j of group g (-1: empty column).
-__device__ __forceinline__ int64_t group_element(int64_t g, int j, bool pairs, int nex, int ney, int64_t nelem)
-{
-    if (!pairs) {
-        const int64_t e = g * kGroup + j;
-        return e < nelem ? e : -1;
-    }
-    const int npx = (nex + 1) / 2;
-    const int px = (int)(g % npx);
-    const int64_t row = g / npx;  // ey + ney ez
-    const int cx = 2 * px + j / 6;
-    if (j >= 12 || cx >= nex) return -1;
-    return 6 * (cx + (int64_t)nex * row) + j % 6;
-}
-
-__global__ void k_tet_qdata(int Q, int nex, int ney, int pairs, int64_t nelem, int64_t nslots,
-                            const double *__restrict__ vert, const double *__restrict__ wq, double *__restrict__ qdata,
-                            int *__restrict__ bad)
-{
-    const int64_t slot = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (slot >= nslots) return;
-    const int64_t g = slot / kGroup;
-    const int j = (int)(slot % kGroup);
-    const int64_t e = group_element(g, j, pairs != 0, nex, ney, nelem);
-    double M[6] = {0, 0, 0, 0, 0, 0};
-    if (e >= 0) {
+    const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (e >= nelem) return;
+    double M[6];
+    {
         const int64_t cube = e / 6;
         const int t = (int)(e % 6);
         const int ex = (int)(cube % nex), ey = (int)((cube / nex) % ney), ez = (int)(cube / ((int64_t)nex * ney));
@@ -144,252 +104,286 @@ __global__ void k_tet_qdata(int Q, int nex, int ney, int pairs, int64_t nelem, i
         M[4] = aa(0, 2);
         M[5] = aa(0, 1);
     }
-    double *qd = qdata + (size_t)g * Q * 6 * kGroup + j;
-    for (int m = 0; m < Q; ++m) {
-        const double w = wq[m];
-        for (int f = 0; f < 6; ++f) qd[((size_t)m * 6 + f) * kGroup] = w * M[f];
-    }
+    for (int f = 0; f < 6; ++f) fac[6 * e + f] = M[f];
 }
 
-// LDS: the gradient fragments of one point block, shared by the kWaves element groups of the thread group.
-constexpr size_t frag_block_doubles(const Dims &D) { return (size_t)3 * (D.Pk / 4) * 64 + (size_t)12 * (D.Pn / 16) * 64; }
+// Node slot i of the box: coordinates (bx, by, bz) in [0, 8p] x [0, p] x [0, p].
+template <int p>
+struct Box {
+    static constexpr int BX = kCubes * p + 1, BY = p + 1, NB = BX * BY * BY;
+    __device__ static __forceinline__ void coords(int i, int &bx, int &by, int &bz)
+    {
+        bx = i % BX;
+        by = (i / BX) % BY;
+        bz = i / (BX * BY);
+    }
+};
 
-// Pair groups: lattice-block coordinates (bx, by, bz) in [0, 2p] x [0, p] x [0, p] of basis
-// function n of column j (tetrahedron j % 6 of hexahedron j / 6 of the pair).
-__device__ __forceinline__ void pair_block_coords(int p, int j, const int32_t *__restrict__ lattice, int n, int &bx,
-                                                  int &by, int &bz)
+// Box position of basis function n of column j (tetrahedron j % 6 of hexahedron j / 6).
+template <int p>
+__device__ __forceinline__ int box_node(int j, const int32_t *__restrict__ lattice, int n)
 {
     int a0, a1, a2;
     kuhn_perm(j % 6, a0, a1, a2);
     (void)a2;
     const int n1 = lattice[4 * n], n2 = lattice[4 * n + 1], n3 = lattice[4 * n + 2];
+    // lattice offset n1 v1 + n2 v2 + n3 v3 with v1 = e_a0, v2 = e_a0 + e_a1, v3 = (1,1,1)
     int a[3] = {n3, n3, n3};
     a[a0] += n1 + n2;
     a[a1] += n2;
-    bx = (j / 6) * p + a[0];
-    by = a[1];
-    bz = a[2];
+    return (j / 6) * p + a[0] + Box<p>::BX * (a[1] + Box<p>::BY * a[2]);
 }
 
-// Global lattice node of block node (bx, by, bz) of pair (px, row), -1 if masked or past the mesh.
-__device__ __forceinline__ int32_t pair_node(int p, int nex, int ney, int nez, int dirichlet, int px, int64_t row,
-                                             int bx, int by, int bz)
+template <int p>
+__global__ void __launch_bounds__(set_threads * tet_sets(p))
+k_tet_apply(const int ngx, const int nex, const int ney, const int nez, const int dirichlet, const int per,
+            const int32_t *__restrict__ lattice, const double *__restrict__ frag, const double *__restrict__ fac,
+            const double *__restrict__ x, double *__restrict__ y)
 {
-    const int nx = p * nex + 1, ny = p * ney + 1, nz = p * nez + 1;
-    const int ey = (int)(row % ney), ez = (int)(row / ney);
-    const int I = 2 * p * px + bx, J = p * ey + by, K = p * ez + bz;
-    if (I >= nx) return -1;
-    if (dirichlet && (I == 0 || I == nx - 1 || J == 0 || J == ny - 1 || K == 0 || K == nz - 1)) return -1;
-    return I + nx * (J + ny * K);
-}
+    using B = Box<p>;
+    constexpr int P = n_basis(p), T = tet_tiles(p), NS = round_up(P, 4) / 4, NT = round_up(P, 16) / 16;
+    constexpr int FT = tet_tile_doubles(p), SETS = tet_sets(p), NTH = set_threads * SETS;
+    constexpr bool STREAM = tet_stream(p);
+    constexpr int NB = B::NB, R = (NB + set_threads - 1) / set_threads;
+    extern __shared__ __align__(16) double smem[];
+    const int tid = threadIdx.x, set = tid / set_threads, t3 = tid - set * set_threads;
+    const int lane = t3 & 63, wave = t3 >> 6, el = lane & 15, kq = lane >> 4;
+    double *const sF = smem;
+    // per set: input and output boxes (one and the same where the fragments are streamed: there LDS is short, and
+    // the products are long enough to hide two more barriers), then the factors of its 48 columns
+    double *const xb = sF + (STREAM ? 2 : T) * FT + set * tet_set_doubles(p);
+    double *const yb = STREAM ? xb : xb + round_up(NB, 2), *const sD = yb + round_up(NB, 2);
 
-template <int p, int q>
-__global__ void __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(p == 4 ? 3 : 2)))
-k_tet_apply(int64_t ngroups, int nex, int ney, int nez, int dirichlet, const int32_t *__restrict__ lattice,
-            const double *__restrict__ afrag, const double *__restrict__ bfrag, const int32_t *__restrict__ offsets,
-            const double *__restrict__ qdata, const double *__restrict__ x, double *__restrict__ y)
-{
-    constexpr Dims D = dims(p, q);
-    constexpr int P = D.P, Q = D.Q, NS = D.Pk / 4, NT = D.Pn / 16, NB = D.Qp / 16;
-    constexpr int AL = 3 * NS * 64, BL = 12 * NT * 64, FL = AL + BL;
-    constexpr bool PAIRS = pair_groups(p);
-    constexpr int NBLK = pair_block_nodes(p), BXN = 2 * p + 1, BYN = p + 1;
-    extern __shared__ __align__(16) double sfrag[];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x / 64;
-    const int64_t g0 = xcd_remap(blockIdx.x, gridDim.x) * kWaves + wave;  // wavefront-uniform
-    // every wavefront takes part in the staging and its barriers; one past the last group computes on
-    // the last group's data and stores nothing
-    const bool active = g0 < ngroups;
-    const int64_t g = active ? g0 : ngroups - 1;
-    const int el = lane % 16, kq = lane / 16;
-    const int32_t *off = PAIRS ? nullptr : offsets + (size_t)g * P * kGroup;
-    // pair groups: pair coordinates, whether column el holds an element, this wavefront's block sums
-    const int npx = (nex + 1) / 2;
-    const int px = (int)(g % npx);
-    const int64_t row = g / npx;
-    const bool col_ok = el < 12 && 2 * px + el / 6 < nex;
-    double *const sblk = sfrag + FL + wave * round_up(NBLK, 2);
-    if constexpr (PAIRS)
-        for (int i = lane; i < NBLK; i += 64) sblk[i] = 0.0;
-
-    // B operand of phase 1: lane holds X[basis 4s + kq][element el] for every step s
-    // (branch-free: every load is issued, from a clamped index, and the value selected afterwards, so
-    // the loads of all steps are in flight together instead of one round trip per step)
-    double xf[NS];
-    int32_t xo[NS];
+    // LDS positions of this lane's operands: X[4 s + kq][column 16 wave + el], and result register r of output
+    // tile t: element 4 r + kq, basis function 16 t + el (65535: no basis function)
+    uint32_t xa[(NS + 1) / 2], ya[NT * 2];
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
         const int n = 4 * s + kq;
-        if constexpr (PAIRS) {
-            int bx, by, bz;
-            pair_block_coords(p, el, lattice, n < P ? n : P - 1, bx, by, bz);
-            const int32_t o = pair_node(p, nex, ney, nez, dirichlet, px, row, bx, by, bz);
-            xo[s] = col_ok && n < P ? o : -1;
-        } else {
-            const int32_t o = __builtin_nontemporal_load(&off[(n < P ? n : P - 1) * kGroup + el]);
-            xo[s] = n < P ? o : -1;
-        }
+        const uint32_t v = n < P ? (uint32_t)box_node<p>(16 * wave + el, lattice, n) : 65535u;
+        if (s & 1) xa[s / 2] |= v << 16;
+        else xa[s / 2] = v;
     }
 #pragma unroll
-    for (int s = 0; s < NS; ++s) {
-        const double v = x[xo[s] >= 0 ? xo[s] : 0];
-        xf[s] = xo[s] >= 0 ? v : 0.0;
+    for (int i = 0; i < NT * 4; ++i) {
+        const int n = 16 * (i / 4) + el, j = 16 * wave + 4 * (i % 4) + kq;
+        const uint32_t v = n < P ? (uint32_t)box_node<p>(j, lattice, n) : 65535u;
+        if (i & 1) ya[i / 2] |= v << 16;
+        else ya[i / 2] = v;
     }
-    d4 yacc[NT];
-#pragma unroll
-    for (int t = 0; t < NT; ++t) yacc[t] = d4{0.0, 0.0, 0.0, 0.0};
+    auto half = [](uint32_t v, int i) {
+        asm volatile("" : "+v"(v));  // unpacked at each use, not held unpacked
+        return i & 1 ? v >> 16 : v & 65535u;
+    };
 
-    const double *qg = qdata + (size_t)g * Q * 6 * kGroup + el;
-    // staging is software-pipelined: the B fragments of block b travel (global -> registers) during
-    // phase 1, the A fragments of block b+1 during phase 2; each lands in LDS at the next barrier
-    constexpr int NTH = 64 * kWaves, RA = (AL + NTH - 1) / NTH, RB = (BL + NTH - 1) / NTH;
-    double *const sA = sfrag, *const sB = sfrag + AL;
-    const int tid = threadIdx.x;
-    double stage[RA > RB ? RA : RB];
+    const int nx = p * nex + 1, ny = p * ney + 1, nz = p * nez + 1;
+    const int64_t nsteps = (int64_t)ngx * ney * nez;
+    // contiguous runs of steps, y fastest (neighbours in y share the largest faces)
+    const int64_t first = (xcd_remap(blockIdx.x, gridDim.x) * SETS + set) * per;
+    struct Step {
+        int64_t node, elem;  // first lattice node, first element
+        int ncols, cx, ey, ez;
+        bool on, edge;       // edge: some node may be masked or outside the mesh
+    };
+    auto step_at = [&](int i) {
+        Step q;
+        const int64_t s = first + i;
+        q.on = i < per && s < nsteps;
+        const unsigned u = (unsigned)(q.on ? s : 0);
+        q.ey = (int)(u % (unsigned)ney);
+        const unsigned v = u / (unsigned)ney;
+        const int gx = (int)(v % (unsigned)ngx);
+        q.ez = (int)(v / (unsigned)ngx);
+        q.cx = gx * kCubes;
+        const int nc = nex - q.cx < kCubes ? nex - q.cx : kCubes;
+        q.ncols = 6 * nc;
+        q.node = (int64_t)p * (q.cx + (int64_t)nx * (q.ey + (int64_t)ny * q.ez));
+        q.elem = 6 * (q.cx + (int64_t)nex * (q.ey + (int64_t)ney * q.ez));
+        q.edge = nc < kCubes || (dirichlet && (gx == 0 || gx == ngx - 1 || q.ey == 0 || q.ey == ney - 1 || q.ez == 0 ||
+                                               q.ez == nez - 1));
+        return q;
+    };
+    // Node slots of this lane: their offsets from a step's first node are the same in every step (32 bits: N < 2^31),
+    // kept in registers where there are few of them.
+    constexpr int RK = STREAM ? 1 : R;
+    uint32_t offs[RK];
+    auto offset_of = [&](int r) {
+        int bx, by, bz, i = t3 + r * set_threads;
+        asm volatile("" : "+v"(i));  // recomputed at each use: kept, they would spill
+        B::coords(i, bx, by, bz);
+        return (uint32_t)bx + (uint32_t)nx * ((uint32_t)by + (uint32_t)ny * (uint32_t)bz);
+    };
 #pragma unroll
-    for (int k = 0; k < RA; ++k)
-        if (tid + k * NTH < AL) sA[tid + k * NTH] = afrag[tid + k * NTH];
-    __syncthreads();
-    for (int b = 0; b < NB; ++b) {
-        // this lane's factors for the block (issued first: their latency overlaps phase 1)
-        double qv[4][6];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int m = 16 * b + 4 * r + kq;
-            const double *qd = qg + (size_t)(m < Q ? m : Q - 1) * 6 * kGroup;
-#pragma unroll
-            for (int f = 0; f < 6; ++f) {
-                const double v = __builtin_nontemporal_load(&qd[f * kGroup]);
-                qv[r][f] = m < Q ? v : 0.0;
-            }
+    for (int r = 0; r < RK; ++r) offs[r] = offset_of(r);
+    auto slot = [&](const Step &q, int r, uint32_t &off) {  // false where masked or outside the mesh
+        off = STREAM ? offset_of(r) : offs[STREAM ? 0 : r];
+        bool ok = q.on && t3 + r * set_threads < NB;
+        if (q.edge) {
+            int bx, by, bz, i = t3 + r * set_threads;
+            asm volatile("" : "+v"(i));
+            B::coords(i, bx, by, bz);
+            const int I = p * q.cx + bx, J = p * q.ey + by, K = p * q.ez + bz;
+            ok = ok && I < nx && !(dirichlet && (I == 0 || I == nx - 1 || J == 0 || J == ny - 1 || K == 0 || K == nz - 1));
         }
-        {
-            const double *bb = bfrag + (size_t)b * BL;
+        return ok;
+    };
+    double xs[R];
+    d2 fd = {0.0, 0.0};
+    auto load = [&](const Step &q) {
 #pragma unroll
-            for (int k = 0; k < RB; ++k) stage[k] = tid + k * NTH < BL ? bb[tid + k * NTH] : 0.0;
+        for (int r = 0; r < R; ++r) {
+            uint32_t off;
+            xs[r] = slot(q, r, off) ? (x + q.node)[off] : 0.0;
         }
-        const double *A = sA + lane;
-        d4 u[3];
+        // factors of the set's columns (none past the row's end: those columns' results are dropped)
+        if (q.on && t3 < 3 * q.ncols) fd = reinterpret_cast<const d2 *>(fac + 6 * q.elem)[t3];
+    };
+
+    constexpr int RF = (FT + NTH - 1) / NTH;  // streamed fragments: a tile's share of one lane
+    double stage[STREAM ? RF : 1];
+    auto stage_load = [&](int tile) {
 #pragma unroll
-        for (int d = 0; d < 3; ++d) u[d] = d4{0.0, 0.0, 0.0, 0.0};
+        for (int k = 0; k < RF; ++k)
+            if (tid + k * NTH < FT) stage[k] = frag[(size_t)tile * FT + tid + k * NTH];
+    };
+    auto stage_store = [&](int buf) {
 #pragma unroll
-        for (int s = 0; s < NS; ++s)
-#pragma unroll
-            for (int d = 0; d < 3; ++d) u[d] = mma(A[(d * NS + s) * 64], xf[s], u[d]);
-        // pointwise: register r <-> point 16 b + 4 r + kq of element el
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const double xx = qv[r][0], yy = qv[r][1], zz = qv[r][2], yz = qv[r][3], xz = qv[r][4], xy = qv[r][5];
-            const double ur = u[0][r], us = u[1][r], ut = u[2][r];
-            u[0][r] = xx * ur + xy * us + xz * ut;
-            u[1][r] = xy * ur + yy * us + yz * ut;
-            u[2][r] = xz * ur + yz * us + zz * ut;
-        }
-#pragma unroll
-        for (int k = 0; k < RB; ++k)
-            if (tid + k * NTH < BL) sB[tid + k * NTH] = stage[k];
-        __syncthreads();  // B fragments of b in LDS; every wavefront is done with the A fragments of b
-        if (b + 1 < NB) {
-            const double *ab = afrag + (size_t)(b + 1) * AL;
-#pragma unroll
-            for (int k = 0; k < RA; ++k) stage[k] = tid + k * NTH < AL ? ab[tid + k * NTH] : 0.0;
-        }
-        const double *Bf = sB + lane;
-#pragma unroll
-        for (int d = 0; d < 3; ++d)
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-#pragma unroll
-                for (int t = 0; t < NT; ++t) yacc[t] = mma(u[d][r], Bf[((d * 4 + r) * NT + t) * 64], yacc[t]);
-        if (b + 1 < NB) {
-#pragma unroll
-            for (int k = 0; k < RA; ++k)
-                if (tid + k * NTH < AL) sA[tid + k * NTH] = stage[k];
-        }
-        __syncthreads();  // A fragments of b+1 in LDS; every wavefront is done with the B fragments of b
-    }
-    if (!active) return;
-    // result register r of tile t: element 4 r + kq, basis function 16 t + el
-    if constexpr (PAIRS) {
-        // sum the pair's 12 element results over its lattice block on chip, then one atomic per node
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            const int n = 16 * t + el;
-            if (n < P) {
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int j = 4 * r + kq;
-                    if (j < 12 && 2 * px + j / 6 < nex) {
-                        int bx, by, bz;
-                        pair_block_coords(p, j, lattice, n, bx, by, bz);
-                        atomicAdd(&sblk[bx + BXN * (by + BYN * bz)], yacc[t][r]);
-                    }
-                }
-            }
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        for (int i = lane; i < NBLK; i += 64) {
-            const int bx = i % BXN, by = (i / BXN) % BYN, bz = i / (BXN * BYN);
-            const int32_t o = pair_node(p, nex, ney, nez, dirichlet, px, row, bx, by, bz);
-            if (o >= 0) unsafeAtomicAdd(&y[o], sblk[i]);
-        }
+        for (int k = 0; k < RF; ++k)
+            if (tid + k * NTH < FT) sF[buf * FT + tid + k * NTH] = stage[k];
+    };
+    int buf = 0;
+    if constexpr (STREAM) {
+        stage_load(0);
+        stage_store(0);
     } else {
+        for (int i = tid; i < T * FT; i += NTH) sF[i] = frag[i];
+    }
+
+    Step q = step_at(0);
+    load(q);
+    for (int it = 0; it < per; ++it) {
 #pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            const int n = 16 * t + el;
-            if (n < P) {
+        for (int r = 0; r < R; ++r)
+            if (t3 + r * set_threads < NB) {
+                xb[t3 + r * set_threads] = xs[r];
+                if (!STREAM) yb[t3 + r * set_threads] = 0.0;
+            }
+        if (t3 < 3 * 48) reinterpret_cast<d2 *>(sD)[t3] = fd;
+        __syncthreads();
+        double xf[NS];
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int32_t o = off[n * kGroup + 4 * r + kq];
-                    if (o >= 0) unsafeAtomicAdd(&y[o], yacc[t][r]);
+        for (int s = 0; s < NS; ++s) {
+            const uint32_t v = half(xa[s / 2], s);
+            xf[s] = v != 65535u ? xb[v != 65535u ? v : 0] : 0.0;
+        }
+        if constexpr (STREAM) {
+            __syncthreads();
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                if (t3 + r * set_threads < NB) yb[t3 + r * set_threads] = 0.0;
+        }
+        const d2 *const dcol = reinterpret_cast<const d2 *>(sD) + 3 * (16 * wave + el);
+        d2 f0, f1, f2;
+        if constexpr (!STREAM) f0 = dcol[0], f1 = dcol[1], f2 = dcol[2];
+        const Step cur = q;
+        q = step_at(it + 1);
+        if (!STREAM && it + 1 < per) load(q);  // travels behind the products
+        d4 yacc[NT];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) yacc[t] = d4{0.0, 0.0, 0.0, 0.0};
+        // one tile: fragments U at a time, the next U in flight (all at once would not fit the registers)
+        auto tile = [&](const double *F) {
+            constexpr int S = NS + 3 * NT, U = STREAM ? 2 : 4, NG = (S + U - 1) / U;
+            double fr[2][U], v[3];
+            d4 u = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int k = 0; k < U; ++k) fr[0][k] = k < S ? F[k * 64 + lane] : 0.0;
+#pragma unroll
+            for (int g = 0; g < NG; ++g) {
+#pragma unroll
+                for (int k = 0; k < U; ++k)
+                    if ((g + 1) * U + k < S) fr[(g + 1) & 1][k] = F[((g + 1) * U + k) * 64 + lane];
+#pragma unroll
+                for (int k = 0; k < U; ++k) {
+                    const int i = g * U + k;
+                    if (i < NS) u = mma(fr[g & 1][k], xf[i < NS ? i : 0], u);
+                    if (i == NS) {
+                        if constexpr (STREAM) f0 = dcol[0], f1 = dcol[1], f2 = dcol[2];
+                        const double xx = f0[0], yy = f0[1], zz = f1[0], yz = f1[1], xz = f2[0], xy = f2[1];
+                        v[0] = xx * u[0] + xy * u[1] + xz * u[2];
+                        v[1] = xy * u[0] + yy * u[1] + yz * u[2];
+                        v[2] = xz * u[0] + yz * u[1] + zz * u[2];
+                    }
+                    if (i >= NS && i < S) yacc[(i - NS) % NT] = mma(v[(i - NS) / NT], fr[g & 1][k], yacc[(i - NS) % NT]);
                 }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        if constexpr (STREAM) {
+            // (the barrier after the first tile also separates clearing the box from adding to it)
+            static_assert(T > 1, "a barrier before the box is added to");
+            for (int t = 0; t < T; ++t) {
+                stage_load(t + 1 < T ? t + 1 : 0);
+                tile(sF + buf * FT);
+                buf ^= 1;
+                stage_store(buf);
+                __syncthreads();  // the next tile's fragments are in; this tile's may be overwritten
+            }
+        } else {
+#pragma unroll
+            for (int t = 0; t < T; ++t) tile(sF + t * FT);
+        }
+        if (cur.on) {
+#pragma unroll
+            for (int i = 0; i < NT * 4; ++i) {
+                const uint32_t v = half(ya[i / 2], i);
+                if (v != 65535u && 16 * wave + 4 * (i % 4) + kq < cur.ncols) atomicAdd(&yb[v], yacc[i / 4][i % 4]);
             }
         }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            uint32_t off;
+            if (slot(cur, r, off)) unsafeAtomicAdd(y + cur.node + off, yb[t3 + r * set_threads]);
+        }
+        if (STREAM && it + 1 < per) load(q);
     }
-}
-
-template <int p, int q>
-hipError_t apply_pq(const TetLaunch &a)
-{
-    const int64_t nblk = (a.ngroups + kWaves - 1) / kWaves;
-    const size_t lds = (frag_block_doubles(dims(p, q)) + (pair_groups(p) ? kWaves * round_up(pair_block_nodes(p), 2) : 0)) *
-                       sizeof(double);
-    auto kern = k_tet_apply<p, q>;
-    if (lds > 65536) {
-        const hipError_t e =
-            hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL(kern, dim3((unsigned)nblk), dim3(64 * kWaves), lds, a.stream, a.ngroups, a.nex, a.ney, a.nez,
-                       a.dirichlet, a.lattice, a.afrag, a.bfrag, a.offsets, a.qdata, a.x, a.y);
-    return hipGetLastError();
 }
 
 template <int p>
 hipError_t apply_p(const TetLaunch &a)
 {
-    if (a.q == p) return apply_pq<p, p>(a);
-    if (a.q == p + 1) return apply_pq<p, p + 1>(a);
-    return hipErrorInvalidValue;
+    constexpr size_t lds = tet_lds(p);
+    static_assert(lds <= 163840, "LDS of a thread group");
+    auto kern = k_tet_apply<p>;
+    if (lds > 65536) {
+        const hipError_t e =
+            hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+    }
+    // one resident round of thread groups, each with a contiguous share of the steps
+    const int ngx = (a.nex + kCubes - 1) / kCubes;
+    const int64_t nsteps = (int64_t)ngx * a.ney * a.nez;
+    static const int resident = [&] {
+        int n = 0;
+        return hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kern, set_threads * tet_sets(p), lds) == hipSuccess && n > 0
+                   ? n
+                   : 1;
+    }();
+    const int64_t sets = (int64_t)kComputeUnits * resident * tet_sets(p);
+    const int64_t per = (nsteps + sets - 1) / sets;
+    const int64_t nset = (nsteps + per - 1) / per, nblk = (nset + tet_sets(p) - 1) / tet_sets(p);
+    hipLaunchKernelGGL(kern, dim3((unsigned)nblk), dim3(set_threads * tet_sets(p)), lds, a.stream, ngx, a.nex, a.ney,
+                       a.nez, a.dirichlet, (int)per, a.lattice, a.frag, a.fac, a.x, a.y);
+    return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t launch_tet_setup(const TetSetupLaunch &s)
 {
-    const int P = n_basis(s.p), Q = s.q * s.q * s.q;
-    const bool pairs = pair_groups(s.p);
-    const int64_t total = s.ngroups * P * kGroup, nslots = s.ngroups * kGroup;
-    if (!pairs) {
-        hipLaunchKernelGGL(k_tet_offsets, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s.stream, s.p, P, s.nex,
-                           s.ney, s.nez, s.dirichlet, s.nelem, total, s.lattice, s.offsets);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL(k_tet_qdata, dim3((unsigned)((nslots + 127) / 128)), dim3(128), 0, s.stream, Q, s.nex, s.ney,
-                       pairs ? 1 : 0, s.nelem, nslots, s.vert, s.wq, s.qdata, s.bad);
+    hipLaunchKernelGGL(k_tet_factors, dim3((unsigned)((s.nelem + 127) / 128)), dim3(128), 0, s.stream, s.nex, s.ney,
+                       s.nelem, s.vert, s.fac, s.bad);
     return hipGetLastError();
 }
 

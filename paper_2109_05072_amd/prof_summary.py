@@ -66,9 +66,9 @@ def _short(name: str) -> str:
         P, Q, colloc, T, G, NT, VC, det = m.groups()
         vc = f" VC={VC}" if VC != "1" else ""
         return f"k_mass p={int(P) - 1} q={Q} {T} G={G} NT={NT}{vc}{' det' if det == 'true' else ''}"
-    m = re.match(r"void mfhex::tet::\(anonymous namespace\)::k_tet_apply<(\d+), (\d+)>", name)
+    m = re.match(r"void mfhex::tet::\(anonymous namespace\)::k_tet_apply<(\d+)>", name)
     if m:
-        return f"k_tet_apply p={m.group(1)} q={m.group(2)}"
+        return f"k_tet_apply p={m.group(1)}"
     name = name.replace("(anonymous namespace)::", "").replace("void ", "")
     return name.split("(")[0].split("<")[0].split("::")[-1][:60]
 

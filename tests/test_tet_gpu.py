@@ -162,3 +162,18 @@ def test_tet_fully_masked_mesh_gives_zero(gpu_lib):
     assert op.n_elem == 6 and op.n_nodes == 8
     y = host(op.apply(dev(synth.uniform_vector(8)), dev(np.full(8, 3.0))))
     assert np.all(y == 0.0)
+
+
+@pytest.mark.parametrize("p", [1, 2, 3, 4, 5, 6])
+@pytest.mark.parametrize("nex", [1, 7, 8, 9, 17])
+def test_tet_rows_that_do_not_fill_the_last_box(gpu_lib, p, nex):
+    # boxes of 8 hexahedra along x: rows one short of, equal to and one past a multiple, every mask face in one box
+    op, pr = build(gpu_lib, (nex, 2, 2 if p < 5 else 1), p, p, nex % 2 == 1)
+    x = synth.uniform_vector(pr.n_nodes, seed=nex)
+    yo = otet.apply(pr, x)
+    y = host(op.apply(dev(x)))
+    print("tet ragged", p, nex, relerr(y, yo) if np.abs(yo).max() else np.abs(y).max(), flush=True)
+    if np.abs(yo).max():
+        assert relerr(y, yo) <= TOL64
+    else:
+        assert np.all(y == 0.0)
