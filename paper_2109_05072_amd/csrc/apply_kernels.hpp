@@ -1034,6 +1034,40 @@ static hipError_t launch_line_v(const ApplyLaunch &a)
     return go(k_line<P, Q, COLLOC, MODE, VARK, T, G, NT, DET, int64_t>);
 }
 
+// Chunks of 4 or 8 vectors of the collocated diffusion operator (k_mline).
+template <int Q, typename T, int V>
+static hipError_t launch_mline_v(const ApplyLaunch &a)
+{
+    constexpr int VC = variant_vc(V), G = mline_g(Q, V), NT = mline_nt(Q, V);
+    constexpr size_t lds = mline_lds<Q, VC, T>(G);
+    static_assert(lds <= kMaxLds, "LDS of a multi-vector group");
+    LineArgs<T> k{};
+    k.bas = static_cast<const T *>(a.basis_dev);
+    k.bas64 = a.basis64;
+    k.qdata = static_cast<const T *>(a.v.qdata);
+    k.x = static_cast<const T *>(a.x);
+    k.y = static_cast<T *>(a.y);
+    k.nex = a.v.nex;
+    k.ney = a.v.ney;
+    k.nez = a.v.nez;
+    k.dirichlet = a.dirichlet;
+    k.nvec = a.nvec;
+    k.ngx = (a.v.nex + G - 1) / G;
+    const int nch = (a.nvec + VC - 1) / VC;
+    k.march = line_march(a, (int64_t)k.ngx * a.v.nez * nch, NT);
+    k.nych = (a.v.ney + k.march - 1) / k.march;
+    const int64_t nblk = (int64_t)k.ngx * k.nych * a.v.nez * nch;
+    auto go = [&](auto kern) {
+        const hipError_t e = prepare_lds(kern, lds);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(kern, dim3((unsigned)nblk), dim3(NT), lds, a.stream, k);
+        return hipGetLastError();
+    };
+    const int64_t slab = (int64_t)Q * (a.v.nex * (Q - 1) + 1) * (a.v.ney * (int64_t)(Q - 1) + 1) * a.nvec * (int64_t)sizeof(T);
+    if (slab < (int64_t)1 << 31) return go(k_mline<Q, VC, T, G, NT, uint32_t>);
+    return go(k_mline<Q, VC, T, G, NT, int64_t>);
+}
+
 // The element-at-a-time kernels with stored factors (k_apply, k_mass).
 template <int P, int Q, bool COLLOC, int MODE, bool VARK, typename T, int V, bool DET>
 static hipError_t launch_element_v(const ApplyLaunch &a)
@@ -1088,6 +1122,8 @@ static hipError_t launch_apply_v(const ApplyLaunch &a)
 {
     if constexpr (line_variant(MODE, COLLOC, OTF, V)) return launch_line_v<P, Q, COLLOC, MODE, VARK, T, V, DET>(a);
     else if constexpr (variant_gf(V) || OTF) return hipErrorInvalidValue;
+    else if constexpr (!DET && !VARK && mline_variant(MODE, COLLOC, V) && apply_lds(P, Q, MODE, sizeof(T), V) <= kMaxLds)
+        return launch_mline_v<Q, T, V>(a);
     else return launch_element_v<P, Q, COLLOC, MODE, VARK, T, V, DET>(a);
 }
 

@@ -8,6 +8,7 @@
 #include <cstdint>
 #include <cstring>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "blas.h"
@@ -172,8 +173,8 @@ bool valid_variant(const mfhex_op_s &op, int prec, int variant)
 int default_variant(const mfhex_op_s &op, int prec, int nvec)
 {
     // one vector: the measured single-vector best for this operator and q;
-    // several: the largest chunk that fits the LDS budget and does not exceed
-    // the vector count
+    // several: for the chunks of k_apply and k_mass the largest that fits the
+    // LDS budget and does not exceed the vector count
     if (nvec <= 1) {
         const int mode = mode_of(op);
         const bool otf = (op.d.flags & MFHEX_FLAG_OTF) != 0, coll = op.basis.colloc;
@@ -195,9 +196,25 @@ int default_variant(const mfhex_op_s &op, int prec, int nvec)
         }
         return line_variant(mode, coll, otf, slot) ? slot : 9 + slot;
     }
+    const int eb = prec == MFHEX_F32 ? 4 : 8;
+    if (mline_variant(mode_of(op), op.basis.colloc, 6) && !op.ebuf && !op.d.variable_kappa) {
+        // Collocated diffusion: the least sum of the chunks' times.  A chunk of 8 takes 1.4 times one of 4 (1e6 nodes,
+        // 12 vectors FP64, p = 2 .. 6: three of 4 in 226, 213, 211, 216, 184 us, two of 8 in 227, 191, 205, 191,
+        // 167; 3e6 nodes, 5 vectors, p = 3, 6: 300, 296 in 4s, 238, 218 in an 8; 4 vectors, p = 3: 148 and 239), in
+        // FP32 at q = 4 .. 6 one of 16 (k_apply) 2.3 times (16 vectors, p = 3 .. 5: 133, 152, 147 against 168, 159,
+        // 161 in 8s; 24: 312, 277, 263 against 242, 235, 236).
+        const bool pair = nvec == 2 && op.Q >= (prec == MFHEX_F32 ? 9 : 7);  // p = 6 .. 8: 106, 96, 97 against 113, 116, 174 us
+        if (pair && valid_variant(op, prec, 5)) return 5;
+        int best = 0, cost = INT32_MAX;
+        for (const auto &[v, t] : {std::pair{6, 10}, {7, 14}, {8, 23}}) {
+            if (!valid_variant(op, prec, v) || (v == 8 && (prec != MFHEX_F32 || op.Q < 4 || op.Q > 6))) continue;
+            const int sum = t * ((nvec + variant_vc(v) - 1) / variant_vc(v));
+            if (sum < cost) best = v, cost = sum;
+        }
+        if (best) return best;
+    }
     // (with the scatter staging that several chunks need, the chunk must still leave room for two
     // thread groups per compute unit)
-    const int eb = prec == MFHEX_F32 ? 4 : 8;
     for (int v = 8; v >= 5; --v) {  // the multi-vector chunk variants
         if (variant_vc(v) > nvec || !valid_variant(op, prec, v)) continue;
         const bool stage = nvec > variant_vc(v);
@@ -628,9 +645,15 @@ int mfhex_get_config(mfhex_op op, int prec, int nrhs, int32_t *variant, int32_t 
     const LaunchCfg c = config_for(*op, prec, nrhs * op->d.ncomp);
     if (variant) *variant = c.variant;
     const bool line = line_variant(mode_of(*op), op->basis.colloc, (op->d.flags & MFHEX_FLAG_OTF) != 0, c.variant);
-    const int g = line ? kLineG[op->Q - 2][line_slot(c.variant)] : variant_g(op->Q, c.variant, mode_of(*op));
+    const bool mline = !op->ebuf && mline_variant(mode_of(*op), op->basis.colloc, c.variant);
+    const int g = line    ? kLineG[op->Q - 2][line_slot(c.variant)]
+                  : mline ? mline_g(op->Q, c.variant)
+                          : variant_g(op->Q, c.variant, mode_of(*op));
     if (elems_per_group) *elems_per_group = g;
-    if (threads_per_group) *threads_per_group = line ? line_nt(op->Q, g) : variant_nt(op->Q, c.variant);
+    if (threads_per_group)
+        *threads_per_group = line    ? line_nt(op->Q, g)
+                             : mline ? mline_nt(op->Q, c.variant)
+                                     : variant_nt(op->Q, c.variant);
     if (groups_per_block) *groups_per_block = c.chain;
     return MFHEX_OK;
 }

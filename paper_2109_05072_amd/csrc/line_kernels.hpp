@@ -37,6 +37,9 @@
 // element instead of formed from the vertices: 253 us at p = 3; not kept, the workspace has no room.)
 #pragma once
 
+#include <type_traits>
+#include <utility>
+
 #include "geom.hpp"
 #include "mfhex_internal.h"
 
@@ -68,7 +71,11 @@ __device__ __forceinline__ cptr<T> after(cptr<T> p, const T &v)
     asm volatile("" : "+s"(p) : "v"(v));
     return p;
 }
-constexpr bool rows_in_flight(int NI, int NO, int bytes) { return 2 * ((NO + 1) / 2) * NI * bytes > 256; }
+constexpr bool rows_in_flight(int NI, int NO, int bytes)
+{
+    // (NI == NO: the collocated derivative, the only matrix of its kernel; else B and the derivative)
+    return (NI == NO ? 1 : 2) * ((NO + 1) / 2) * NI * bytes > 240;
+}
 
 // A line of N values, folded: e_i = v_i + v_{N-1-i}, d_i = v_i - v_{N-1-i} (i < N/2), e_{N/2} = the middle value.
 template <int N, typename T>
@@ -285,7 +292,7 @@ struct LineArgs {
     const T *bas;
     const double *bas64;
     const double *vert, *kappa;
-    const T *x;
+    const T *qdata, *x;  // qdata: stored factors (k_mline)
     T *y, *ebuf;
     int nex, ney, nez, dirichlet, nvec;
     int ngx, nych, march;  // element groups per row, y-chunks per column, elements per march
@@ -650,6 +657,297 @@ k_line(const LineArgs<T> a)
             carry = out[P - 1];
             const bool m0 = a.dirichlet && ey == 0, m1 = a.dirichlet && ey == a.ney - 1;
             // one row address at a time in scalar registers
+            gptr<T> row = (gptr<T>)yb;
+            if (!m0) global_add(row + lane0, out[0]);
+#pragma unroll
+            for (int j = 1; j < P - 1; ++j) {
+                row += stride;
+                asm volatile("" : "+s"(row) : "v"(out[j]));
+                global_add(row + lane0, out[j]);
+            }
+            if (!more && !m1) global_add(row + stride + lane0, out[P - 1]);
+        }
+        yb += p * stride;
+        if (more) group_sync<NT>();
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Collocated diffusion, VC vectors of a multi-vector together: the stages of
+// k_line with the vector as the fastest lane index, so that a gather, an LDS
+// access and an atomic touch runs of VC consecutive values (64 bytes for 8
+// FP64 vectors).  The factors are the stored ones: lane v of the VC lanes of a
+// z-line loads the six factors of the points v, v + VC, ... one element ahead,
+// and the others take them by DPP broadcasts inside the group, 12 moves a point
+// in place of six loads.  (Factors evaluated in the kernel as in k_line read
+// half the bytes but took 267 against 254 us at p = 6, 294 against 272 at p = 5
+// and 411 against 344 at p = 2, 3e6 nodes of 8 vectors; they won at p = 7 and 8
+// only, 354 against 370 and 395 against 442.)
+// Measured, k_apply with chunks before and this now, FP64: p = 6, 8 vectors of
+// 1e7 nodes 1766 -> 868 us (1.6 GB of 8-vector data), p = 3, 12 vectors of 1e6
+// nodes 280 -> 193.  The LDS of two groups of 7 wavefronts fills a CU at p = 6:
+// 883 us become 694 without the atomics, 577 without the loads as well, and 521
+// without barriers, so that memory and the stages' latency share the time; the
+// vector units are busy for 31% of it.
+// ---------------------------------------------------------------------------
+
+// The value of lane K of each group of VC lanes (VC = 4: a quad; 8: half a row of 16).
+template <int VC, int K>
+__device__ __forceinline__ double lane_bcast(double v)
+{
+    static_assert(VC == 4 || VC == 8, "groups of 4 or 8 lanes");
+    if constexpr (VC == 8) {
+        const long s = __builtin_bit_cast(long, v);
+        const long lo = __builtin_amdgcn_update_dpp(s, s, 0x150 + K, 0xf, 0xf, false);      // row_newbcast
+        const long hi = __builtin_amdgcn_update_dpp(lo, s, 0x150 + K + 8, 0xf, 0xc, false);  // upper half of the row
+        return __builtin_bit_cast(double, hi);
+    } else {
+        const int2 s = __builtin_bit_cast(int2, v);
+        int2 r;  // quad_perm
+        r.x = __builtin_amdgcn_update_dpp(s.x, s.x, K * 0x55, 0xf, 0xf, false);
+        r.y = __builtin_amdgcn_update_dpp(s.y, s.y, K * 0x55, 0xf, 0xf, false);
+        return __builtin_bit_cast(double, r);
+    }
+}
+template <int VC, int K>
+__device__ __forceinline__ float lane_bcast(float v)
+{
+    const int s = __builtin_bit_cast(int, v);
+    if constexpr (VC == 8) {
+        const int lo = __builtin_amdgcn_update_dpp(s, s, 0x150 + K, 0xf, 0xf, false);
+        return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(lo, s, 0x150 + K + 8, 0xf, 0xc, false));
+    } else {
+        return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(s, s, K * 0x55, 0xf, 0xf, false));
+    }
+}
+
+template <typename F, int... I>
+__device__ __forceinline__ void static_for_seq(F f, std::integer_sequence<int, I...>)
+{
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void static_for(F f)
+{
+    static_for_seq(f, std::make_integer_sequence<int, N>{});
+}
+
+template <int Q, int VC, typename T>
+constexpr size_t mline_lds(int G)
+{
+    return (size_t)3 * G * LineLds<Q, Q>::ELEM * VC * sizeof(T);
+}
+
+template <int Q, int VC, typename T, int G, int NT, typename OFF>
+__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4)))
+k_mline(const LineArgs<T> a)
+{
+    using L = LineLds<Q, Q>;
+    constexpr int P = Q, p = P - 1, W = G * p + 1, Q2 = Q * Q;
+    constexpr int SX = VC, SY = L::PITCH * VC, SZ = L::PLANE * VC, ELEM = L::ELEM * VC;
+    constexpr int NM = (Q + VC - 1) / VC;  // points of a z-line whose factors one lane computes
+    static_assert(G * Q2 * VC <= NT, "one line per lane");
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    T *const A = reinterpret_cast<T *>(smem_raw), *const Bb = A + G * ELEM, *const C = Bb + G * ELEM;
+    const int tid = threadIdx.x, vc = tid % VC, lt = tid / VC;
+    // chunks of vectors fastest: those of one element run side by side and share its lines in the L2
+    const unsigned nch = (a.nvec + VC - 1) / VC;
+    const unsigned xcd = blockIdx.x % kNumXcd, nq = gridDim.x / kNumXcd, nr = gridDim.x % kNumXcd;
+    const unsigned bid = xcd * nq + (xcd < nr ? xcd : nr) + blockIdx.x / kNumXcd;
+    const int vec = (int)(bid % nch) * VC + vc;
+    LinePos pos;
+    {
+        const unsigned g = bid / nch, r = g / (unsigned)a.ngx;
+        pos.ex0 = (int)(g % (unsigned)a.ngx) * G;
+        pos.nvalid = a.nex - pos.ex0 < G ? a.nex - pos.ex0 : G;
+        pos.ey0 = (int)(r % (unsigned)a.nych) * a.march;
+        pos.ey1 = pos.ey0 + a.march < a.ney ? pos.ey0 + a.march : a.ney;
+        pos.ez = (int)(r / (unsigned)a.nych);
+    }
+    const cptr<T> bas = (cptr<T>)(uintptr_t)a.bas;
+    const int nx = a.nex * p + 1, ny = a.ney * p + 1, nz = a.nez * p + 1;
+
+    // lane roles as in k_line, of line lt and vector vc
+    static_assert(G * ELEM < 1 << 14, "positions in 14 bits");
+    constexpr uint32_t kAct = 1u << 14, kDual = 1u << 15;
+    uint32_t rxz, ry, rz;
+    const int ky = lt / W, X = lt - ky * W;
+    {
+        int g = 0, i = X;
+        if constexpr (G > 1) {
+            g = X / p;
+            if (g > pos.nvalid - 1) g = pos.nvalid - 1;
+            i = X - g * p;
+        }
+        ry = 0;
+        if (lt < W * P && X <= pos.nvalid * p)
+            ry = (uint32_t)(g * ELEM + ky * SZ + i * SX + vc) | kAct | (G > 1 && i == 0 && g > 0 ? kDual : 0u);
+        const int bx = lt % Q, kx = (lt / Q) % Q, gx = lt / Q2;
+        rxz = 0;
+        if (lt < G * Q2 && gx < pos.nvalid)  // row b of plane k, and z-line (a, b)
+            rxz = (uint32_t)(gx * ELEM + kx * SZ + bx * SY + vc) | kAct |
+                  ((uint32_t)(gx * ELEM + kx * SY + bx * SX + vc) | kAct) << 16;
+        rz = (uint32_t)bx | (uint32_t)kx << 4 | (uint32_t)gx << 8;
+    }
+    const auto at = [](uint32_t r) { return (int)(r & (kAct - 1)); };
+    const int64_t stride = (int64_t)nx * a.nvec;
+    const int64_t node0 = (((int64_t)pos.ez * p * ny + (int64_t)pos.ey0 * p) * nx + (int64_t)pos.ex0 * p) * a.nvec;
+    const T *xb = a.x + node0;
+    T *yb = a.y + node0;
+    const int I = pos.ex0 * p + X, K = pos.ez * p + ky;
+    const bool io = (ry & kAct) && vec < a.nvec && !(a.dirichlet && (I == 0 || I == nx - 1 || K == 0 || K == nz - 1));
+    const OFF lane0 = ((OFF)ky * (OFF)ny * (OFF)nx + (OFF)X) * (OFF)a.nvec + (OFF)vec;
+
+    T xv[P], carry = T(0);
+#pragma unroll
+    for (int j = 0; j < P; ++j) xv[j] = io ? (xb + j * stride)[lane0] : T(0);
+    // factors of this lane's points (a, b, vc + m VC) of the element at ey
+    T gm[NM][kQdDiff];
+    auto q_load = [&](int ey) {
+        if (rxz >> 16 & kAct) {
+            const int64_t e = pos.ex0 + (int)(rz >> 8) + (int64_t)a.nex * (ey + (int64_t)a.ney * pos.ez);
+            const T *qd = a.qdata + e * (kQdDiff * Q2 * Q) + (rz >> 4 & 15) * Q + (rz & 15);
+#pragma unroll
+            for (int m = 0; m < NM; ++m) {
+                const int c = vc + m * VC < Q ? vc + m * VC : Q - 1;
+#pragma unroll
+                for (int i = 0; i < kQdDiff; ++i) gm[m][i] = __builtin_nontemporal_load(&qd[i * Q2 * Q + c * Q2]);
+            }
+        }
+    };
+    q_load(pos.ey0);
+
+    for (int ey = pos.ey0; ey < pos.ey1; ++ey) {
+        const bool more = ey + 1 < pos.ey1;
+        cptr<T> Df;
+        auto matrices = [&]() { Df = opaque<T>(bas) + basis_df(P, Q); };
+        matrices();
+        // --- Y -----------------------------------------------------------------------------
+        if (ry & kAct) {
+            const int ly = at(ry), ly2 = ly - ELEM + p * SX;
+            T v[P];
+#pragma unroll
+            for (int j = 0; j < P; ++j) v[j] = xv[j];
+            if (a.dirichlet) {
+                if (ey == 0) v[0] = T(0);
+                if (ey == a.ney - 1) v[P - 1] = T(0);
+            }
+            Folded<P, T> f;
+            f.set(v);
+            auto put = [&](T *arr, int o, T lo, T hi) {
+                arr[ly + o * SY] = lo;
+                if (2 * o + 1 != Q) arr[ly + (Q - 1 - o) * SY] = hi;
+                if (ry & kDual) {
+                    arr[ly2 + o * SY] = lo;
+                    if (2 * o + 1 != Q) arr[ly2 + (Q - 1 - o) * SY] = hi;
+                }
+            };
+#pragma unroll
+            for (int o = 0; o < (Q + 1) / 2; ++o) put(A, o, v[o], v[P - 1 - o]);
+            line_all<P, Q, -1>(Df, f, [&](int o, T lo, T hi) { put(Bb, o, lo, hi); });
+        }
+        // the next element's inputs travel behind all the stages that follow
+        if (more) {
+            xv[0] = xv[P - 1];
+            xb += p * stride;
+            if (io) {
+                gptr<const T> row = (gptr<const T>)xb;
+#pragma unroll
+                for (int j = 1; j < P; ++j) {
+                    row += stride;
+                    asm volatile("" : "+s"(row));
+                    xv[j] = row[lane0];
+                }
+            }
+        }
+        group_sync<NT>();
+        // --- X -----------------------------------------------------------------------------
+        if (rxz & kAct) {
+            const int lx = at(rxz);
+            matrices();
+            T v[P];
+            Folded<P, T> f;
+            line_read<P, SX>(A + lx, v);
+            f.set(v);
+            line_all<P, Q, -1>(Df, f, [&](int o, T lo, T hi) {
+                C[lx + o * SX] = lo;
+                if (2 * o + 1 != Q) C[lx + (Q - 1 - o) * SX] = hi;
+            });
+        }
+        group_sync<NT>();
+        // --- Z -----------------------------------------------------------------------------
+        if (rxz >> 16 & kAct) {
+            const int lz = at(rxz >> 16);
+            matrices();
+            T v[P], ur[Q], us[Q], ut[Q];
+            Folded<P, T> f;
+            line_read<P, SZ>(A + lz, v);
+            f.set(v);
+            line_all<P, Q, -1>(Df, f, [&](int o, T lo, T hi) {
+                ut[o] = lo;
+                if (2 * o + 1 != Q) ut[Q - 1 - o] = hi;
+            });
+            line_read<Q, SZ>(Bb + lz, us);
+            line_read<Q, SZ>(C + lz, ur);
+            static_for<Q>([&](auto ci) {
+                constexpr int c = ci, m = c / VC, k = c % VC;
+                T g[kQdDiff];
+#pragma unroll
+                for (int i = 0; i < kQdDiff; ++i) g[i] = lane_bcast<VC, k>(gm[m][i]);
+                const T r = ur[c], s = us[c], t = ut[c];
+                ur[c] = g[0] * r + g[5] * s + g[4] * t;
+                us[c] = g[5] * r + g[1] * s + g[3] * t;
+                ut[c] = g[4] * r + g[3] * s + g[2] * t;
+                asm volatile("" : "+v"(ur[c]), "+v"(us[c]), "+v"(ut[c]));  // one point's factors at a time
+            });
+            matrices();
+            TransAcc<P, T> t;
+            t.zero();
+            t.template add<Q, -1>(Df, ut);
+#pragma unroll
+            for (int k = 0; k < P; ++k) {
+                A[lz + k * SZ] = t.out(k);
+                Bb[lz + k * SZ] = us[k];
+                C[lz + k * SZ] = ur[k];
+            }
+        }
+        if (more) q_load(ey + 1);
+        group_sync<NT>();
+        // --- X^T ---------------------------------------------------------------------------
+        if (rxz & kAct) {
+            const int lx = at(rxz);
+            matrices();
+            T w[Q];
+            TransAcc<P, T> t;
+            t.zero();
+            line_read<Q, SX>(C + lx, w);
+            t.template add<Q, -1>(Df, w);
+#pragma unroll
+            for (int i = 0; i < P; ++i) A[lx + i * SX] += t.out(i);
+        }
+        group_sync<NT>();
+        // --- Y^T and scatter ---------------------------------------------------------------
+        if (io) {
+            const int ly = at(ry), ly2 = ly - ELEM + p * SX;
+            matrices();
+            T w[Q], out[P];
+            TransAcc<P, T> t;
+            t.zero();
+            auto get = [&](const T *arr) {
+                line_read<Q, SY>(arr + ly, w);
+                if (ry & kDual) {
+#pragma unroll
+                    for (int b = 0; b < Q; ++b) w[b] += arr[ly2 + b * SY];
+                }
+            };
+            get(Bb);
+            t.template add<Q, -1>(Df, w);
+            get(A);
+#pragma unroll
+            for (int j = 0; j < P; ++j) out[j] = t.out(j) + w[j];
+            out[0] += carry;
+            carry = out[P - 1];
+            const bool m0 = a.dirichlet && ey == 0, m1 = a.dirichlet && ey == a.ney - 1;
             gptr<T> row = (gptr<T>)yb;
             if (!m0) global_add(row + lane0, out[0]);
 #pragma unroll

@@ -172,6 +172,14 @@ constexpr bool line_variant(int mode, bool colloc, bool otf, int v)
 {
     return mode == 0 ? v < 5 && !colloc : mode == 1 && (colloc || otf ? v < 5 : v >= 9 && v <= 14);
 }
+// Collocated diffusion, several vectors: variants 6 and 7 are the line-fused multi-vector kernel (k_mline) with chunks
+// of 4 and 8 vectors; G q^2 VC lanes.  G fills the last wavefront (q <= 5) while two groups fit a CU's LDS.
+constexpr bool mline_variant(int mode, bool colloc, int v) { return mode == 1 && colloc && (v == 6 || v == 7); }
+constexpr int mline_g(int Q, int v)
+{
+    return v == 7 ? (Q == 2 ? 8 : Q == 3 ? 3 : Q == 4 ? 2 : Q == 5 ? 2 : 1) : (Q == 2 ? 16 : Q == 3 ? 7 : Q == 4 ? 4 : Q == 5 ? 2 : 1);
+}
+constexpr int mline_nt(int Q, int v) { return (mline_g(Q, v) * Q * Q * (v == 7 ? 8 : 4) + 63) / 64 * 64; }
 constexpr bool variant_gf(int v) { return v >= 9 && v <= 14; }
 // The mass operator keeps one LDS array per element instead of three and has
 // far less work per element, so at low order its single-vector variants

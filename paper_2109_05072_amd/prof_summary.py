@@ -61,6 +61,10 @@ def _short(name: str) -> str:
         kind = {"0": "mass", "1": "diffusion"}[mode]
         return (f"k_line p={int(P) - 1} q={Q} {kind}{' kappa' if vark == 'true' else ''} {T} G={G} NT={NT}"
                 f"{' det' if det == 'true' else ''}{'' if off == 'unsigned int' else ' wide'}")
+    m = re.match(r"void mfhex::k_mline<(\d+), (\d+), (\w+), (\d+), (\d+), ([\w ]+)>", name)
+    if m:
+        Q, VC, T, G, NT, off = m.groups()
+        return f"k_mline p={int(Q) - 1} q={Q} diffusion {T} G={G} NT={NT} VC={VC}{'' if off == 'unsigned int' else ' wide'}"
     m = re.match(r"void mfhex::k_mass<(\d+), (\d+), (\w+), (\w+), (\d+), (\d+), (\d+)(?:, (true|false))?>", name)
     if m:
         P, Q, colloc, T, G, NT, VC, det = m.groups()
@@ -119,7 +123,7 @@ def traffic_summary(fetch_dir: str, write_dir: str, command: str) -> str:
            f"scale fetch x{f_scale:.4f}, write x{w_scale:.4f}",
            f"{'kernel':<60} {'fetch_KiB':>12} {'write_KiB':>12} {'traffic_bytes':>15} {'avg_us':>9}"]
     for k in fe:
-        if not any(n in k for n in ("k_apply", "k_mass", "k_line")) or k not in wr:
+        if not any(n in k for n in ("k_apply", "k_mass", "k_line", "k_mline")) or k not in wr:
             continue
         f = sum(fe[k]) / len(fe[k])
         w = sum(wr[k]) / len(wr[k])
@@ -193,7 +197,7 @@ def counter_summary(dirs, command: str, sources=KERNEL_SOURCES) -> str:
     per = {}
     for k in vals:
         sk = _short(k)
-        if sk.startswith(("k_apply", "k_mass", "k_line", "k_tet")):
+        if sk.startswith(("k_apply", "k_mass", "k_line", "k_mline", "k_tet")):
             per[sk] = {c: sum(v) / len(v) for c, v in vals[k].items()}
     header = [f"# rocprofv3 counters per dispatch (mean over dispatches)", f"# command: {command}",
               f"# kernel source hash: {kernel_source_hash(sources)}", _TABLE_NOTE]
@@ -229,7 +233,7 @@ def read_traffic(path: str):
         return {}
     res = {}
     for line in txt.splitlines():
-        if line.startswith(("k_apply", "k_mass", "k_line")):
+        if line.startswith(("k_apply", "k_mass", "k_line", "k_mline")):
             parts = line.split()
             name = " ".join(parts[:-4])
             res[name] = float(parts[-2])
