@@ -921,60 +921,6 @@ k_mass(const T *__restrict__ bas, const int nex, const int64_t ngroups, const in
 }
 
 // ---------------------------------------------------------------------------
-// Coefficient gradient g[e][pt] = (Dhat r)^T G0 (Dhat u) at every point.
-// ---------------------------------------------------------------------------
-template <int P, int Q, bool COLLOC, int G, int NT>
-__global__ void __launch_bounds__(NT)
-k_kgrad(const double *__restrict__ bas, const int64_t nelem, const int32_t *__restrict__ offsets,
-        const double *__restrict__ qdata, const double *__restrict__ u, const double *__restrict__ r,
-        double *__restrict__ gout)
-{
-    using T = double;
-    constexpr int Q2 = Q * Q, Q3 = Q2 * Q;
-    constexpr int NPT = G * Q3, RQ = (NPT + NT - 1) / NT;
-    using L = Lds<Q>;
-    extern __shared__ __align__(16) unsigned char smem_raw[];
-    T *const s0 = reinterpret_cast<T *>(smem_raw);
-    T *const s1 = s0 + G * L::BUF;
-    T *const s2 = s1 + G * L::BUF;
-    T *const t0 = s2 + G * L::BUF;
-    T *const t1 = t0 + G * L::BUF;
-    T *const t2 = t1 + G * L::BUF;
-    const int tid = threadIdx.x;
-    const int64_t e0 = xcd_block(blockIdx.x, gridDim.x) * G;
-    int32_t off[NodeIO<P, G, NT, 1>::NR];
-    static_assert(G == 1, "one element per group");
-    load_offsets<P, G, NT, 1>(off, offsets, e0, 1, tid);
-    gather<P, Q, G, NT, 1, T>(s0, off, u, 1, 0, 1, tid);
-    gather<P, Q, G, NT, 1, T>(t0, off, r, 1, 0, 1, tid);
-    group_sync<NT>();
-    interp<P, Q, COLLOC, G, NT, T>(s0, bas, tid);
-    interp<P, Q, COLLOC, G, NT, T>(t0, bas, tid);
-    grad<P, Q, G, NT, T>(s0, s1, s2, bas, tid);
-    grad<P, Q, G, NT, T>(t0, t1, t2, bas, tid);
-#pragma unroll 4
-    for (int k = 0; k < RQ; ++k) {
-        const int id = tid + k * NT;
-        if (id < NPT) {
-            const int g = id / Q3, pt = id - g * Q3;
-            if (e0 + g < nelem) {
-                const int a = pt % Q, b = (pt / Q) % Q, c = pt / Q2;
-                const int ls = g * L::BUF + a + L::PITCH * b + L::PLANE * c;
-                const T *qd = qdata + (e0 + g) * (kQdDiff * Q3) + pt;
-                T gm[kQdDiff];
-#pragma unroll
-                for (int m = 0; m < kQdDiff; ++m) gm[m] = __builtin_nontemporal_load(&qd[m * Q3]);
-                const T ur = s1[ls], us = s2[ls], ut = s0[ls];
-                const T vr = gm[0] * ur + gm[5] * us + gm[4] * ut;
-                const T vs = gm[5] * ur + gm[1] * us + gm[3] * ut;
-                const T vt = gm[4] * ur + gm[3] * us + gm[2] * ut;
-                __builtin_nontemporal_store(t1[ls] * vr + t2[ls] * vs + t0[ls] * vt, &gout[(e0 + g) * Q3 + pt]);
-            }
-        }
-    }
-}
-
-// ---------------------------------------------------------------------------
 // Host launchers for one (P, Q) pair.
 // ---------------------------------------------------------------------------
 template <typename K>
@@ -989,12 +935,12 @@ static hipError_t prepare_lds(K kernel, size_t lds)
 // depth (mass) or 8, and no more than leave four
 // rounds of resident groups on the chip (16384 wavefronts), since a march trades parallelism for carried faces.
 // (p = 3, 5, 7 at 1e7 nodes: 2, 4 and 8 within 3%, 16 up to 10% slower.)
-static int line_march(const ApplyLaunch &a, int64_t columns, int nt)
+static int line_march(int mode, int chain, bool auto_chain, int ney, int64_t columns, int nt)
 {
-    const int64_t cap = a.mode == kMass ? a.chain : 8;
-    int64_t m = columns * a.v.ney * (nt / 64) / 16384;
-    m = m < cap && (a.mode != kMass || a.auto_chain) ? m : cap;
-    m = m < a.v.ney ? m : a.v.ney;
+    const int64_t cap = mode == kMass ? chain : 8;
+    int64_t m = columns * ney * (nt / 64) / 16384;
+    m = m < cap && (mode != kMass || auto_chain) ? m : cap;
+    m = m < ney ? m : ney;
     return (int)(m < 1 ? 1 : m);
 }
 
@@ -1019,7 +965,7 @@ static hipError_t launch_line_v(const ApplyLaunch &a)
     k.dirichlet = a.dirichlet;
     k.nvec = a.nvec;
     k.ngx = (a.v.nex + G - 1) / G;
-    k.march = line_march(a, (int64_t)k.ngx * a.v.nez * a.nvec, NT);
+    k.march = line_march(a.mode, a.chain, a.auto_chain, a.v.ney, (int64_t)k.ngx * a.v.nez * a.nvec, NT);
     k.nych = (a.v.ney + k.march - 1) / k.march;
     const int64_t nblk = (int64_t)k.ngx * k.nych * a.v.nez;
     auto go = [&](auto kern) {
@@ -1054,7 +1000,7 @@ static hipError_t launch_mline_v(const ApplyLaunch &a)
     k.nvec = a.nvec;
     k.ngx = (a.v.nex + G - 1) / G;
     const int nch = (a.nvec + VC - 1) / VC;
-    k.march = line_march(a, (int64_t)k.ngx * a.v.nez * nch, NT);
+    k.march = line_march(a.mode, a.chain, a.auto_chain, a.v.ney, (int64_t)k.ngx * a.v.nez * nch, NT);
     k.nych = (a.v.ney + k.march - 1) / k.march;
     const int64_t nblk = (int64_t)k.ngx * k.nych * a.v.nez * nch;
     auto go = [&](auto kern) {
@@ -1179,14 +1125,26 @@ static hipError_t launch_apply_pq(const ApplyLaunch &a)
 template <int P, int Q, bool COLLOC>
 static hipError_t launch_kgrad_pq(const KgradLaunch &a)
 {
-    constexpr int G = 1, NT = Q <= 6 ? 64 : 128;
-    const int64_t nblk = a.v.nelem;
-    const size_t lds = (size_t)G * 6 * Lds<Q>::BUF * sizeof(double);
+    constexpr int G = kgrad_g(Q), NT = (2 * G * Q * Q + 63) / 64 * 64;
+    constexpr size_t lds = kgrad_lds<P, Q>(G);
+    static_assert(lds <= kMaxLds, "LDS of a coefficient gradient group");
+    KgradArgs k{};
+    k.bas = a.basis_dev;
+    k.vert = a.vert;
+    k.u = a.u;
+    k.r = a.r;
+    k.g = a.g;
+    k.nex = a.v.nex;
+    k.ney = a.v.ney;
+    k.nez = a.v.nez;
+    k.dirichlet = a.dirichlet;
+    k.ngx = (a.v.nex + G - 1) / G;
+    k.march = line_march(kDiff, 0, true, a.v.ney, (int64_t)k.ngx * a.v.nez, NT);
+    k.nych = (a.v.ney + k.march - 1) / k.march;
     auto kern = k_kgrad<P, Q, COLLOC, G, NT>;
-    hipError_t err = prepare_lds(kern, lds);
-    if (err != hipSuccess) return err;
-    hipLaunchKernelGGL(kern, dim3((unsigned)nblk), dim3(NT), lds, a.stream, a.basis_dev, a.v.nelem, a.v.offsets,
-                       static_cast<const double *>(a.v.qdata), a.u, a.r, a.g);
+    const hipError_t e = prepare_lds(kern, lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3((unsigned)((int64_t)k.ngx * k.nych * a.v.nez)), dim3(NT), lds, a.stream, k);
     return hipGetLastError();
 }
 

@@ -573,6 +573,8 @@ int mfhex_kappa_grad(mfhex_op op, const double *u_dev, const double *r_dev, doub
     a.P = op->P;
     a.colloc = op->basis.colloc;
     a.basis_dev = op->basis64;
+    a.vert = op->vert;
+    a.dirichlet = op->d.dirichlet;
     a.u = u_dev;
     a.r = r_dev;
     a.g = g_dev;

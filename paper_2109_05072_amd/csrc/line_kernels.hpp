@@ -94,13 +94,14 @@ struct Folded {
     }
 };
 
-// Output pair (o, NO-1-o) of a contraction of a folded line; SYM +1: M[NO-1-o][NI-1-i] = M[o][i], -1: = -M[o][i].
+// Even and odd half of the output pair (o, NO-1-o) of a contraction of a folded line: the outputs are E + O and, for
+// SYM +1 (M[NO-1-o][NI-1-i] = M[o][i]), E - O, for SYM -1 (M[NO-1-o][NI-1-i] = -M[o][i]) O - E.
 template <int NI, int NO, int SYM, typename T>
-__device__ __forceinline__ void line_pair(cptr<T> M, const Folded<NI, T> &f, int o, T &lo, T &hi)
+__device__ __forceinline__ void line_pair(cptr<T> M, const Folded<NI, T> &f, int o, T &E, T &O)
 {
     constexpr int H = NI / 2;
     const cptr<T> row = M + o * NI;
-    T E = T(0), O = T(0);
+    E = T(0), O = T(0);
     const bool middle = 2 * o + 1 == NO;  // one output: only its even (SYM +1) or odd (-1) half is non-zero
 #pragma unroll
     for (int i = 0; i < H; ++i) {
@@ -109,25 +110,31 @@ __device__ __forceinline__ void line_pair(cptr<T> M, const Folded<NI, T> &f, int
     }
     if constexpr (NI & 1)
         if (!middle || SYM > 0) E += row[2 * H] * f.e[H];
-    lo = E + O;
-    hi = SYM > 0 ? E - O : O - E;
 }
 
-// All output pairs of a contraction: put(o, lo, hi).
+// All output pairs of a contraction: put(o, E, O, E + O).
 template <int NI, int NO, int SYM, typename T, typename Put>
-__device__ __forceinline__ void line_all(cptr<T> M, const Folded<NI, T> &f, Put put)
+__device__ __forceinline__ void line_halves(cptr<T> M, const Folded<NI, T> &f, Put put)
 {
     constexpr bool TIE = rows_in_flight(NI, NO, sizeof(T));
     if (TIE) M = after<T>(M, f.e[0]);
     cptr<T> cur = M, next = M;
 #pragma unroll
     for (int o = 0; o < (NO + 1) / 2; ++o) {
-        T lo, hi;
-        line_pair<NI, NO, SYM>(cur, f, o, lo, hi);
+        T E, O;
+        line_pair<NI, NO, SYM>(cur, f, o, E, O);
         cur = next;
+        T lo = E + O;
         if (TIE) next = after<T>(M, lo);
-        put(o, lo, hi);
+        put(o, E, O, lo);
     }
+}
+
+// The same as put(o, lo, hi) of the outputs o and NO-1-o.
+template <int NI, int NO, int SYM, typename T, typename Put>
+__device__ __forceinline__ void line_all(cptr<T> M, const Folded<NI, T> &f, Put put)
+{
+    line_halves<NI, NO, SYM>(M, f, [&](int o, T E, T O, T lo) { put(o, lo, SYM > 0 ? E - O : O - E); });
 }
 
 // Transposed contraction of a line of NO values with the same folded rows, accumulated over several matrices:
@@ -959,6 +966,257 @@ k_mline(const LineArgs<T> a)
             if (!more && !m1) global_add(row + stride + lane0, out[P - 1]);
         }
         yb += p * stride;
+        if (more) group_sync<NT>();
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Coefficient gradient g[e][pt] = (Dhat r)^T G0 (Dhat u) at every point: the
+// forward stages of k_line for both vectors at once, on neighbouring lanes (u
+// even, r odd).  The lanes of a pair share the points of their z-line, o of the
+// one and Q-1-o of the other, the two outputs that a folded row gives: a lane
+// forms E +- O and E -+ O with the signs of its side, keeps its own point's
+// value and hands the other one over by a DPP swap, so that the geometry of a
+// point is evaluated once (both lanes at every point: 238 against 219 us at
+// p = 6, 327 against 314 at p = 4, 1e7 nodes).
+// Before, one element per wavefront with six LDS arrays and stored factors, and
+// now: Gauss, 1e7 nodes, p = 4 510 -> 314 us, p = 6 434 -> 219; 3e6 nodes,
+// p = 2 370 -> 191, p = 8 154 -> 69.  p = 4 moves 0.43 GB (90 us); the FP64
+// issue is about 190 us of its 314, the rest is the latency of three stages.
+// ---------------------------------------------------------------------------
+struct KgradArgs {
+    const double *bas, *vert, *u, *r;
+    double *g;
+    int nex, ney, nez, dirichlet;
+    int ngx, nych, march;
+};
+
+// The value of the other lane of the pair.
+__device__ __forceinline__ double lane_swap(double v)
+{
+    int2 s = __builtin_bit_cast(int2, v);
+    s.x = __builtin_amdgcn_update_dpp(s.x, s.x, 0xb1, 0xf, 0xf, false);  // quad_perm [1, 0, 3, 2]
+    s.y = __builtin_amdgcn_update_dpp(s.y, s.y, 0xb1, 0xf, 0xf, false);
+    return __builtin_bit_cast(double, s);
+}
+
+template <int P, int Q>
+constexpr size_t kgrad_lds(int G)
+{
+    return ((size_t)6 * G * LineLds<P, Q>::ELEM + (size_t)G * kTriCoef + 2 * Q + 12 * (G + 1)) * 8;
+}
+
+template <int P, int Q, bool COLLOC, int G, int NT>
+__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(line_waves(Q, kDiff))))
+k_kgrad(const KgradArgs a)
+{
+    using L = LineLds<P, Q>;
+    using T = double;
+    constexpr int p = P - 1, W = G * p + 1, Q2 = Q * Q, Q3 = Q2 * Q;
+    constexpr int SX = 2, SY = L::PITCH * 2, SZ = L::PLANE * 2, ELEM = L::ELEM * 2;
+    constexpr int NOH = (Q + 1) / 2;
+    static_assert(2 * G * Q2 <= NT, "one line of one vector per lane");
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    T *const A = reinterpret_cast<T *>(smem_raw), *const Bb = A + G * ELEM, *const C = Bb + G * ELEM;
+    T *const sC = C + G * ELEM;
+    const int tid = threadIdx.x, vec = tid & 1, lt = tid >> 1;
+    const LinePos pos = line_pos_of<G>(a, blockIdx.x, gridDim.x);
+    const cptr<T> bas = (cptr<T>)(uintptr_t)a.bas;
+    const int nx = a.nex * p + 1, ny = a.ney * p + 1, nz = a.nez * p + 1;
+
+    // lane roles as in k_line, of line lt and vector vec
+    static_assert(G * ELEM < 1 << 14, "positions in 14 bits");
+    constexpr uint32_t kAct = 1u << 14, kDual = 1u << 15;
+    uint32_t rxz, ry, rz;
+    const int ky = lt / W, X = lt - ky * W;
+    {
+        int g = 0, i = X;
+        if constexpr (G > 1) {
+            g = X / p;
+            if (g > pos.nvalid - 1) g = pos.nvalid - 1;
+            i = X - g * p;
+        }
+        ry = 0;
+        if (lt < W * P && X <= pos.nvalid * p)
+            ry = (uint32_t)(g * ELEM + ky * SZ + i * SX + vec) | kAct | (G > 1 && i == 0 && g > 0 ? kDual : 0u);
+        const int bx = lt % Q, kx = (lt / Q) % P, gx = lt / (Q * P);
+        rxz = 0;
+        if (lt < G * P * Q && gx < pos.nvalid) rxz = (uint32_t)(gx * ELEM + kx * SZ + bx * SY + vec) | kAct;
+        const int az = lt % Q, bz = (lt / Q) % Q, gz = lt / Q2;
+        if (lt < G * Q2 && gz < pos.nvalid) rxz |= ((uint32_t)(gz * ELEM + bz * SY + az * SX + vec) | kAct) << 16;
+        rz = (uint32_t)az | (uint32_t)bz << 4 | (uint32_t)gz << 8;
+    }
+    const auto at = [](uint32_t v) { return (int)(v & (kAct - 1)); };
+    const int I = pos.ex0 * p + X, K = pos.ez * p + ky;
+    const bool io = (ry & kAct) && !(a.dirichlet && (I == 0 || I == nx - 1 || K == 0 || K == nz - 1));
+    gptr<const T> xb = (gptr<const T>)(vec ? a.r : a.u) + ((int64_t)K * ny + (int64_t)pos.ey0 * p) * nx + I;
+
+    T xv[P];
+#pragma unroll
+    for (int j = 0; j < P; ++j) xv[j] = io ? xb[(int64_t)j * nx] : T(0);
+
+    // vertices and trilinear coefficients as in k_line
+    constexpr int VP = 6 * (G + 1), RV = (VP + NT - 1) / NT, RC = (G * kTriCoef + NT - 1) / NT;
+    T *const sR = sC + G * kTriCoef, *const sV = sR + 2 * Q;
+    double vtx[RV];
+    auto vtx_load = [&](int vy) {
+#pragma unroll
+        for (int r = 0; r < RV; ++r) {
+            const int t = tid + r * NT, z = t / (VP / 2), c = t - z * (VP / 2);
+            if (t < VP && c < 3 * (pos.nvalid + 1))
+                vtx[r] = a.vert[3 * (pos.ex0 + (int64_t)(a.nex + 1) * (vy + (int64_t)(a.ney + 1) * (pos.ez + z))) + c];
+        }
+    };
+    auto vtx_store = [&](int vy) {
+#pragma unroll
+        for (int r = 0; r < RV; ++r)
+            if (tid + r * NT < VP) sV[(vy & 1) * VP + tid + r * NT] = vtx[r];
+    };
+    vtx_load(pos.ey0);
+    vtx_store(pos.ey0);
+    vtx_load(pos.ey0 + 1);
+    if (tid < 2 * Q) sR[tid] = a.bas[basis_xq(P, Q) + tid];
+    for (int ey = pos.ey0; ey < pos.ey1; ++ey) {
+        const bool more = ey + 1 < pos.ey1;
+        cptr<T> Bf, Gf;
+        auto matrices = [&]() {
+            const cptr<T> b = opaque<T>(bas);
+            Bf = b + basis_bf(P, Q);
+            Gf = b + (COLLOC ? basis_df(P, Q) : basis_gf(P, Q));
+        };
+        matrices();
+        // --- Y -----------------------------------------------------------------------------
+        vtx_store(ey + 1);
+        if (ry & kAct) {
+            const int ly = at(ry), ly2 = ly - ELEM + p * SX;
+            T v[P];
+#pragma unroll
+            for (int j = 0; j < P; ++j) v[j] = xv[j];
+            if (a.dirichlet) {
+                if (ey == 0) v[0] = T(0);
+                if (ey == a.ney - 1) v[P - 1] = T(0);
+            }
+            Folded<P, T> f;
+            f.set(v);
+            auto put = [&](T *arr, int o, T lo, T hi) {
+                arr[ly + o * SY] = lo;
+                if (2 * o + 1 != Q) arr[ly + (Q - 1 - o) * SY] = hi;
+                if (ry & kDual) {
+                    arr[ly2 + o * SY] = lo;
+                    if (2 * o + 1 != Q) arr[ly2 + (Q - 1 - o) * SY] = hi;
+                }
+            };
+            if constexpr (COLLOC) {
+#pragma unroll
+                for (int o = 0; o < NOH; ++o) put(A, o, v[o], v[P - 1 - o]);
+            } else {
+                line_all<P, Q, 1>(Bf, f, [&](int o, T lo, T hi) { put(A, o, lo, hi); });
+            }
+            line_all<P, Q, -1>(Gf, f, [&](int o, T lo, T hi) { put(Bb, o, lo, hi); });
+        }
+        if (more) {
+            vtx_load(ey + 2);
+            xv[0] = xv[P - 1];
+            xb += (int64_t)p * nx;
+            if (io) {
+#pragma unroll
+                for (int j = 1; j < P; ++j) xv[j] = xb[(int64_t)j * nx];
+            }
+        }
+        group_sync<NT>();
+        // --- X -----------------------------------------------------------------------------
+#pragma unroll
+        for (int r = 0; r < RC; ++r) {
+            int t = tid + r * NT;
+            asm volatile("" : "+v"(t));
+            if (t < pos.nvalid * kTriCoef) {
+                const int g = t / kTriCoef, c = t - g * kTriCoef, m = c / 3;
+                sC[t] = tri_coef(sV + 3 * g + (c - 3 * m), (ey & 1) * VP, VP - (ey & 1) * VP, VP / 2, m + 1);
+            }
+        }
+        if (rxz & kAct) {
+            const int lx = at(rxz);
+            matrices();
+            T v[P];
+            Folded<P, T> f;
+            auto put = [&](T *arr, int o, T lo, T hi) {
+                arr[lx + o * SX] = lo;
+                if (2 * o + 1 != Q) arr[lx + (Q - 1 - o) * SX] = hi;
+            };
+            line_read<P, SX>(A + lx, v);
+            f.set(v);
+            line_all<P, Q, -1>(Gf, f, [&](int o, T lo, T hi) { put(C, o, lo, hi); });
+            if constexpr (!COLLOC) {
+                line_all<P, Q, 1>(Bf, f, [&](int o, T lo, T hi) { put(A, o, lo, hi); });
+                line_read<P, SX>(Bb + lx, v);
+                f.set(v);
+                line_all<P, Q, 1>(Bf, f, [&](int o, T lo, T hi) { put(Bb, o, lo, hi); });
+            }
+        }
+        group_sync<NT>();
+        // --- Z -----------------------------------------------------------------------------
+        if (rxz >> 16 & kAct) {
+            const int lz = at(rxz >> 16), az = rz & 15, bz = rz >> 4 & 15, gz = rz >> 8;
+            matrices();
+            T v[P];
+            Folded<P, T> f;
+            // [0]: the lane's points, o of u's lane and Q-1-o of r's; [1]: the other lane's
+            T ur[2][NOH], us[2][NOH], ut[2][NOH];
+            const T sg = vec ? T(-1) : T(1);
+            auto split = [&](T (&u)[2][NOH], cptr<T> M, const T *arr, auto sym) {
+                line_read<P, SZ>(arr + lz, v);
+                f.set(v);
+                line_halves<P, Q, decltype(sym)::value>(M, f, [&](int o, T E, T O, T) {
+                    const T x = decltype(sym)::value > 0 ? E : O, y = decltype(sym)::value > 0 ? O : E;
+                    u[0][o] = x + sg * y;
+                    u[1][o] = x - sg * y;
+                });
+            };
+            split(ut, Gf, A, std::integral_constant<int, -1>{});
+            if constexpr (COLLOC) {
+                const int l0 = vec ? lz + (Q - 1) * SZ : lz, l1 = vec ? lz : lz + (Q - 1) * SZ, st = vec ? -SZ : SZ;
+#pragma unroll
+                for (int o = 0; o < NOH; ++o) {
+                    us[0][o] = Bb[l0 + o * st];
+                    us[1][o] = Bb[l1 - o * st];
+                    ur[0][o] = C[l0 + o * st];
+                    ur[1][o] = C[l1 - o * st];
+                }
+            } else {
+                split(us, Bf, Bb, std::integral_constant<int, 1>{});
+                split(ur, Bf, C, std::integral_constant<int, 1>{});
+            }
+            ZLineGeom g;
+            g.set(sC + gz * kTriCoef, sR[az], sR[bz]);
+            const double wz = sR[Q + az] * sR[Q + bz];
+            const int c0 = vec ? Q - 1 : 0, cs = vec ? -1 : 1;
+            gptr<T> out = (gptr<T>)a.g + (pos.ex0 + gz + (int64_t)a.nex * (ey + (int64_t)a.ney * pos.ez)) * Q3 +
+                          c0 * Q2 + bz * Q + az;
+#pragma unroll
+            for (int o = 0; o < NOH; ++o) {
+                g.pin();
+                double jr[3], js[3], r2[3], h[3], q[3];
+                g.columns(sR[c0 + cs * o], jr, js);
+                cross(jr, js, r2);
+                const double f0 = wz * sR[Q + c0 + cs * o] * fast_rcp(dot3(g.jt, r2));
+                double d = ur[0][o], e = us[0][o], t = ut[0][o];
+#pragma unroll
+                for (int k = 0; k < 3; ++k) h[k] = e * jr[k] - d * js[k];
+                cross(g.jt, h, q);
+#pragma unroll
+                for (int k = 0; k < 3; ++k) q[k] += t * r2[k];
+                d = lane_swap(ur[1][o]), e = lane_swap(us[1][o]), t = lane_swap(ut[1][o]);
+#pragma unroll
+                for (int k = 0; k < 3; ++k) h[k] = e * jr[k] - d * js[k];
+                double q2[3];
+                cross(g.jt, h, q2);
+#pragma unroll
+                for (int k = 0; k < 3; ++k) q2[k] += t * r2[k];
+                double val = f0 * dot3(q, q2);
+                asm volatile("" : "+v"(val));
+                if (2 * o + 1 != Q || !vec) __builtin_nontemporal_store(val, out + cs * o * Q2);
+            }
+        }
         if (more) group_sync<NT>();
     }
 }

@@ -88,9 +88,10 @@ struct DiagLaunch {
 struct KgradLaunch {
     OpView v;
     int P, colloc;
-    const double *basis_dev;
+    const double *basis_dev, *vert;
     const double *u, *r;
     double *g;
+    int dirichlet;
     hipStream_t stream;
 };
 
@@ -180,6 +181,12 @@ constexpr int mline_g(int Q, int v)
     return v == 7 ? (Q == 2 ? 8 : Q == 3 ? 3 : Q == 4 ? 2 : Q == 5 ? 2 : 1) : (Q == 2 ? 16 : Q == 3 ? 7 : Q == 4 ? 4 : Q == 5 ? 2 : 1);
 }
 constexpr int mline_nt(int Q, int v) { return (mline_g(Q, v) * Q * Q * (v == 7 ? 8 : 4) + 63) / 64 * 64; }
+// Elements of a coefficient gradient group (q = 2 .. 10), two lanes per z-line: the lanes of a wavefront filled at low q
+// (q = 5, 6 Gauss, G = 5, 3 against 2, 1: 129, 327 against 155, 395 us at 3e6 and 1e7 nodes); from q = 7 one element,
+// whose two or three wavefronts hide more than a larger group's fuller ones (q = 7: 109 us, 163 with G = 3; q = 9: 70,
+// 103 with G = 2).
+constexpr int kKgradG[9] = {8, 7, 4, 5, 3, 1, 1, 1, 1};
+constexpr int kgrad_g(int Q) { return kKgradG[Q - 2]; }
 constexpr bool variant_gf(int v) { return v >= 9 && v <= 14; }
 // The mass operator keeps one LDS array per element instead of three and has
 // far less work per element, so at low order its single-vector variants
