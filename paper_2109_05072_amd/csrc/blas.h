@@ -25,23 +25,23 @@ enum : int {
     kScRZTmp = 12,
     kNumSc = 16
 };
-enum : int { kFinStore = 0, kFinAlpha = 1, kFinBeta = 2, kFinAlphaPre = 3, kFinBetaPre = 4 };
-
 // prec arguments are MFHEX_F64 / MFHEX_F32.
 hipError_t launch_dot(const void *a, int pa, const void *b, int pb, int64_t n, double *partial, hipStream_t s);
-// kFinStore: sc[k] = sum; kFinAlpha: pAp, alpha = rr / pAp (flag on pAp <= 0);
-// kFinBeta: rr_new, beta = rr_new / rr, rr = rr_new, hist[k] = sqrt(rr_new).
-// Preconditioned forms: kFinAlphaPre: alpha = rz / pAp; kFinBetaPre: the
-// partials hold r.r then r.z (2 kRedBlocks): rr = rr_new, beta = rz_new / rz,
-// rz = rz_new, hist[k] = sqrt(rr_new).
-hipError_t launch_finalize(const double *partial, double *sc, int op, int k, double *hist, int hist_len,
-                           hipStream_t s);
-hipError_t launch_update_xr(double *x, void *r, const void *p, const void *Ap, int prec, const double *sc, int64_t n,
-                            double *partial, hipStream_t s);
-hipError_t launch_update_p(const void *r, void *p, int prec, const double *sc, int64_t n, hipStream_t s);
-// x += alpha p; r -= alpha Ap; z = dinv r; partials of r.r and r.z (2 kRedBlocks).
+// sc[k] = the sum of the partials.
+hipError_t launch_finalize(const double *partial, double *sc, int k, hipStream_t s);
+// From partials of r.r (and, preconditioned, of r.z after them): rr = rr_new, rz = rz_new, beta = rr_new / rr_prev or
+// rz_new / rz_prev, hist[k] = sqrt(rr_new).
+hipError_t launch_beta(const double *partial, double *sc, bool pre, int k, double *hist, int hist_len, hipStream_t s);
+// alpha = rr / pAp or, preconditioned, rz / pAp, with the partials pap of p.Ap (flag on pAp <= 0; rr and rz saved as
+// the previous ones); x += alpha p; r -= alpha Ap; partials of r.r (other memory than pap).
+hipError_t launch_update_xr(double *x, void *r, const void *p, const void *Ap, int prec, const double *pap, double *sc,
+                            bool pre, int64_t n, double *partial, hipStream_t s);
+// launch_beta's step unless partial is null (then the stored beta); p = r + beta p; zero = 0 unless null.
+hipError_t launch_update_p(const void *r, void *p, void *zero, int prec, const double *partial, double *sc, bool pre,
+                           int k, double *hist, int hist_len, int64_t n, hipStream_t s);
+// Preconditioned launch_update_xr with z = dinv r and partials of r.r and r.z (2 kRedBlocks).
 hipError_t launch_update_xrz(double *x, void *r, const void *p, const void *Ap, const void *dinv, void *z, int prec,
-                             const double *sc, int64_t n, double *partial, hipStream_t s);
+                             const double *pap, double *sc, int64_t n, double *partial, hipStream_t s);
 // z = dinv r; partials of r.z (kRedBlocks).
 hipError_t launch_precond(const void *r, const void *dinv, void *z, int prec, int64_t n, double *partial,
                           hipStream_t s);

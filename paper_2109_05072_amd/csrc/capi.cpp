@@ -124,7 +124,7 @@ CgLayout cg_layout(int64_t n)
     L.ap32 = o;
     o += al(n * 4);
     L.partial = o;
-    o += al(2 * kRedBlocks * 8);
+    o += al(3 * kRedBlocks * 8);
     L.sc = o;
     o += al(kNumSc * 8);
     L.hist = o;

@@ -2,9 +2,9 @@
 //
 // FP64 mode: unpreconditioned Hestenes-Stiefel CG (the solver Sec. 1 pairs with
 // sum-factorized operator evaluation; the benchmarks of Sec. 2 run it
-// unpreconditioned).  One iteration is apply, dot, fused x/r update with the
-// new residual norm, and the direction update; alpha and beta never leave the
-// GPU.  The host reads the scalars back every `check_every` iterations.  When
+// unpreconditioned).  One iteration is apply, dot, fused x/r update with alpha
+// and the new residual norm, and the direction update with beta, which also
+// clears Ap; alpha and beta never leave the GPU.  The host reads the scalars back every `check_every` iterations.  When
 // the recursive residual reaches the tolerance, the true residual b - A x is
 // computed; the solve stops only if it meets the tolerance too, and otherwise
 // continues from it.
@@ -66,7 +66,7 @@ int read_scalars(Ctx &ctx)
 int dot_store(Ctx &ctx, const void *a, int pa, const void *b, int pb, int slot)
 {
     HIP(launch_dot(a, pa, b, pb, ctx.n, ctx.partial, ctx.s), "dot kernel");
-    HIP(launch_finalize(ctx.partial, ctx.sc, kFinStore, slot, nullptr, 0, ctx.s), "finalize kernel");
+    HIP(launch_finalize(ctx.partial, ctx.sc, slot, ctx.s), "finalize kernel");
     return MFHEX_OK;
 }
 
@@ -80,7 +80,7 @@ int precond_store(Ctx &ctx, int prec, const void *r, void *z, int slot)
         const void *dinv = prec == MFHEX_F64 ? (const void *)ctx.dinv64 : (const void *)ctx.dinv32;
         HIP(launch_precond(r, dinv, z, prec, ctx.n, ctx.partial, ctx.s), "preconditioner kernel");
     }
-    HIP(launch_finalize(ctx.partial, ctx.sc, kFinStore, slot, nullptr, 0, ctx.s), "finalize kernel");
+    HIP(launch_finalize(ctx.partial, ctx.sc, slot, ctx.s), "finalize kernel");
     return MFHEX_OK;
 }
 
@@ -89,7 +89,7 @@ int true_residual(Ctx &ctx, const double *b, const double *x, double *r64, float
 {
     TRY(apply_impl(ctx.op, MFHEX_F64, 1, x, ctx.ap64, ctx.s, true, -1));
     HIP(launch_residual(b, ctx.ap64, r64, r32, ctx.n, ctx.partial, ctx.s), "residual kernel");
-    HIP(launch_finalize(ctx.partial, ctx.sc, kFinStore, kScRRTrue, nullptr, 0, ctx.s), "finalize kernel");
+    HIP(launch_finalize(ctx.partial, ctx.sc, kScRRTrue, ctx.s), "finalize kernel");
     return MFHEX_OK;
 }
 
@@ -101,10 +101,10 @@ int cg64(Ctx &ctx, const double *b, double *x, const mfhex_cg_opts &o, bool x0_z
     if (x0_zero) {
         HIP(hipMemsetAsync(x, 0, n * sizeof(double), ctx.s), "hipMemsetAsync");
         HIP(launch_residual(b, nullptr, ctx.r64, nullptr, n, ctx.partial, ctx.s), "residual kernel");
-        HIP(launch_finalize(ctx.partial, ctx.sc, kFinStore, kScRR, nullptr, 0, ctx.s), "finalize kernel");
+        HIP(launch_finalize(ctx.partial, ctx.sc, kScRR, ctx.s), "finalize kernel");
     } else {
         TRY(true_residual(ctx, b, x, ctx.r64, nullptr));
-        HIP(launch_finalize(ctx.partial, ctx.sc, kFinStore, kScRR, nullptr, 0, ctx.s), "finalize kernel");
+        HIP(launch_finalize(ctx.partial, ctx.sc, kScRR, ctx.s), "finalize kernel");
     }
     if (ctx.pre) TRY(precond_store(ctx, MFHEX_F64, ctx.r64, ctx.z64, kScRZ));
     double *const zr = ctx.pre ? ctx.z64 : ctx.r64;  // search directions come from z (= r unpreconditioned)
@@ -113,28 +113,28 @@ int cg64(Ctx &ctx, const double *b, double *x, const mfhex_cg_opts &o, bool x0_z
     const int every = std::max(1, o.check_every);
     int k = k0;
     int status = MFHEX_ERR_NOCONV;
+    double *const pap = ctx.partial + 2 * kRedBlocks;
+    bool zeroed = false;  // the direction update has cleared Ap
     while (k < o.maxit) {
-        TRY(apply_impl(ctx.op, MFHEX_F64, 1, ctx.p64, ctx.ap64, ctx.s, true, -1));
-        HIP(launch_dot(ctx.p64, MFHEX_F64, ctx.ap64, MFHEX_F64, n, ctx.partial, ctx.s), "dot kernel");
-        HIP(launch_finalize(ctx.partial, ctx.sc, ctx.pre ? kFinAlphaPre : kFinAlpha, 0, nullptr, 0, ctx.s),
-            "finalize kernel");
-        if (ctx.mg) {
-            // r.r from the update, then z = V(r) and r.z into the second half of the partials
-            HIP(launch_update_xr(x, ctx.r64, ctx.p64, ctx.ap64, MFHEX_F64, ctx.sc, n, ctx.partial, ctx.s),
+        TRY(apply_impl(ctx.op, MFHEX_F64, 1, ctx.p64, ctx.ap64, ctx.s, !zeroed, -1));
+        HIP(launch_dot(ctx.p64, MFHEX_F64, ctx.ap64, MFHEX_F64, n, pap, ctx.s), "dot kernel");
+        if (ctx.pre && !ctx.mg) {
+            HIP(launch_update_xrz(x, ctx.r64, ctx.p64, ctx.ap64, ctx.dinv64, ctx.z64, MFHEX_F64, pap, ctx.sc, n,
+                                  ctx.partial, ctx.s),
                 "update kernel");
+        } else {
+            HIP(launch_update_xr(x, ctx.r64, ctx.p64, ctx.ap64, MFHEX_F64, pap, ctx.sc, ctx.pre, n, ctx.partial, ctx.s),
+                "update kernel");
+        }
+        if (ctx.mg) {
+            // z = V(r) and r.z into the second half of the partials
             TRY(mg_vcycle(ctx.op, ctx.r64, ctx.z64, ctx.s));
             HIP(launch_dot(ctx.r64, MFHEX_F64, ctx.z64, MFHEX_F64, n, ctx.partial + kRedBlocks, ctx.s), "dot kernel");
-        } else if (ctx.pre)
-            HIP(launch_update_xrz(x, ctx.r64, ctx.p64, ctx.ap64, ctx.dinv64, ctx.z64, MFHEX_F64, ctx.sc, n, ctx.partial,
-                                  ctx.s),
-                "update kernel");
-        else
-            HIP(launch_update_xr(x, ctx.r64, ctx.p64, ctx.ap64, MFHEX_F64, ctx.sc, n, ctx.partial, ctx.s),
-                "update kernel");
+        }
         ++k;
-        HIP(launch_finalize(ctx.partial, ctx.sc, ctx.pre ? kFinBetaPre : kFinBeta, k, ctx.hist, kHist, ctx.s),
-            "finalize kernel");
-        if (!exact && (k % every == 0 || k == o.maxit)) {
+        const bool check = !exact && (k % every == 0 || k == o.maxit);
+        if (check) HIP(launch_beta(ctx.partial, ctx.sc, ctx.pre, k, ctx.hist, kHist, ctx.s), "beta kernel");
+        if (check) {
             TRY(read_scalars(ctx));
             const double *h = ctx.op->pinned;
             if (h[kScFlag] != 0.0) {
@@ -169,7 +169,10 @@ int cg64(Ctx &ctx, const double *b, double *x, const mfhex_cg_opts &o, bool x0_z
                 HIP(hipStreamSynchronize(ctx.s), "hipStreamSynchronize");
             }
         }
-        HIP(launch_update_p(zr, ctx.p64, MFHEX_F64, ctx.sc, n, ctx.s), "update kernel");
+        zeroed = !ctx.op->ebuf && k < o.maxit;
+        HIP(launch_update_p(zr, ctx.p64, zeroed ? ctx.ap64 : nullptr, MFHEX_F64, check ? nullptr : ctx.partial, ctx.sc,
+                            ctx.pre, k, ctx.hist, kHist, n, ctx.s),
+            "update kernel");
     }
     if (exact) {
         TRY(read_scalars(ctx));
@@ -239,7 +242,7 @@ int cg_solve(mfhex_op op, const double *b, double *x, void *work, const mfhex_cg
         if (o->x0_is_zero) {
             HIP(hipMemsetAsync(x, 0, n * sizeof(double), s), "hipMemsetAsync");
             HIP(launch_residual(b, nullptr, nullptr, ctx.r32, n, ctx.partial, s), "residual kernel");
-            HIP(launch_finalize(ctx.partial, ctx.sc, kFinStore, kScRRTrue, nullptr, 0, s), "finalize kernel");
+            HIP(launch_finalize(ctx.partial, ctx.sc, kScRRTrue, s), "finalize kernel");
         } else {
             TRY(true_residual(ctx, b, x, nullptr, ctx.r32));
         }
@@ -257,23 +260,23 @@ int cg_solve(mfhex_op op, const double *b, double *x, void *work, const mfhex_cg
         const double delta = o->replace_delta > 0.0 ? o->replace_delta : 0.1;
         status = MFHEX_ERR_NOCONV;
         bool fallback = false;
+        double *const pap = ctx.partial + 2 * kRedBlocks;
+        bool zeroed = false;
         while (iters < o->maxit) {
-            TRY(apply_impl(op, MFHEX_F32, 1, ctx.p32, ctx.ap32, s, true, -1));
-            HIP(launch_dot(ctx.p32, MFHEX_F32, ctx.ap32, MFHEX_F32, n, ctx.partial, s), "dot kernel");
-            HIP(launch_finalize(ctx.partial, ctx.sc, ctx.pre ? kFinAlphaPre : kFinAlpha, 0, nullptr, 0, s),
-                "finalize kernel");
+            TRY(apply_impl(op, MFHEX_F32, 1, ctx.p32, ctx.ap32, s, !zeroed, -1));
+            HIP(launch_dot(ctx.p32, MFHEX_F32, ctx.ap32, MFHEX_F32, n, pap, ctx.s), "dot kernel");
             if (ctx.pre)
-                HIP(launch_update_xrz(x, ctx.r32, ctx.p32, ctx.ap32, ctx.dinv32, ctx.z32, MFHEX_F32, ctx.sc, n,
+                HIP(launch_update_xrz(x, ctx.r32, ctx.p32, ctx.ap32, ctx.dinv32, ctx.z32, MFHEX_F32, pap, ctx.sc, n,
                                       ctx.partial, s),
                     "update kernel");
             else
-                HIP(launch_update_xr(x, ctx.r32, ctx.p32, ctx.ap32, MFHEX_F32, ctx.sc, n, ctx.partial, s),
+                HIP(launch_update_xr(x, ctx.r32, ctx.p32, ctx.ap32, MFHEX_F32, pap, ctx.sc, false, n, ctx.partial, s),
                     "update kernel");
             ++iters;
             ++since;
-            HIP(launch_finalize(ctx.partial, ctx.sc, ctx.pre ? kFinBetaPre : kFinBeta, iters, ctx.hist, kHist, s),
-                "finalize kernel");
-            if (iters % every == 0 || iters == o->maxit) {
+            const bool check = iters % every == 0 || iters == o->maxit;
+            if (check) HIP(launch_beta(ctx.partial, ctx.sc, ctx.pre, iters, ctx.hist, kHist, s), "beta kernel");
+            if (check) {
                 TRY(read_scalars(ctx));
                 const double *h = op->pinned;
                 if (h[kScFlag] != 0.0) {
@@ -323,7 +326,10 @@ int cg_solve(mfhex_op op, const double *b, double *x, void *work, const mfhex_cg
                     HIP(hipStreamSynchronize(s), "hipStreamSynchronize");
                 }
             }
-            HIP(launch_update_p(zr, ctx.p32, MFHEX_F32, ctx.sc, n, s), "update kernel");
+            zeroed = !op->ebuf && iters < o->maxit;
+            HIP(launch_update_p(zr, ctx.p32, zeroed ? ctx.ap32 : nullptr, MFHEX_F32, check ? nullptr : ctx.partial,
+                                ctx.sc, ctx.pre, iters, ctx.hist, kHist, n, s),
+                "update kernel");
         }
         if (fallback && iters < o->maxit) {
             out.fell_back_to_f64 = 1;

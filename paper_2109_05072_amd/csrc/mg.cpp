@@ -142,7 +142,7 @@ std::vector<double> interp_matrix(const double *xc, int nc, const double *xf, in
 
 double read_dot(mfhex_op op, double *partial, hipStream_t s, int *err)
 {
-    *err = check_hip(op, launch_finalize(partial, partial + kRedBlocks, kFinStore, 0, nullptr, 0, s), "finalize");
+    *err = check_hip(op, launch_finalize(partial, partial + kRedBlocks, 0, s), "finalize");
     if (*err) return 0.0;
     double h = 0.0;
     *err = check_hip(op, hipMemcpyAsync(&h, partial + kRedBlocks, sizeof(double), hipMemcpyDeviceToHost, s), "copy");
