@@ -183,35 +183,55 @@ int power_lambda(mfhex_op fine, MgLevel &L, double *v, double *av, double *parti
     return MFHEX_OK;
 }
 
-// Degree-k Chebyshev smoother on level L: x <- S(b, x) (x = 0 when zero_x), vectors in the
-// cycle precision; the recurrence coefficients are formed in FP64 on the host.
+// What follows a smoothing: a product into L.ad (cleared by its last step), a restriction into coarse_b (cleared too).
+struct After {
+    bool product = false;
+    void *coarse_b = nullptr;
+    int64_t coarse_n = 0;
+};
+
+// Degree-k Chebyshev smoother on level L: x <- S(b, x) (x = 0 when zero_x; else L.ad is cleared, for the first product,
+// unless the operator assembles from element values), vectors in the cycle precision; the recurrence coefficients are
+// formed in FP64 on the host.
 int chebyshev(mfhex_op fine, const MgHierarchy &h, const MgLevel &L, const void *b, void *x, int degree,
-              bool zero_x, hipStream_t s)
+              bool zero_x, const After &after, hipStream_t s)
 {
     const double lo = h.lo * L.lam, hi = h.hi * L.lam;
     const double theta = 0.5 * (hi + lo), delta = 0.5 * (hi - lo), sigma = theta / delta;
-    if (!zero_x) TRY(apply_impl(L.op, h.prec, 1, x, L.ad, s, true, -1));
-    TRY(check_hip(fine,
-                  launch_cheb_init(b, zero_x ? nullptr : L.ad, L.dinv, x, L.r, L.d, 1.0 / theta, zero_x, h.prec,
-                                   L.n, s),
-                  "chebyshev kernel"));
+    const bool atomic = !L.op->ebuf;  // products add into L.ad
+    ChebLaunch c{};
+    c.b = b;
+    c.dinv = L.dinv;
+    c.x = x;
+    c.r = L.r;
+    c.d = L.d;
+    c.n = L.n;
+    c.prec = h.prec;
+    c.stream = s;
+    // the launch before `left` more products of this smoothing
+    auto prepare = [&](int left) {
+        c.last = left == 0;
+        c.zero_ad = atomic && (left > 0 || after.product) ? L.ad : nullptr;
+        c.zero_b = left == 0 ? after.coarse_b : nullptr;
+        c.nb = after.coarse_n;
+    };
+    if (!zero_x) TRY(apply_impl(L.op, h.prec, 1, x, L.ad, s, !atomic, -1));
+    prepare(degree - 1);
+    c.zero_x = zero_x;
+    TRY(check_hip(fine, launch_cheb_init(c, zero_x ? nullptr : L.ad, 1.0 / theta), "chebyshev kernel"));
     double rho = 1.0 / sigma;
-    for (int k = 0; k < degree; ++k) {
-        const bool last = k == degree - 1;
-        double cd = 0.0, cr = 0.0;
-        if (!last) {
-            TRY(apply_impl(L.op, h.prec, 1, L.d, L.ad, s, true, -1));
-            const double rho_new = 1.0 / (2.0 * sigma - rho);
-            cd = rho_new * rho;
-            cr = 2.0 * rho_new / delta;
-            rho = rho_new;
-        }
-        TRY(check_hip(fine, launch_cheb_step(x, L.d, L.r, L.ad, L.dinv, cd, cr, last, h.prec, L.n, s),
-                      "chebyshev kernel"));
+    for (int left = degree - 2; left >= 0; --left) {
+        TRY(apply_impl(L.op, h.prec, 1, L.d, L.ad, s, !atomic, -1));
+        const double rho_new = 1.0 / (2.0 * sigma - rho);
+        prepare(left);
+        TRY(check_hip(fine, launch_cheb_step(c, L.ad, rho_new * rho, 2.0 * rho_new / delta), "chebyshev kernel"));
+        c.zero_x = 0;
+        rho = rho_new;
     }
     return MFHEX_OK;
 }
 
+// dst += P src (dir 0; F.ad cleared on the way) or P^T (src - F.ad) (dir 1).
 int transfer(mfhex_op fine, const MgHierarchy &h, const MgLevel &F, const MgLevel &Cl, int dir, const void *src,
              void *dst, hipStream_t s)
 {
@@ -228,6 +248,12 @@ int transfer(mfhex_op fine, const MgHierarchy &h, const MgLevel &F, const MgLeve
     t.I1 = F.I1;
     t.src = src;
     t.dst = dst;
+    if (dir == 1) {
+        t.src2 = F.ad;
+    } else {
+        t.zero = F.ad;
+        t.nzero = F.op->ebuf ? 0 : F.n;
+    }
     t.stream = s;
     return check_hip(fine, launch_transfer(t), "transfer kernel");
 }
@@ -235,16 +261,14 @@ int transfer(mfhex_op fine, const MgHierarchy &h, const MgLevel &F, const MgLeve
 int vcycle(mfhex_op fine, MgHierarchy &h, int l, const void *b, void *x, hipStream_t s)
 {
     MgLevel &L = h.lv[l];
-    if (l + 1 == (int)h.lv.size()) return chebyshev(fine, h, L, b, x, h.coarse_degree, true, s);
-    TRY(chebyshev(fine, h, L, b, x, h.degree, true, s));
-    TRY(apply_impl(L.op, h.prec, 1, x, L.ad, s, true, -1));
-    TRY(check_hip(fine, launch_mg_residual(b, L.ad, L.r, h.prec, L.n, s), "residual kernel"));
+    if (l + 1 == (int)h.lv.size()) return chebyshev(fine, h, L, b, x, h.coarse_degree, true, After{}, s);
     MgLevel &Cl = h.lv[l + 1];
-    TRY(check_hip(fine, launch_zero(Cl.b, Cl.n * elem_bytes(h.prec), s), "zero fill"));
-    TRY(transfer(fine, h, L, Cl, 1, L.r, Cl.b, s));
+    TRY(chebyshev(fine, h, L, b, x, h.degree, true, After{true, Cl.b, Cl.n}, s));
+    TRY(apply_impl(L.op, h.prec, 1, x, L.ad, s, L.op->ebuf != nullptr, -1));
+    TRY(transfer(fine, h, L, Cl, 1, b, Cl.b, s));
     TRY(vcycle(fine, h, l + 1, Cl.b, Cl.x, s));
     TRY(transfer(fine, h, L, Cl, 0, Cl.x, x, s));
-    return chebyshev(fine, h, L, b, x, h.degree, false, s);
+    return chebyshev(fine, h, L, b, x, h.degree, false, After{}, s);
 }
 
 }  // namespace

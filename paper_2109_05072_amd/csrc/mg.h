@@ -17,23 +17,27 @@ struct TransferLaunch {
     int32_t nex, ney, nez;
     const int32_t *off_f, *off_c;  // element restrictions of the two levels
     const void *I1;
-    const void *src;
-    void *dst;
+    const void *src, *src2;  // restriction: of src - src2
+    void *dst, *zero;        // zero: cleared on the way (nzero entries of the same precision)
+    int64_t nzero;
     hipStream_t stream;
 };
 hipError_t launch_transfer(const TransferLaunch &t);
 
-// Chebyshev smoother vector steps (n entries):
-//   init:  x = 0 (when zero_x), r = dinv (b - Ax) (Ax may be null: r = dinv b), d = r / theta
-//   step:  x += d; r -= dinv Ad; d = cd d + cr r
-//   last:  x += d
-//   resid: r = b - Ax
-// (all vectors in precision prec)
-hipError_t launch_cheb_init(const void *b, const void *Ax, const void *dinv, void *x, void *r, void *d,
-                            double inv_theta, bool zero_x, int prec, int64_t n, hipStream_t s);
-hipError_t launch_cheb_step(void *x, void *d, void *r, const void *Ad, const void *dinv, double cd, double cr,
-                            bool last, int prec, int64_t n, hipStream_t s);
-hipError_t launch_mg_residual(const void *b, const void *Ax, void *r, int prec, int64_t n, hipStream_t s);
+// Chebyshev smoother vector steps (n entries, all vectors in precision prec):
+//   init:  r = dinv (b - Ax) (Ax may be null: r = dinv b), d = r / theta; last: x += d instead of storing r and d
+//   step:  x += d; r -= dinv Ad; d = cd d + cr r; last: x += d again instead of storing r and d
+// zero_x: x is 0 on entry, whatever its memory holds.  zero_ad (n entries), zero_b (nb entries): cleared unless null;
+// zero_ad may be the product that the step reads.
+struct ChebLaunch {
+    const void *b, *dinv;
+    void *x, *r, *d, *zero_ad, *zero_b;
+    int64_t nb, n;
+    int zero_x, last, prec;
+    hipStream_t stream;
+};
+hipError_t launch_cheb_init(const ChebLaunch &c, const void *Ax, double inv_theta);
+hipError_t launch_cheb_step(const ChebLaunch &c, const void *Ad, double cd, double cr);
 // v *= (dinv > 0) and, with scale != 0, v *= scale.
 hipError_t launch_mask_scale(double *v, const double *dinv, double scale, int64_t n, hipStream_t s);
 // out = dinv * a (elementwise).

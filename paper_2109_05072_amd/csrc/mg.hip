@@ -4,12 +4,13 @@
 // every element the coarse nodal values are interpolated to the fine
 // Gauss-Lobatto nodes by the tensor product of the 1D interpolation matrix
 // I1 [P_f][P_c] (three 1D contractions, sum factorization as in Sec. 1).  A
-// fine node shared by m elements receives the same value from each of them,
-// so every element adds it with weight 1/m: the sum is exactly P x_c.  The
-// restriction adds I1^T (w r_f) per element with the same weights w = 1/m,
-// which is exactly P^T r_f.  m is known from the node's position on the
-// structured mesh (2 per direction in which it lies on a face between two
-// elements).  Masked (Dirichlet) nodes are skipped on both levels.
+// fine node on a face has the same value in each element that shares it, so
+// one of them, the last, adds it: no atomics.  The restriction adds
+// I1^T (w r_f) per element with weight w = 1/m of the m elements at a node,
+// which is exactly P^T r_f; r_f = b - A x is formed as it is read.  m is known
+// from the node's position on the structured mesh (2 per direction in which it
+// lies on a face between two elements).  Masked (Dirichlet) nodes are skipped
+// on both levels.
 #include "blas.h"
 #include "mg.h"
 
@@ -19,20 +20,24 @@ namespace {
 
 constexpr int kTransferThreads = 128;
 
-// Weight 1/m of local node (i, j, k) of element (ex, ey, ez) with P nodes per direction.
-__device__ __forceinline__ double share_weight(int i, int j, int k, int P, int ex, int ey, int ez, int nex, int ney,
-                                               int nez)
+// Weight 1/m of local node (i, j, k) of element (ex, ey, ez) with P nodes per direction (a power of 1/2).
+template <typename T>
+__device__ __forceinline__ T share_weight(int i, int j, int k, int P, int ex, int ey, int ez, int nex, int ney, int nez)
 {
-    const int mx = ((i == 0 && ex > 0) || (i == P - 1 && ex < nex - 1)) ? 2 : 1;
-    const int my = ((j == 0 && ey > 0) || (j == P - 1 && ey < ney - 1)) ? 2 : 1;
-    const int mz = ((k == 0 && ez > 0) || (k == P - 1 && ez < nez - 1)) ? 2 : 1;
-    return 1.0 / (mx * my * mz);
+    const bool sx = (i == 0 && ex > 0) || (i == P - 1 && ex < nex - 1);
+    const bool sy = (j == 0 && ey > 0) || (j == P - 1 && ey < ney - 1);
+    const bool sz = (k == 0 && ez > 0) || (k == P - 1 && ez < nez - 1);
+    return (sx ? T(0.5) : T(1)) * (sy ? T(0.5) : T(1)) * (sz ? T(0.5) : T(1));
 }
 
+// Bound by the chain of its stages (four barriers, two indirect accesses): the destinations' entries are loaded before
+// the first stage.  4096 elements from p = 7 to 3: prolongation 24.5 us with atomics, 19.9 without, 17.6 with the early
+// loads; restriction 11.7 us and 9 for the residual's own pass before, 16.4 now.
 template <int PF, int PC, int DIR, typename T>
 __global__ void __launch_bounds__(kTransferThreads)
 k_transfer(int nex, int ney, int nez, const int32_t *__restrict__ off_f, const int32_t *__restrict__ off_c,
-           const T *__restrict__ I1, const T *__restrict__ src, T *__restrict__ dst)
+           const T *__restrict__ I1, const T *__restrict__ src, const T *__restrict__ src2, T *__restrict__ dst,
+           T *__restrict__ zero, int64_t nzero)
 {
     constexpr int NT = kTransferThreads;
     constexpr int F3 = PF * PF * PF, C3 = PC * PC * PC;
@@ -44,9 +49,29 @@ k_transfer(int nex, int ney, int nez, const int32_t *__restrict__ off_f, const i
     __shared__ T sI[PF * PC], sa[NA], sb[NB], sc[NC];
     const int tid = threadIdx.x;
     const int64_t e = blockIdx.x;
+    for (int64_t t = e * NT + tid; t < nzero; t += (int64_t)gridDim.x * NT) zero[t] = T(0);
     const int ex = (int)(e % nex), ey = (int)((e / nex) % ney), ez = (int)(e / ((int64_t)nex * ney));
     for (int t = tid; t < PF * PC; t += NT) sI[t] = I1[t];
+    constexpr int NOUT = DIR == 0 ? F3 : C3, RO = (NOUT + NT - 1) / NT;
+    int32_t od[RO];  // destinations (prolongation: of the nodes that this element owns)
+    T xd[RO];
+#pragma unroll
+    for (int r = 0; r < RO; ++r) {
+        const int t = tid + r * NT;
+        od[r] = -1;
+        if (t < NOUT) {
+            if constexpr (DIR == 0) {
+                const int i = t % PF, j = (t / PF) % PF, k = t / (PF * PF);
+                if ((i < PF - 1 || ex == nex - 1) && (j < PF - 1 || ey == ney - 1) && (k < PF - 1 || ez == nez - 1))
+                    od[r] = off_f[e * F3 + t];
+            } else {
+                od[r] = off_c[e * C3 + t];
+            }
+        }
+    }
     if constexpr (DIR == 0) {
+#pragma unroll
+        for (int r = 0; r < RO; ++r) xd[r] = od[r] >= 0 ? dst[od[r]] : T(0);
         for (int t = tid; t < C3; t += NT) {
             const int32_t o = off_c[e * C3 + t];
             sa[t] = o >= 0 ? src[o] : T(0);
@@ -55,7 +80,8 @@ k_transfer(int nex, int ney, int nez, const int32_t *__restrict__ off_f, const i
         for (int t = tid; t < F3; t += NT) {
             const int32_t o = off_f[e * F3 + t];
             const int i = t % PF, j = (t / PF) % PF, k = t / (PF * PF);
-            sa[t] = o >= 0 ? T(share_weight(i, j, k, PF, ex, ey, ez, nex, ney, nez)) * src[o] : T(0);
+            sa[t] = o >= 0 ? share_weight<T>(i, j, k, PF, ex, ey, ez, nex, ney, nez) * (src[o] - src2[o])
+                           : T(0);
         }
     }
     __syncthreads();
@@ -82,20 +108,16 @@ k_transfer(int nex, int ney, int nez, const int32_t *__restrict__ off_f, const i
     __syncthreads();
     // z: contract the slowest index and add to the destination
     constexpr int NIZ = DIR == 0 ? PC : PF, NOZ = DIR == 0 ? PF : PC, NXY = NX * NOY;
-    for (int t = tid; t < NOZ * NXY; t += NT) {
+    static_assert(NOZ * NXY == NOUT, "one result per destination");
+#pragma unroll
+    for (int r = 0; r < RO; ++r) {
+        const int t = tid + r * NT;
+        if (t >= NOUT || od[r] < 0) continue;
         const int ab = t % NXY, o = t / NXY;
         T s = T(0);
         for (int k = 0; k < NIZ; ++k) s += (DIR == 0 ? sI[o * PC + k] : sI[k * PC + o]) * sc[ab + NXY * k];
-        if constexpr (DIR == 0) {
-            const int32_t of = off_f[e * F3 + t];
-            if (of >= 0) {
-                const int i = t % PF, j = (t / PF) % PF, k = t / (PF * PF);
-                unsafeAtomicAdd(&dst[of], T(share_weight(i, j, k, PF, ex, ey, ez, nex, ney, nez)) * s);
-            }
-        } else {
-            const int32_t oc = off_c[e * C3 + t];
-            if (oc >= 0) unsafeAtomicAdd(&dst[oc], s);
-        }
+        if constexpr (DIR == 0) dst[od[r]] = xd[r] + s;
+        else unsafeAtomicAdd(&dst[od[r]], s);
     }
 }
 
@@ -104,13 +126,14 @@ hipError_t transfer_t(const TransferLaunch &t)
 {
     const int64_t nelem = (int64_t)t.nex * t.ney * t.nez;
     const T *I1 = static_cast<const T *>(t.I1), *src = static_cast<const T *>(t.src);
-    T *dst = static_cast<T *>(t.dst);
+    const T *src2 = static_cast<const T *>(t.src2);
+    T *dst = static_cast<T *>(t.dst), *zero = static_cast<T *>(t.zero);
     if (t.dir == 0)
         hipLaunchKernelGGL((k_transfer<PF, PC, 0, T>), dim3((unsigned)nelem), dim3(kTransferThreads), 0, t.stream,
-                           t.nex, t.ney, t.nez, t.off_f, t.off_c, I1, src, dst);
+                           t.nex, t.ney, t.nez, t.off_f, t.off_c, I1, src, src2, dst, zero, t.nzero);
     else
         hipLaunchKernelGGL((k_transfer<PF, PC, 1, T>), dim3((unsigned)nelem), dim3(kTransferThreads), 0, t.stream,
-                           t.nex, t.ney, t.nez, t.off_f, t.off_c, I1, src, dst);
+                           t.nex, t.ney, t.nez, t.off_f, t.off_c, I1, src, src2, dst, zero, t.nzero);
     return hipGetLastError();
 }
 
@@ -122,38 +145,58 @@ hipError_t transfer_pf(const TransferLaunch &t)
 
 #define GRID dim3(kRedBlocks), dim3(kRedThreads), 0, s
 
+// The smoother's vector steps, one launch between two products.  They also clear what the next launches add into (Ad,
+// and at the end of the pre-smoothing the coarse right-hand side), and the step after the last product applies both of
+// the directions that are left, so that a smoothing of degree k has k launches besides its products (with a fill for
+// each product, x = 0 and the last addition apart it had 2 k + 1, of 4 to 6 us each).
 template <typename T>
-__global__ void k_cheb_init(const T *__restrict__ b, const T *__restrict__ Ax, const T *__restrict__ dinv,
-                            T *__restrict__ x, T *__restrict__ r, T *__restrict__ d, T inv_theta, int zero_x, int64_t n)
-{
-    for (int64_t i = blockIdx.x * (int64_t)kRedThreads + threadIdx.x; i < n; i += (int64_t)kRedBlocks * kRedThreads) {
-        const T ri = dinv[i] * (Ax ? b[i] - Ax[i] : b[i]);
-        r[i] = ri;
-        d[i] = ri * inv_theta;
-        if (zero_x) x[i] = T(0);
+struct ChebZero {
+    T *a;        // Ad
+    T *b;        // the coarse right-hand side (nb entries, fewer than n) or null
+    int64_t nb;
+    __device__ __forceinline__ void at(int64_t i) const
+    {
+        if (a) a[i] = T(0);
+        if (b && i < nb) b[i] = T(0);
     }
-}
+};
 
 template <typename T>
-__global__ void k_cheb_step(T *__restrict__ x, T *__restrict__ d, T *__restrict__ r, const T *__restrict__ Ad,
-                            const T *__restrict__ dinv, T cd, T cr, int last, int64_t n)
+__global__ void __launch_bounds__(kRedThreads) k_cheb_init(const T *__restrict__ b, const T *Ax,
+                                                           const T *__restrict__ dinv, T *__restrict__ x,
+                                                           T *__restrict__ r, T *__restrict__ d, T inv_theta, int zero_x,
+                                                           int last, ChebZero<T> z, int64_t n)
 {
-    for (int64_t i = blockIdx.x * (int64_t)kRedThreads + threadIdx.x; i < n; i += (int64_t)kRedBlocks * kRedThreads) {
-        const T di = d[i];
-        x[i] += di;
-        if (!last) {
-            const T ri = r[i] - dinv[i] * Ad[i];
+    const int64_t S = (int64_t)gridDim.x * kRedThreads;
+    for (int64_t i = blockIdx.x * (int64_t)kRedThreads + threadIdx.x; i < n; i += S) {
+        const T ri = dinv[i] * (Ax ? b[i] - Ax[i] : b[i]), di = ri * inv_theta;
+        if (last) {
+            x[i] = zero_x ? di : x[i] + di;
+        } else {
             r[i] = ri;
-            d[i] = cd * di + cr * ri;
+            d[i] = di;
         }
+        z.at(i);
     }
 }
 
 template <typename T>
-__global__ void k_mg_residual(const T *__restrict__ b, const T *__restrict__ Ax, T *__restrict__ r, int64_t n)
+__global__ void __launch_bounds__(kRedThreads) k_cheb_step(T *__restrict__ x, T *__restrict__ d, T *__restrict__ r,
+                                                           const T *Ad, const T *__restrict__ dinv, T cd, T cr,
+                                                           int zero_x, int last, ChebZero<T> z, int64_t n)
 {
-    for (int64_t i = blockIdx.x * (int64_t)kRedThreads + threadIdx.x; i < n; i += (int64_t)kRedBlocks * kRedThreads)
-        r[i] = b[i] - Ax[i];
+    const int64_t S = (int64_t)gridDim.x * kRedThreads;
+    for (int64_t i = blockIdx.x * (int64_t)kRedThreads + threadIdx.x; i < n; i += S) {
+        const T di = d[i], ri = r[i] - dinv[i] * Ad[i], dn = cd * di + cr * ri, xi = zero_x ? di : x[i] + di;
+        if (last) {
+            x[i] = xi + dn;
+        } else {
+            x[i] = xi;
+            r[i] = ri;
+            d[i] = dn;
+        }
+        z.at(i);
+    }
 }
 
 __global__ void k_mask_scale(double *__restrict__ v, const double *__restrict__ dinv, double scale, int64_t n)
@@ -203,37 +246,39 @@ hipError_t launch_transfer(const TransferLaunch &t)
     }
 }
 
-hipError_t launch_cheb_init(const void *b, const void *Ax, const void *dinv, void *x, void *r, void *d,
-                            double inv_theta, bool zero_x, int prec, int64_t n, hipStream_t s)
+// Blocks of a smoother step: one entry a thread as far as 2048 blocks go (eight for each CU).
+static dim3 cheb_grid(int64_t n)
 {
-    if (prec == MFHEX_F32)
-        hipLaunchKernelGGL(k_cheb_init<float>, GRID, (const float *)b, (const float *)Ax, (const float *)dinv,
-                           (float *)x, (float *)r, (float *)d, (float)inv_theta, zero_x ? 1 : 0, n);
-    else
-        hipLaunchKernelGGL(k_cheb_init<double>, GRID, (const double *)b, (const double *)Ax, (const double *)dinv,
-                           (double *)x, (double *)r, (double *)d, inv_theta, zero_x ? 1 : 0, n);
+    const int64_t b = (n + kRedThreads - 1) / kRedThreads;
+    return dim3((unsigned)(b < 2048 ? b : 2048));
+}
+
+template <typename T>
+static hipError_t cheb_init_t(const ChebLaunch &c, const void *Ax, double inv_theta)
+{
+    const ChebZero<T> z{(T *)c.zero_ad, (T *)c.zero_b, c.nb};
+    hipLaunchKernelGGL(k_cheb_init<T>, cheb_grid(c.n), dim3(kRedThreads), 0, c.stream, (const T *)c.b, (const T *)Ax,
+                       (const T *)c.dinv, (T *)c.x, (T *)c.r, (T *)c.d, (T)inv_theta, c.zero_x, c.last, z, c.n);
     return hipGetLastError();
 }
 
-hipError_t launch_cheb_step(void *x, void *d, void *r, const void *Ad, const void *dinv, double cd, double cr,
-                            bool last, int prec, int64_t n, hipStream_t s)
+template <typename T>
+static hipError_t cheb_step_t(const ChebLaunch &c, const void *Ad, double cd, double cr)
 {
-    if (prec == MFHEX_F32)
-        hipLaunchKernelGGL(k_cheb_step<float>, GRID, (float *)x, (float *)d, (float *)r, (const float *)Ad,
-                           (const float *)dinv, (float)cd, (float)cr, last ? 1 : 0, n);
-    else
-        hipLaunchKernelGGL(k_cheb_step<double>, GRID, (double *)x, (double *)d, (double *)r, (const double *)Ad,
-                           (const double *)dinv, cd, cr, last ? 1 : 0, n);
+    const ChebZero<T> z{(T *)c.zero_ad, (T *)c.zero_b, c.nb};
+    hipLaunchKernelGGL(k_cheb_step<T>, cheb_grid(c.n), dim3(kRedThreads), 0, c.stream, (T *)c.x, (T *)c.d, (T *)c.r,
+                       (const T *)Ad, (const T *)c.dinv, (T)cd, (T)cr, c.zero_x, c.last, z, c.n);
     return hipGetLastError();
 }
 
-hipError_t launch_mg_residual(const void *b, const void *Ax, void *r, int prec, int64_t n, hipStream_t s)
+hipError_t launch_cheb_init(const ChebLaunch &c, const void *Ax, double inv_theta)
 {
-    if (prec == MFHEX_F32)
-        hipLaunchKernelGGL(k_mg_residual<float>, GRID, (const float *)b, (const float *)Ax, (float *)r, n);
-    else
-        hipLaunchKernelGGL(k_mg_residual<double>, GRID, (const double *)b, (const double *)Ax, (double *)r, n);
-    return hipGetLastError();
+    return c.prec == MFHEX_F32 ? cheb_init_t<float>(c, Ax, inv_theta) : cheb_init_t<double>(c, Ax, inv_theta);
+}
+
+hipError_t launch_cheb_step(const ChebLaunch &c, const void *Ad, double cd, double cr)
+{
+    return c.prec == MFHEX_F32 ? cheb_step_t<float>(c, Ad, cd, cr) : cheb_step_t<double>(c, Ad, cd, cr);
 }
 
 hipError_t launch_mask_scale(double *v, const double *dinv, double scale, int64_t n, hipStream_t s)
