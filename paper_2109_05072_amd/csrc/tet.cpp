@@ -175,17 +175,18 @@ void eval_basis(int p, const double *xi, int M, double *B, double *G)
     for (int m = 0; m < M; ++m) {
         const double lam[4] = {1.0 - xi[3 * m] - xi[3 * m + 1] - xi[3 * m + 2], xi[3 * m], xi[3 * m + 1],
                                xi[3 * m + 2]};
+        double R[4][kMaxP + 1], D[4][kMaxP + 1];
+        for (int i = 0; i < 4; ++i)
+            for (int k = 0; k <= p; ++k) silvester(k, p * lam[i], R[i][k], D[i][k]);
         for (int n = 0; n < P; ++n) {
             const int k[4] = {p - L[4 * n] - L[4 * n + 1] - L[4 * n + 2], L[4 * n], L[4 * n + 1], L[4 * n + 2]};
-            double r[4], dr[4];
-            for (int i = 0; i < 4; ++i) silvester(k[i], p * lam[i], r[i], dr[i]);
             double dl[4];
             for (int i = 0; i < 4; ++i) {
-                dl[i] = p * dr[i];
+                dl[i] = p * D[i][k[i]];
                 for (int j = 0; j < 4; ++j)
-                    if (j != i) dl[i] *= r[j];
+                    if (j != i) dl[i] *= R[j][k[j]];
             }
-            if (B) B[(size_t)m * P + n] = r[0] * r[1] * r[2] * r[3];
+            if (B) B[(size_t)m * P + n] = R[0][k[0]] * R[1][k[1]] * R[2][k[2]] * R[3][k[3]];
             for (int d = 0; d < 3; ++d) G[((size_t)d * M + m) * P + n] = dl[d + 1] - dl[0];
         }
     }
@@ -195,19 +196,25 @@ void eval_basis(int p, const double *xi, int M, double *B, double *G)
 // Koornwinder-Dubiner products of Jacobi polynomials), not yet normalized: psi [n_rows(p)].
 void eval_psi(int p, double a, double b, double c, double *psi)
 {
+    double pa[kMaxP], pb[kMaxP][kMaxP], pc[kMaxP][kMaxP];  // pb, pc with their powers (1 - b)^i and (1 - c)^(i+j)
+    for (int i = 0; i < p; ++i) {
+        const double bi = std::pow(1.0 - b, i), ci = std::pow(1.0 - c, i);
+        pa[i] = jacobi_poly(i, 0.0, 0.0, 2.0 * a - 1.0);
+        for (int k = 0; i + k < p; ++k) {
+            pb[i][k] = bi * jacobi_poly(k, 2.0 * i + 1.0, 0.0, 2.0 * b - 1.0);
+            pc[i][k] = ci * jacobi_poly(k, 2.0 * i + 2.0, 0.0, 2.0 * c - 1.0);
+        }
+    }
     int m = 0;
     for (int i = 0; i < p; ++i)
         for (int j = 0; i + j < p; ++j)
-            for (int k = 0; i + j + k < p; ++k)
-                psi[m++] = jacobi_poly(i, 0.0, 0.0, 2.0 * a - 1.0) * std::pow(1.0 - b, i) *
-                           jacobi_poly(j, 2.0 * i + 1.0, 0.0, 2.0 * b - 1.0) * std::pow(1.0 - c, i + j) *
-                           jacobi_poly(k, 2.0 * (i + j) + 2.0, 0.0, 2.0 * c - 1.0);
+            for (int k = 0; i + j + k < p; ++k) psi[m++] = pa[i] * pb[i][j] * pc[i + j][k];
 }
 
-// H [3][M][P] with the rule of p + 1 points per direction (exact here: degree 2p - 2 against 2p + 1).
+// H [3][M][P] with the rule of p points per direction (exact here: degree 2p - 2 against 2p - 1).
 std::vector<double> gradient_rows(int p)
 {
-    const int q = p + 1, Q = q * q * q, P = n_basis(p), M = n_rows(p);
+    const int q = p, Q = q * q * q, P = n_basis(p), M = n_rows(p);
     const Rule R = tet_rule(q);
     std::vector<double> g((size_t)3 * Q * P), psi((size_t)Q * M), norm(M, 0.0), H((size_t)3 * M * P, 0.0);
     eval_basis(p, R.xi.data(), Q, nullptr, g.data());
