@@ -30,6 +30,10 @@
 // in reverse order.  With Gauss-Lobatto points collocated at the nodes
 // (q = p+1) B is the identity.  Mass: interpolate, scale by w detJ,
 // interpolate back.
+//
+// These are the kernels of what the line-fused ones (line_kernels.hpp) don't take: the stored-factor variants of
+// diffusion with Gauss points, multi-vector chunks of collocated diffusion that mline_serves leaves here (or where the
+// deterministic scatter is asked for), the matrix-core gradient, collocated mass and the load vector.
 #pragma once
 
 #include <type_traits>
@@ -945,6 +949,21 @@ static int line_march(int mode, int chain, bool auto_chain, int ney, int64_t col
 }
 
 // The line-fused kernel.
+// Thread groups of a line-fused kernel: launches of fewer than 2^32 lanes each, the limit of a grid's extent (several
+// vectors of a large mesh exceed it: a chunk has its own groups).
+template <typename K, typename A>
+static hipError_t launch_groups(K kern, A k, int64_t ngroups, int nt, int ny, size_t lds, hipStream_t s)
+{
+    const int64_t most = ((int64_t)1 << 32) / nt - kNumXcd;
+    for (int64_t b = 0; b < ngroups; b += most) {
+        k.base = (unsigned)b;
+        hipLaunchKernelGGL(kern, dim3((unsigned)(ngroups - b < most ? ngroups - b : most), (unsigned)ny), dim3(nt), lds, s, k);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 template <int P, int Q, bool COLLOC, int MODE, bool VARK, typename T, int V, bool DET>
 static hipError_t launch_line_v(const ApplyLaunch &a)
 {
@@ -971,8 +990,7 @@ static hipError_t launch_line_v(const ApplyLaunch &a)
     auto go = [&](auto kern) {
         const hipError_t e = prepare_lds(kern, lds);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(kern, dim3((unsigned)nblk, (unsigned)a.nvec), dim3(NT), lds, a.stream, k);
-        return hipGetLastError();
+        return launch_groups(kern, k, nblk, NT, a.nvec, lds, a.stream);
     };
     // byte offsets inside a slab of P planes of nodes: 32 bits unless the slab is that large
     const int64_t slab = (int64_t)P * (a.v.nex * (P - 1) + 1) * (a.v.ney * (int64_t)(P - 1) + 1) * a.nvec * (int64_t)sizeof(T);
@@ -1006,8 +1024,7 @@ static hipError_t launch_mline_v(const ApplyLaunch &a)
     auto go = [&](auto kern) {
         const hipError_t e = prepare_lds(kern, lds);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(kern, dim3((unsigned)nblk), dim3(NT), lds, a.stream, k);
-        return hipGetLastError();
+        return launch_groups(kern, k, nblk, NT, 1, lds, a.stream);
     };
     const int64_t slab = (int64_t)Q * (a.v.nex * (Q - 1) + 1) * (a.v.ney * (int64_t)(Q - 1) + 1) * a.nvec * (int64_t)sizeof(T);
     if (slab < (int64_t)1 << 31) return go(k_mline<Q, VC, T, G, NT, uint32_t>);
@@ -1068,9 +1085,11 @@ static hipError_t launch_apply_v(const ApplyLaunch &a)
 {
     if constexpr (line_variant(MODE, COLLOC, OTF, V)) return launch_line_v<P, Q, COLLOC, MODE, VARK, T, V, DET>(a);
     else if constexpr (variant_gf(V) || OTF) return hipErrorInvalidValue;
-    else if constexpr (!DET && !VARK && mline_variant(MODE, COLLOC, V) && apply_lds(P, Q, MODE, sizeof(T), V) <= kMaxLds)
-        return launch_mline_v<Q, T, V>(a);
-    else return launch_element_v<P, Q, COLLOC, MODE, VARK, T, V, DET>(a);
+    else {
+        if constexpr (!DET && !VARK && mline_variant(MODE, COLLOC, V) && apply_lds(P, Q, MODE, sizeof(T), V) <= kMaxLds)
+            if (mline_serves(P, Q, MODE, COLLOC, sizeof(T), V, a.nvec)) return launch_mline_v<Q, T, V>(a);
+        return launch_element_v<P, Q, COLLOC, MODE, VARK, T, V, DET>(a);
+    }
 }
 
 template <int P, int Q, bool COLLOC, int MODE, bool VARK, typename T, bool OTF, bool DET>
@@ -1144,8 +1163,7 @@ static hipError_t launch_kgrad_pq(const KgradLaunch &a)
     auto kern = k_kgrad<P, Q, COLLOC, G, NT>;
     const hipError_t e = prepare_lds(kern, lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3((unsigned)((int64_t)k.ngx * k.nych * a.v.nez)), dim3(NT), lds, a.stream, k);
-    return hipGetLastError();
+    return launch_groups(kern, k, (int64_t)k.ngx * k.nych * a.v.nez, NT, 1, lds, a.stream);
 }
 
 }  // namespace mfhex

@@ -8,7 +8,6 @@
 #include <cstdint>
 #include <cstring>
 #include <string>
-#include <utility>
 #include <vector>
 
 #include "blas.h"
@@ -197,21 +196,19 @@ int default_variant(const mfhex_op_s &op, int prec, int nvec)
         return line_variant(mode, coll, otf, slot) ? slot : 9 + slot;
     }
     const int eb = prec == MFHEX_F32 ? 4 : 8;
-    if (mline_variant(mode_of(op), op.basis.colloc, 6) && !op.ebuf && !op.d.variable_kappa) {
-        // Collocated diffusion: the least sum of the chunks' times.  A chunk of 8 takes 1.4 times one of 4 (1e6 nodes,
-        // 12 vectors FP64, p = 2 .. 6: three of 4 in 226, 213, 211, 216, 184 us, two of 8 in 227, 191, 205, 191,
-        // 167; 3e6 nodes, 5 vectors, p = 3, 6: 300, 296 in 4s, 238, 218 in an 8; 4 vectors, p = 3: 148 and 239), in
-        // FP32 at q = 4 .. 6 one of 16 (k_apply) 2.3 times (16 vectors, p = 3 .. 5: 133, 152, 147 against 168, 159,
-        // 161 in 8s; 24: 312, 277, 263 against 242, 235, 236).
-        const bool pair = nvec == 2 && op.Q >= (prec == MFHEX_F32 ? 9 : 7);  // p = 6 .. 8: 106, 96, 97 against 113, 116, 174 us
-        if (pair && valid_variant(op, prec, 5)) return 5;
-        int best = 0, cost = INT32_MAX;
-        for (const auto &[v, t] : {std::pair{6, 10}, {7, 14}, {8, 23}}) {
-            if (!valid_variant(op, prec, v) || (v == 8 && (prec != MFHEX_F32 || op.Q < 4 || op.Q > 6))) continue;
-            const int sum = t * ((nvec + variant_vc(v) - 1) / variant_vc(v));
-            if (sum < cost) best = v, cost = sum;
-        }
-        if (best) return best;
+    if (!op.ebuf && !op.d.variable_kappa) {
+        // Collocated diffusion: k_mline where it serves the launch (mline_serves), in 8s from five vectors on (3e6 nodes,
+        // FP64, p = 3, 6: 5 vectors 238, 218 us in an 8 and 300, 296 in 4s; 4 vectors 239, 200 and 148, 139).  Two FP64
+        // vectors from q = 5 on are faster as a pair (p = 4, 5, 7: 127, 114, 98 against 142, 141, 116), FP32 ones at
+        // q = 9 (74 against 82); at q = 9 in FP64, where 4 is the largest chunk, so are more than 4 (24 vectors of 2e6
+        // nodes: 901 against 992).
+        const bool f32 = prec == MFHEX_F32;
+        const bool pair = (nvec == 2 && op.Q >= (f32 ? 9 : 5)) || (nvec > 4 && op.Q == 9 && !f32);
+        const auto served = [&](int v) {
+            return valid_variant(op, prec, v) && mline_serves(op.P, op.Q, mode_of(op), op.basis.colloc, eb, v, nvec);
+        };
+        if (!pair && nvec > 4 && served(7)) return 7;
+        if (!pair && (nvec <= 4 || !f32) && served(6)) return 6;
     }
     // (with the scatter staging that several chunks need, the chunk must still leave room for two
     // thread groups per compute unit)
@@ -647,7 +644,8 @@ int mfhex_get_config(mfhex_op op, int prec, int nrhs, int32_t *variant, int32_t 
     const LaunchCfg c = config_for(*op, prec, nrhs * op->d.ncomp);
     if (variant) *variant = c.variant;
     const bool line = line_variant(mode_of(*op), op->basis.colloc, (op->d.flags & MFHEX_FLAG_OTF) != 0, c.variant);
-    const bool mline = !op->ebuf && mline_variant(mode_of(*op), op->basis.colloc, c.variant);
+    const bool mline = !op->ebuf && mline_serves(op->P, op->Q, mode_of(*op), op->basis.colloc, prec == MFHEX_F32 ? 4 : 8,
+                                                 c.variant, nrhs * op->d.ncomp);
     const int g = line    ? kLineG[op->Q - 2][line_slot(c.variant)]
                   : mline ? mline_g(op->Q, c.variant)
                           : variant_g(op->Q, c.variant, mode_of(*op));

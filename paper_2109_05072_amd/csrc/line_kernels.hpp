@@ -303,6 +303,7 @@ struct LineArgs {
     T *y, *ebuf;
     int nex, ney, nez, dirichlet, nvec;
     int ngx, nych, march;  // element groups per row, y-chunks per column, elements per march
+    unsigned base;         // first thread group of this launch
 };
 
 // Marching position of a thread group.
@@ -314,7 +315,7 @@ __device__ __forceinline__ LinePos line_pos_of(const A &a, unsigned bid, unsigne
 {
     // XCD x (blocks are dealt round-robin) takes the x-th contiguous range of the groups
     const unsigned xcd = bid % kNumXcd, nq = nb / kNumXcd, nr = nb % kNumXcd;
-    const unsigned b = xcd * nq + (xcd < nr ? xcd : nr) + bid / kNumXcd;
+    const unsigned b = a.base + xcd * nq + (xcd < nr ? xcd : nr) + bid / kNumXcd;
     LinePos q;
     const int gx = (int)(b % (unsigned)a.ngx);
     const unsigned r = b / (unsigned)a.ngx;
@@ -760,7 +761,7 @@ k_mline(const LineArgs<T> a)
     // chunks of vectors fastest: those of one element run side by side and share its lines in the L2
     const unsigned nch = (a.nvec + VC - 1) / VC;
     const unsigned xcd = blockIdx.x % kNumXcd, nq = gridDim.x / kNumXcd, nr = gridDim.x % kNumXcd;
-    const unsigned bid = xcd * nq + (xcd < nr ? xcd : nr) + blockIdx.x / kNumXcd;
+    const unsigned bid = a.base + xcd * nq + (xcd < nr ? xcd : nr) + blockIdx.x / kNumXcd;
     const int vec = (int)(bid % nch) * VC + vc;
     LinePos pos;
     {
@@ -989,6 +990,7 @@ struct KgradArgs {
     double *g;
     int nex, ney, nez, dirichlet;
     int ngx, nych, march;
+    unsigned base;
 };
 
 // The value of the other lane of the pair.

@@ -230,6 +230,19 @@ constexpr size_t apply_lds(int P, int Q, int mode, int elem_bytes, int v, bool s
 // and 16-vector chunks at q = 6 while still leaving room for a second group on the CU.
 constexpr size_t kMaxLds = 98304;
 constexpr size_t kLdsTwoGroups = 81920;  // at most this much LDS leaves room for two thread groups per CU
+// Whether k_mline takes a launch of nvec vectors in chunks of variant v (else k_apply): chunks of less than 64 bytes a
+// node update half a line at a time, which k_apply's staged runs avoid where two of its groups fit a CU.  Then k_mline
+// wins with one chunk, or with three of which the last is at least half full (k_apply would fill its last run no better):
+// p = 7, FP64, 12 vectors 459 against 517 us, but 9 582 against 543; 24 of 2e6 nodes 794 against 685, 48 of 1e6 747
+// against 641.  FP32, 24 vectors: 340, 310, 289, 270, 287, 249 at p = 2 .. 7 against 520, 399, 345, 297, 472, 307 and 18
+// 518, 415, 404 at p = 2, 6, 7 against 786, 615, 419 (p = 5 437 against 425), 48 392, 365 at p = 2, 6 against 363, 342.
+constexpr bool mline_serves(int P, int Q, int mode, bool colloc, int elem_bytes, int v, int nvec)
+{
+    if (!mline_variant(mode, colloc, v)) return false;
+    const int vc = variant_vc(v), chunks = (nvec + vc - 1) / vc, last = nvec - (chunks - 1) * vc;
+    if (vc * elem_bytes >= 64 || chunks == 1 || apply_lds(P, Q, mode, elem_bytes, v, true) > kLdsTwoGroups) return true;
+    return chunks == 3 && (2 * last >= vc || (elem_bytes == 4 && (Q < 4 || Q > 6)));
+}
 
 // Single-vector launch defaults of the line-fused kernel per q (index q-2).  Measured time of every
 // slot in percent of the best, at about 1e7 nodes and with the idle elements of ragged x rows taken

@@ -49,3 +49,17 @@ def test_offsets_beyond_32_bits(gpu_lib, v):
     for c in (0, 1777, 4095):
         ref = op.apply(x[:, c].contiguous())
         assert float((y[:, c] - ref).abs().max()) <= 1e-13 * float(ref.abs().max())
+
+
+def test_grids_beyond_32_bits(gpu_lib):
+    # 700 x 1 x 700 elements, 4096 vectors of p = 1: 8e9 lanes, more than one launch may have
+    op, pr = build(gpu_lib, 700, 1, 700, 1, "diffusion", "gll", False, f32=True)
+    nrhs = 4096
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(1)
+    x = torch.rand(pr.n_nodes, nrhs, dtype=torch.float32, device="cuda", generator=gen)
+    op.set_config(6, torch.float32, nrhs)
+    y = op.apply(x)
+    for c in (0, 2047, 4095):
+        ref = op.apply(x[:, c].contiguous())
+        assert float((y[:, c] - ref).abs().max()) <= TOL32 * float(ref.abs().max())
