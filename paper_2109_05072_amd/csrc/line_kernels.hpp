@@ -283,10 +283,18 @@ struct LineLds {
     static constexpr int ELEM = P * PLANE;
 };
 constexpr int line_arrays(int mode) { return mode == kMass ? 1 : 3; }
+// Entries of the contraction arrays, up to the FP64 tables behind them: whole doubles (in FP32 with q and G odd the
+// arrays of the collocated operator end in the middle of one).
+template <int P, int Q, typename T>
+constexpr int line_array_len(int mode, int G)
+{
+    constexpr int M = 8 / sizeof(T);
+    return (line_arrays(mode) * G * LineLds<P, Q>::ELEM + M - 1) / M * M;
+}
 template <int P, int Q, typename T>
 constexpr size_t line_lds(int mode, int G)
 {
-    return (size_t)line_arrays(mode) * G * LineLds<P, Q>::ELEM * sizeof(T) + ((size_t)G * kTriCoef + 2 * Q + 12 * (G + 1)) * 8;
+    return (size_t)line_array_len<P, Q, T>(mode, G) * sizeof(T) + ((size_t)G * kTriCoef + 2 * Q + 12 * (G + 1)) * 8;
 }
 
 // Wavefronts per SIMD that the registers are allocated for: the pointwise stage holds the gradient of a z-line
@@ -341,7 +349,7 @@ k_line(const LineArgs<T> a)
     T *const A = reinterpret_cast<T *>(smem_raw);
     T *const Bb = MODE == kMass ? A : A + G * L::ELEM;
     T *const C = MODE == kMass ? A : Bb + G * L::ELEM;
-    double *const sC = reinterpret_cast<double *>(A + line_arrays(MODE) * G * L::ELEM);
+    double *const sC = reinterpret_cast<double *>(A + line_array_len<P, Q, T>(MODE, G));
     const int tid = threadIdx.x;
     const LinePos pos = line_pos_of<G>(a, blockIdx.x, gridDim.x);
     const int vec = blockIdx.y;
