@@ -222,11 +222,13 @@ int default_variant(const mfhex_op_s &op, int prec, int nvec)
     return 0;
 }
 
-// Pipeline depth: the mass kernel chains the measured best number of element
-// groups per thread group; the diffusion kernel takes one.
-int default_chain(const mfhex_op_s &op)
+// Pipeline depth: the mass kernels take the measured best number of element groups per thread group, each its own:
+// k_line's march carries a face, k_mass (collocated, or several vectors) divides its blocks by the depth.  The
+// diffusion kernels take one.
+int default_chain(const mfhex_op_s &op, int variant)
 {
-    return mode_of(op) != kMass ? 1 : (op.basis.colloc ? kDefChainMassColl : kDefChainMass)[op.Q - 2];
+    if (mode_of(op) != kMass) return 1;
+    return (line_variant(kMass, op.basis.colloc, false, variant) ? kDefChainLineMass : kDefChainMass)[op.Q - 2];
 }
 
 LaunchCfg config_for(const mfhex_op_s &op, int prec, int nvec)
@@ -235,7 +237,7 @@ LaunchCfg config_for(const mfhex_op_s &op, int prec, int nvec)
     if (it != op.config.end()) return it->second;
     LaunchCfg c;
     c.variant = default_variant(op, prec, nvec);
-    c.chain = default_chain(op);
+    c.chain = default_chain(op, c.variant);
     return c;
 }
 
@@ -662,7 +664,7 @@ int mfhex_set_config(mfhex_op op, int prec, int nrhs, int32_t variant, int32_t g
 {
     if (!op || nrhs < 1) return fail(MFHEX_ERR_ARG, "bad argument");
     if (!valid_variant(*op, prec, variant)) return set_error(op, MFHEX_ERR_ARG, "invalid launch variant");
-    const int chain = groups_per_block > 0 ? groups_per_block : default_chain(*op);
+    const int chain = groups_per_block > 0 ? groups_per_block : default_chain(*op, variant);
     if (groups_per_block < 0 || chain > kMaxChain || (chain > 1 && mode_of(*op) != kMass))
         return set_error(op, MFHEX_ERR_ARG, "invalid pipeline depth");
     LaunchCfg c;

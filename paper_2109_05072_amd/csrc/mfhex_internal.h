@@ -262,10 +262,12 @@ constexpr int kLineCostMass[9][5] = {{107, 101, 100, 157, 277}, {107, 101, 100, 
 // 213 -> 182, 193 -> 155, 168 -> 130, 165 -> 128, 169 -> 155 us against the stored-factor kernel).
 constexpr int kLineSlot32Gauss[9] = {0, 0, 0, 0, 0, 0, 0, 0, 2};
 constexpr int kLineSlot32Coll[9] = {0, 1, 0, 1, 0, 3, 2, 2, 2};
-// Mass: pipeline depth (elements a group marches through); collocated mass (k_mass): variant and depth.
-constexpr int kDefChainMass[9] = {8, 8, 8, 8, 4, 2, 4, 4, 2};
+// Mass, k_line: pipeline depth (elements a group marches through).
+constexpr int kDefChainLineMass[9] = {8, 8, 8, 8, 4, 2, 4, 4, 2};
+// k_mass (collocated, and several vectors with Gauss points): the collocated one-vector variant, and the depth.  With
+// k_line's depths several vectors of Gauss mass took up to 2.8 times as long (p = 2, 1e4 nodes of 12 vectors: 12 us, 33).
 constexpr int kDefVariantMassColl[9] = {0, 0, 0, 3, 3, 1, 3, 0, 4};
-constexpr int kDefChainMassColl[9] = {2, 2, 2, 4, 2, 4, 4, 4, 2};
+constexpr int kDefChainMass[9] = {2, 2, 2, 4, 2, 4, 4, 4, 2};
 // Device basis block (elements): B [Q][P], B^T [P][Q], D [Q][Q], D^T [Q][Q],
 // then the folded (even-odd) forms of the same four matrices: for a matrix M
 // with NO rows and NI columns, row o < ceil(NO/2) holds

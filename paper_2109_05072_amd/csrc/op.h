@@ -66,7 +66,7 @@ bool valid_variant(const mfhex_op_s &op, int prec, int variant);
 LaunchCfg config_for(const mfhex_op_s &op, int prec, int nvec);
 // diag(M A M) (FP64, masked nodes 0) into d [N].
 int diagonal_impl(mfhex_op op, double *d, hipStream_t s);
-int default_chain(const mfhex_op_s &op);
+int default_chain(const mfhex_op_s &op, int variant);
 int mode_of(const mfhex_op_s &op);
 
 int cg_solve(mfhex_op op, const double *b, double *x, void *work, const mfhex_cg_opts *o, mfhex_cg_stats *st,
