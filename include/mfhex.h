@@ -318,8 +318,10 @@ int mfhex_tune(mfhex_op op, int prec, int nrhs, void *scratch_dev, const char *c
  * Launch configuration the apply uses now for (prec, nrhs): the variant, the
  * elements per thread group and threads per group it stands for, and the
  * pipeline depth (element groups one thread group works through in turn,
- * loading the next group's data while it computes the current one; always 1
- * for diffusion).  Outputs may be NULL. */
+ * loading the next group's data while it computes the current one): the one
+ * that was set, else the one that the mass launch takes for this mesh.  1 for
+ * diffusion, whose line-fused launches choose their march by the mesh.
+ * Outputs may be NULL. */
 int mfhex_get_config(mfhex_op op, int prec, int nrhs, int32_t *variant, int32_t *elems_per_group,
                      int32_t *threads_per_group, int32_t *groups_per_block);
 
@@ -331,8 +333,9 @@ int mfhex_get_config(mfhex_op op, int prec, int nrhs, int32_t *variant, int32_t 
  * read the stored factors; 15 and 16 carry 4 and 8 vectors with the gradient
  * contractions on the FP64 matrix cores, collocated FP64 diffusion only) and
  * pipeline depth
- * groups_per_block (0: the operator's default, measured per order for mass
- * and 1 for diffusion; mass accepts 1 .. 64, diffusion only 1).
+ * groups_per_block (0: the operator's default, which for mass is measured per
+ * order and kernel and, one vector with Gauss points, shortened on small
+ * meshes; 1 for diffusion.  Mass accepts 1 .. 64, diffusion only 1).
  * MFHEX_ERR_ARG if out of range. */
 int mfhex_set_config(mfhex_op op, int prec, int nrhs, int32_t variant, int32_t groups_per_block);
 

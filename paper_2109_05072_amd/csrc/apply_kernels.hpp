@@ -935,19 +935,6 @@ static hipError_t prepare_lds(K kernel, size_t lds)
     return hipSuccess;
 }
 
-// Elements a thread group marches through: a pipeline depth that was asked for (mass); else at most the default
-// depth (mass) or 8, and no more than leave four
-// rounds of resident groups on the chip (16384 wavefronts), since a march trades parallelism for carried faces.
-// (p = 3, 5, 7 at 1e7 nodes: 2, 4 and 8 within 3%, 16 up to 10% slower.)
-static int line_march(int mode, int chain, bool auto_chain, int ney, int64_t columns, int nt)
-{
-    const int64_t cap = mode == kMass ? chain : 8;
-    int64_t m = columns * ney * (nt / 64) / 16384;
-    m = m < cap && (mode != kMass || auto_chain) ? m : cap;
-    m = m < ney ? m : ney;
-    return (int)(m < 1 ? 1 : m);
-}
-
 // The line-fused kernel.
 // Thread groups of a line-fused kernel: launches of fewer than 2^32 lanes each, the limit of a grid's extent (several
 // vectors of a large mesh exceed it: a chunk has its own groups).
@@ -984,7 +971,8 @@ static hipError_t launch_line_v(const ApplyLaunch &a)
     k.dirichlet = a.dirichlet;
     k.nvec = a.nvec;
     k.ngx = (a.v.nex + G - 1) / G;
-    k.march = line_march(a.mode, a.chain, a.auto_chain, a.v.ney, (int64_t)k.ngx * a.v.nez * a.nvec, NT);
+    k.march = MODE == kMass ? (a.chain < a.v.ney ? a.chain : a.v.ney)
+                            : line_march(kMarchDiff, a.v.ney, (int64_t)k.ngx * a.v.nez * a.nvec, NT);
     k.nych = (a.v.ney + k.march - 1) / k.march;
     const int64_t nblk = (int64_t)k.ngx * k.nych * a.v.nez;
     auto go = [&](auto kern) {
@@ -1018,7 +1006,7 @@ static hipError_t launch_mline_v(const ApplyLaunch &a)
     k.nvec = a.nvec;
     k.ngx = (a.v.nex + G - 1) / G;
     const int nch = (a.nvec + VC - 1) / VC;
-    k.march = line_march(a.mode, a.chain, a.auto_chain, a.v.ney, (int64_t)k.ngx * a.v.nez * nch, NT);
+    k.march = line_march(kMarchDiff, a.v.ney, (int64_t)k.ngx * a.v.nez * nch, NT);
     k.nych = (a.v.ney + k.march - 1) / k.march;
     const int64_t nblk = (int64_t)k.ngx * k.nych * a.v.nez * nch;
     auto go = [&](auto kern) {
@@ -1158,7 +1146,7 @@ static hipError_t launch_kgrad_pq(const KgradLaunch &a)
     k.nez = a.v.nez;
     k.dirichlet = a.dirichlet;
     k.ngx = (a.v.nex + G - 1) / G;
-    k.march = line_march(kDiff, 0, true, a.v.ney, (int64_t)k.ngx * a.v.nez, NT);
+    k.march = line_march(kMarchDiff, a.v.ney, (int64_t)k.ngx * a.v.nez, NT);
     k.nych = (a.v.ney + k.march - 1) / k.march;
     auto kern = k_kgrad<P, Q, COLLOC, G, NT>;
     const hipError_t e = prepare_lds(kern, lds);

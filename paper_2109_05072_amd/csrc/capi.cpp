@@ -222,13 +222,18 @@ int default_variant(const mfhex_op_s &op, int prec, int nvec)
     return 0;
 }
 
-// Pipeline depth: the mass kernels take the measured best number of element groups per thread group, each its own:
-// k_line's march carries a face, k_mass (collocated, or several vectors) divides its blocks by the depth.  The
-// diffusion kernels take one.
-int default_chain(const mfhex_op_s &op, int variant)
+// Pipeline depth of a launch.  Where none was asked for (0), the mass kernels take the measured best number of element
+// groups per thread group, each its own: k_line's march carries a face and is shortened on small meshes, k_mass
+// (collocated, or several vectors) divides its blocks by the depth.  Diffusion launches choose their march themselves;
+// their depth is 1.
+int pipeline_depth(const mfhex_op_s &op, int nvec, const LaunchCfg &c)
 {
     if (mode_of(op) != kMass) return 1;
-    return (line_variant(kMass, op.basis.colloc, false, variant) ? kDefChainLineMass : kDefChainMass)[op.Q - 2];
+    if (c.chain > 0) return c.chain;
+    if (!line_variant(kMass, op.basis.colloc, false, c.variant)) return kDefChainMass[op.Q - 2];
+    const int G = kLineG[op.Q - 2][line_slot(c.variant)];
+    const int64_t columns = (int64_t)((op.d.nex + G - 1) / G) * op.d.nez * nvec;
+    return line_march(kDefChainLineMass[op.Q - 2], op.d.ney, columns, line_nt(op.Q, G));
 }
 
 LaunchCfg config_for(const mfhex_op_s &op, int prec, int nvec)
@@ -237,7 +242,6 @@ LaunchCfg config_for(const mfhex_op_s &op, int prec, int nvec)
     if (it != op.config.end()) return it->second;
     LaunchCfg c;
     c.variant = default_variant(op, prec, nvec);
-    c.chain = default_chain(op, c.variant);
     return c;
 }
 
@@ -321,11 +325,9 @@ int apply_impl(mfhex_op op, int prec, int nrhs, const void *x, void *y, hipStrea
     void *const ebuf = ebuf_in ? ebuf_in : op->ebuf;
     if (ebuf && nrhs != 1)
         return set_error(op, MFHEX_ERR_UNSUPPORTED, "deterministic operators apply one right-hand side at a time");
-    const LaunchCfg cfg = config_for(*op, prec, nvec);
-    const int var = variant >= 0 ? variant : cfg.variant;
-    if (!valid_variant(*op, prec, var)) return set_error(op, MFHEX_ERR_ARG, "invalid launch variant");
-    const int nchain = chain > 0 ? chain : cfg.chain;
-    if (nchain > kMaxChain || (nchain > 1 && mode_of(*op) != kMass))
+    const LaunchCfg cfg = variant >= 0 ? LaunchCfg{variant, chain} : config_for(*op, prec, nvec);
+    if (!valid_variant(*op, prec, cfg.variant)) return set_error(op, MFHEX_ERR_ARG, "invalid launch variant");
+    if (cfg.chain < 0 || cfg.chain > kMaxChain || (cfg.chain > 1 && mode_of(*op) != kMass))
         return set_error(op, MFHEX_ERR_ARG, "invalid pipeline depth");
     if (zero && !ebuf) {
         const int c = check_hip(op, launch_zero(y, bytes, s), "zero fill");
@@ -342,9 +344,8 @@ int apply_impl(mfhex_op op, int prec, int nrhs, const void *x, void *y, hipStrea
     a.mode = mode_of(*op);
     a.vark = op->d.variable_kappa;
     a.nvec = nvec;
-    a.variant = var;
-    a.chain = nchain;
-    a.auto_chain = chain <= 0 && op->config.find({prec, nvec}) == op->config.end();
+    a.variant = cfg.variant;
+    a.chain = pipeline_depth(*op, nvec, cfg);
     a.otf = (op->d.flags & MFHEX_FLAG_OTF) != 0;
     a.vert = op->vert;
     a.x = x;
@@ -656,7 +657,7 @@ int mfhex_get_config(mfhex_op op, int prec, int nrhs, int32_t *variant, int32_t 
         *threads_per_group = line    ? line_nt(op->Q, g)
                              : mline ? mline_nt(op->Q, c.variant)
                                      : variant_nt(op->Q, c.variant);
-    if (groups_per_block) *groups_per_block = c.chain;
+    if (groups_per_block) *groups_per_block = pipeline_depth(*op, nrhs * op->d.ncomp, c);
     return MFHEX_OK;
 }
 
@@ -664,13 +665,9 @@ int mfhex_set_config(mfhex_op op, int prec, int nrhs, int32_t variant, int32_t g
 {
     if (!op || nrhs < 1) return fail(MFHEX_ERR_ARG, "bad argument");
     if (!valid_variant(*op, prec, variant)) return set_error(op, MFHEX_ERR_ARG, "invalid launch variant");
-    const int chain = groups_per_block > 0 ? groups_per_block : default_chain(*op, variant);
-    if (groups_per_block < 0 || chain > kMaxChain || (chain > 1 && mode_of(*op) != kMass))
+    if (groups_per_block < 0 || groups_per_block > kMaxChain || (groups_per_block > 1 && mode_of(*op) != kMass))
         return set_error(op, MFHEX_ERR_ARG, "invalid pipeline depth");
-    LaunchCfg c;
-    c.variant = variant;
-    c.chain = chain;
-    op->config[{prec, nrhs * op->d.ncomp}] = c;
+    op->config[{prec, nrhs * op->d.ncomp}] = LaunchCfg{variant, groups_per_block};
     return MFHEX_OK;
 }
 

@@ -51,7 +51,7 @@ enum Mode : int { kMass = 0, kDiff = 1, kRhs = 2 };
 constexpr int kMaxChain = 64;
 struct LaunchCfg {
     int variant = 0;
-    int chain = 1;
+    int chain = 0;  // pipeline depth; 0: automatic (pipeline_depth)
 };
 
 struct ApplyLaunch {
@@ -66,7 +66,6 @@ struct ApplyLaunch {
     int nvec;
     int variant;          // launch variant (elements and threads per group)
     int chain;            // mass: element groups per thread group (software pipeline depth), >= 1
-    bool auto_chain;      // the depth is the operator's default, not one that was asked for
     int otf;              // diffusion FP64: geometric factors evaluated in the kernel from the vertices
     const double *vert;   // device vertex coordinates [(nex+1)(ney+1)(nez+1)][3] (line-fused kernels)
     const void *x;        // input (for kRhs: the per-point f, FP64)
@@ -168,6 +167,15 @@ constexpr int variant_vc(int v)
 constexpr int kLineG[9][5] = {{16, 32, 8, 64, 4}, {7, 14, 28, 4, 2}, {4, 8, 16, 2, 1}, {5, 10, 2, 4, 1}, {7, 3, 5, 1, 2},
                               {5, 1, 2, 4, 3},    {2, 1, 4, 3, 1},   {3, 1, 2, 1, 3},  {1, 3, 2, 1, 2}};
 constexpr int line_nt(int Q, int G) { return (G * Q * Q + 63) / 64 * 64; }
+// Elements a line-fused group marches through where no depth was asked for: at most `most`, and no more than leave
+// four rounds of resident groups on the chip (16384 wavefronts), since a march trades parallelism for carried faces.
+// (Diffusion, p = 3, 5, 7 at 1e7 nodes: 2, 4 and 8 within 3%, 16 up to 10% slower.)
+constexpr int kMarchDiff = 8;
+constexpr int line_march(int most, int ney, int64_t columns, int nt)
+{
+    const int64_t m = columns * ney * (nt / 64) / 16384, cap = most < ney ? most : ney;
+    return (int)(m < 1 ? 1 : m < cap ? m : cap);
+}
 constexpr int line_slot(int v) { return v < 5 ? v : v == 14 ? 0 : v - 9; }
 constexpr bool line_variant(int mode, bool colloc, bool otf, int v)
 {
@@ -262,7 +270,7 @@ constexpr int kLineCostMass[9][5] = {{107, 101, 100, 157, 277}, {107, 101, 100, 
 // 213 -> 182, 193 -> 155, 168 -> 130, 165 -> 128, 169 -> 155 us against the stored-factor kernel).
 constexpr int kLineSlot32Gauss[9] = {0, 0, 0, 0, 0, 0, 0, 0, 2};
 constexpr int kLineSlot32Coll[9] = {0, 1, 0, 1, 0, 3, 2, 2, 2};
-// Mass, k_line: pipeline depth (elements a group marches through).
+// Mass, k_line: largest automatic pipeline depth (elements a group marches through).
 constexpr int kDefChainLineMass[9] = {8, 8, 8, 8, 4, 2, 4, 4, 2};
 // k_mass (collocated, and several vectors with Gauss points): the collocated one-vector variant, and the depth.  With
 // k_line's depths several vectors of Gauss mass took up to 2.8 times as long (p = 2, 1e4 nodes of 12 vectors: 12 us, 33).

@@ -56,7 +56,7 @@ void mg_release(mfhex_op op);
 int check_hip(mfhex_op op, hipError_t e, const char *what);
 
 // Internal apply: y (+)= A x on `s` with an explicit configuration.
-// variant < 0 / chain <= 0: the handle's configuration for (prec, nvec).
+// variant < 0: the handle's configuration for (prec, nvec), else this variant with depth chain (0: automatic).
 // ebuf (optional): element-value buffer that makes this call deterministic (element values stored,
 // then summed per node in a fixed order), in place of the operator's own.
 int apply_impl(mfhex_op op, int prec, int nrhs, const void *x, void *y, hipStream_t s, bool zero, int variant = -1,
@@ -66,7 +66,7 @@ bool valid_variant(const mfhex_op_s &op, int prec, int variant);
 LaunchCfg config_for(const mfhex_op_s &op, int prec, int nvec);
 // diag(M A M) (FP64, masked nodes 0) into d [N].
 int diagonal_impl(mfhex_op op, double *d, hipStream_t s);
-int default_chain(const mfhex_op_s &op, int variant);
+int pipeline_depth(const mfhex_op_s &op, int nvec, const LaunchCfg &c);
 int mode_of(const mfhex_op_s &op);
 
 int cg_solve(mfhex_op op, const double *b, double *x, void *work, const mfhex_cg_opts *o, mfhex_cg_stats *st,

@@ -85,7 +85,7 @@ int tune(mfhex_op op, int prec, int nrhs, void *scratch, const char *cache_path,
         if ((c = check_hip(op, hipMemcpyAsync(x64, ytest, len * es, hipMemcpyDeviceToDevice, s), "copy"))) return cleanup(c);
     }
     const int def = default_variant(*op, prec, nvec);
-    if ((c = apply_impl(op, prec, nrhs, x, yref, s, true, def, default_chain(*op, def)))) return cleanup(c);
+    if ((c = apply_impl(op, prec, nrhs, x, yref, s, true, def, 0))) return cleanup(c);
     std::vector<LaunchCfg> cand;
     const std::vector<int> depths = mode_of(*op) == kMass ? std::vector<int>{1, 2, 4} : std::vector<int>{1};
     for (int e = 0; e < kNumVariants; ++e)
@@ -132,7 +132,6 @@ int tune(mfhex_op op, int prec, int nrhs, void *scratch, const char *cache_path,
     if (c) return cleanup(c);
     LaunchCfg best;
     best.variant = def;
-    best.chain = default_chain(*op, def);
     float best_ms = 1e30f;
     for (size_t i = 0; i < ok.size(); ++i) {
         std::vector<float> t = times[i];
@@ -148,7 +147,7 @@ int tune(mfhex_op op, int prec, int nrhs, void *scratch, const char *cache_path,
         FILE *f = std::fopen(cache_path, "a");
         if (f) {
             std::fprintf(f, "%s %d %d %d %d %d %d %d\n", arch_name(op->device).c_str(), op->d.kind, op->d.quad, op->d.p,
-                         nvec, prec, best.variant, best.chain);
+                         nvec, prec, best.variant, pipeline_depth(*op, nvec, best));
             std::fclose(f);
         }
     }

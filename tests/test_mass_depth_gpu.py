@@ -19,3 +19,16 @@ def test_several_vectors_take_the_depth_of_their_kernel(gpu_lib, p):
         assert gauss.get_config(nrhs=nrhs)[3] == depth
         assert gauss.get_config(torch.float32, nrhs)[3] == depth
     assert three.get_config()[3] == depth
+
+
+@pytest.mark.parametrize("p,ne,largest", [(1, (3, 2, 2), 1), (3, (40, 24, 24), 7), (3, (3, 70, 3), 1)])
+def test_the_default_depth_is_automatic_when_it_is_set(gpu_lib, p, ne, largest):
+    # meshes that leave a march fewer elements than the largest default: depth 0 is that same launch, and what is
+    # reported is what runs (16384 wavefronts stay in flight)
+    op, _ = build(gpu_lib, *ne, p, "mass", "gauss", False)
+    default = op.get_config()
+    assert 1 <= default[3] <= largest
+    op.set_config(default[0], groups_per_block=0)
+    assert op.get_config() == default
+    op.set_config(default[0], groups_per_block=64)
+    assert op.get_config()[3] == 64
