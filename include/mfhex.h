@@ -302,7 +302,8 @@ int mfhex_mg_level(mfhex_op op, int level, int32_t *p, int64_t *n_nodes, double 
  * non-tensor products in MAGMA (Sec. 2.2), run here on the caller's own
  * operator: time every launch variant of the
  * fused kernel (elements per thread group, threads per group; for the mass
- * operator also pipeline depths 1, 2 and 4) on this operator, reject any whose
+ * operator its automatic depth and 1, 2 and 4) on this operator, the default
+ * launch among them, reject any whose
  * result differs from the default configuration by more than 1e-13 (relative,
  * max norm; 1e-5 for FP32), time the others in three interleaved rounds of ten
  * applies, keep the one with the smallest median for this handle and append

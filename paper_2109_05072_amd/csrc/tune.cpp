@@ -1,7 +1,8 @@
 // Autotuner for the fused apply: per (operator, precision, number of vectors)
 // pick the launch variant (elements and threads per group) and, for the mass
 // operator, the pipeline depth (element groups per thread group) by
-// measurement.
+// measurement.  The launch that it would replace, the default variant with
+// its automatic depth, is a candidate itself and wins a tie.
 //
 // Every candidate is first checked against the default configuration on a
 // random input (max-norm relative difference <= 1e-13 in FP64, 1e-5 in FP32;
@@ -86,16 +87,16 @@ int tune(mfhex_op op, int prec, int nrhs, void *scratch, const char *cache_path,
     }
     const int def = default_variant(*op, prec, nvec);
     if ((c = apply_impl(op, prec, nrhs, x, yref, s, true, def, 0))) return cleanup(c);
-    std::vector<LaunchCfg> cand;
-    const std::vector<int> depths = mode_of(*op) == kMass ? std::vector<int>{1, 2, 4} : std::vector<int>{1};
-    for (int e = 0; e < kNumVariants; ++e)
-        if (valid_variant(*op, prec, e))
-            for (int d : depths) {
-                LaunchCfg k;
-                k.variant = e;
-                k.chain = d;
-                cand.push_back(k);
-            }
+    // the default launch first: it stays unless another is faster; then every variant with the automatic depth and
+    // (mass) the others, each launch once
+    std::vector<LaunchCfg> cand{LaunchCfg{def, 0}};
+    for (int e = 0; e < kNumVariants; ++e) {
+        if (!valid_variant(*op, prec, e)) continue;
+        if (e != def) cand.push_back(LaunchCfg{e, 0});
+        if (mode_of(*op) != kMass) continue;
+        for (int d : {1, 2, 4})
+            if (d != pipeline_depth(*op, nvec, LaunchCfg{e, 0})) cand.push_back(LaunchCfg{e, d});
+    }
     hipEvent_t e0, e1;
     if ((c = check_hip(op, hipEventCreate(&e0), "hipEventCreate"))) return cleanup(c);
     if ((c = check_hip(op, hipEventCreate(&e1), "hipEventCreate"))) return cleanup(c);
@@ -130,8 +131,7 @@ int tune(mfhex_op op, int prec, int nrhs, void *scratch, const char *cache_path,
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (c) return cleanup(c);
-    LaunchCfg best;
-    best.variant = def;
+    LaunchCfg best{def, 0};
     float best_ms = 1e30f;
     for (size_t i = 0; i < ok.size(); ++i) {
         std::vector<float> t = times[i];

@@ -1,0 +1,138 @@
+// The autotuner (csrc/tune.cpp) with the GPU replaced by a model: apply_impl notes which configuration wrote which
+// vector, the difference kernel and the event clock answer from tables of the test.  One argument: the check to run.
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <functional>
+#include <map>
+#include <string>
+#include <vector>
+
+#include "../../paper_2109_05072_amd/csrc/blas.h"
+#include "../../paper_2109_05072_amd/csrc/op.h"
+
+using namespace mfhex;
+
+namespace {
+struct Run {
+    int variant, chain;
+    bool operator<(const Run &o) const { return variant != o.variant ? variant < o.variant : chain < o.chain; }
+};
+int g_default = 0;
+std::function<bool(const Run &)> g_valid = [](const Run &) { return true; };
+std::function<double(const Run &)> g_time = [](const Run &) { return 1.0; };
+std::function<double(const Run &, const Run &)> g_diff = [](const Run &, const Run &) { return 0.0; };
+std::map<const void *, Run> g_wrote;
+std::map<Run, int> g_timed;  // applies between events
+Run g_last{};
+double g_rel = 0.0;
+bool g_timing = false;
+}  // namespace
+
+namespace mfhex {
+int set_error(mfhex_op, int code, const std::string &) { return code; }
+int check_hip(mfhex_op, hipError_t e, const char *) { return e == hipSuccess ? MFHEX_OK : MFHEX_ERR_HIP; }
+int mode_of(const mfhex_op_s &op) { return op.d.kind == MFHEX_DIFFUSION ? kDiff : kMass; }
+bool valid_variant(const mfhex_op_s &, int, int v) { return v >= 0 && v < kNumVariants && g_valid({v, 0}); }
+int default_variant(const mfhex_op_s &, int, int) { return g_default; }
+int pipeline_depth(const mfhex_op_s &op, int, const LaunchCfg &c) { return mode_of(op) != kMass ? 1 : c.chain > 0 ? c.chain : 8; }
+hipError_t launch_fill_uniform(double *, int64_t, uint64_t, hipStream_t) { return hipSuccess; }
+hipError_t launch_copy(const void *, int, void *, int, int64_t, hipStream_t) { return hipSuccess; }
+hipError_t launch_relmaxdiff(const void *a, const void *b, int64_t, int, double *, double *, hipStream_t)
+{
+    g_rel = g_diff(g_wrote.at(a), g_wrote.at(b));
+    return hipSuccess;
+}
+int apply_impl(mfhex_op op, int, int, const void *, void *y, hipStream_t, bool, int variant, int chain, void *)
+{
+    if (chain > 1 && mode_of(*op) != kMass) return MFHEX_ERR_ARG;
+    g_wrote[y] = g_last = Run{variant, chain};
+    if (g_timing) ++g_timed[g_last];
+    return MFHEX_OK;
+}
+}  // namespace mfhex
+
+extern "C" {
+hipError_t hipGetDevicePropertiesR0600(hipDeviceProp_tR0600 *p, int)
+{
+    std::strcpy(p->gcnArchName, "gfx950:sramecc+");
+    return hipSuccess;
+}
+hipError_t hipMemcpyAsync(void *d, const void *, size_t n, hipMemcpyKind kind, hipStream_t)
+{
+    if (kind == hipMemcpyDeviceToHost && n == 2 * sizeof(double)) {
+        static_cast<double *>(d)[0] = g_rel;
+        static_cast<double *>(d)[1] = 1.0;
+    }
+    return hipSuccess;
+}
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipEventCreate(hipEvent_t *e) { return *e = nullptr, hipSuccess; }
+hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return g_timing = !g_timing, hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventElapsedTime(float *ms, hipEvent_t, hipEvent_t) { return *ms = (float)g_time(g_last), hipSuccess; }
+}
+
+static int fails = 0;
+#define CHECK(cond, ...)                            \
+    do {                                            \
+        if (!(cond)) {                              \
+            std::fprintf(stderr, "FAIL: " __VA_ARGS__); \
+            std::fprintf(stderr, "\n");             \
+            ++fails;                                \
+        }                                           \
+    } while (0)
+
+static mfhex_op_s make(int kind, int quad, int p, int nex, int ney, int nez, uint32_t flags = 0)
+{
+    mfhex_op_s op;
+    op.d = mfhex_desc{};
+    op.d.kind = kind;
+    op.d.quad = quad;
+    op.d.p = p;
+    op.d.q = quad == MFHEX_GAUSS ? p + 2 : p + 1;
+    op.d.ncomp = 1;
+    op.d.nex = nex;
+    op.d.ney = ney;
+    op.d.nez = nez;
+    op.d.flags = flags;
+    op.basis.colloc = quad != MFHEX_GAUSS;
+    op.P = p + 1;
+    op.Q = op.d.q;
+    op.E = (int64_t)nex * ney * nez;
+    op.N = 1000;
+    return op;
+}
+
+static LaunchCfg tuned(mfhex_op_s &op, const char *cache = nullptr)
+{
+    std::vector<char> scratch(MFHEX_TUNE_SCRATCH(op.N));
+    g_timed.clear();
+    CHECK(tune(&op, MFHEX_F64, 1, scratch.data(), cache, nullptr) == MFHEX_OK, "tune");
+    return op.config.at({MFHEX_F64, 1});
+}
+
+// The default launch (its variant with the automatic depth) is the fastest: the tuner keeps it.
+static void keeps_the_default()
+{
+    mfhex_op_s op = make(MFHEX_MASS, MFHEX_GAUSS, 3, 30, 30, 30);
+    g_valid = [](const Run &r) { return r.variant < 5; };
+    g_default = 2;
+    g_time = [](const Run &r) { return r.variant == 2 && (r.chain == 0 || r.chain == 8) ? 1.0 : 1.2; };
+    LaunchCfg c = tuned(op);
+    CHECK(c.variant == 2 && (c.chain == 0 || c.chain == 8), "default dropped for variant %d depth %d", c.variant, c.chain);
+    g_time = [](const Run &r) { return r.variant == 4 && r.chain == 4 ? 0.9 : 1.0; };
+    c = tuned(op);
+    CHECK(c.variant == 4 && c.chain == 4, "faster candidate missed: variant %d depth %d", c.variant, c.chain);
+}
+
+int main(int argc, char **argv)
+{
+    const std::string what = argc > 1 ? argv[1] : "";
+    if (what == "default") keeps_the_default();
+    else return std::fprintf(stderr, "unknown check %s\n", what.c_str()), 2;
+    if (fails) return 1;
+    std::printf("tune %s: OK\n", what.c_str());
+    return 0;
+}
