@@ -305,7 +305,10 @@ int mfhex_mg_level(mfhex_op op, int level, int32_t *p, int64_t *n_nodes, double 
  * operator its automatic depth and 1, 2 and 4) on this operator, the default
  * launch among them, reject any whose
  * result differs from the default configuration by more than 1e-13 (relative,
- * max norm; 1e-5 for FP32), time the others in three interleaved rounds of ten
+ * max norm; 1e-5 for FP32; variants that read stored factors where the default
+ * evaluates them, or the reverse, agree to 1e-13 with one another and to 1e-8
+ * with the default, for the rounding of the factors on ill-conditioned
+ * elements), time the others in three interleaved rounds of ten
  * applies, keep the one with the smallest median for this handle and append
  * "<arch> kind quad p nvec prec variant depth" to the text cache
  * at cache_path (NULL: no file); handles created later read the file named by

@@ -127,10 +127,43 @@ static void keeps_the_default()
     CHECK(c.variant == 4 && c.chain == 4, "faster candidate missed: variant %d depth %d", c.variant, c.chain);
 }
 
+// Variants with stored factors (0 .. 4) and with factors evaluated in the kernel (9 .. 14) differ by rounding that the
+// conditioning of the elements amplifies (2e-13 between the two at a shear of 1e4): sound ones of either are timed, wrong
+// ones of either are not.
+static void checks_results_by_factor_source()
+{
+    mfhex_op_s op = make(MFHEX_DIFFUSION, MFHEX_GAUSS, 3, 30, 30, 30);
+    g_valid = [](const Run &r) { return r.variant < 5 || (r.variant >= 9 && r.variant <= 14); };
+    g_default = 9;
+    int wrong = -1;
+    double off = 0.0;
+    g_diff = [&](const Run &a, const Run &b) {
+        if (a.variant != b.variant && (a.variant == wrong || b.variant == wrong)) return off;
+        return (a.variant < 5) == (b.variant < 5) ? 1e-15 : 2e-13;
+    };
+    int fast = 3;
+    g_time = [&](const Run &r) { return r.variant == fast ? 0.5 : 1.0; };
+    CHECK(tuned(op).variant == 3, "sound stored-factor variant dropped");
+    g_default = 0;
+    fast = 12;
+    CHECK(tuned(op).variant == 12, "sound in-kernel variant dropped");
+    for (int d : {0, 9})
+        for (int v : {0, 1, 4, 9, 10, 14})
+            for (double by : {1.0, 1e-3, 1e-12}) {
+                // (1e-12 from the others of its source: too much, unless it is the one that stands for the source)
+                if (v == d || (by == 1e-12 && (v == 0 || v == 9))) continue;
+                g_default = d;
+                wrong = fast = v;
+                off = by;
+                CHECK(tuned(op).variant != v, "default %d: variant %d is wrong by %g and was taken", d, v, by);
+            }
+}
+
 int main(int argc, char **argv)
 {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "default") keeps_the_default();
+    else if (what == "source") checks_results_by_factor_source();
     else return std::fprintf(stderr, "unknown check %s\n", what.c_str()), 2;
     if (fails) return 1;
     std::printf("tune %s: OK\n", what.c_str());
