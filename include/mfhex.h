@@ -310,9 +310,13 @@ int mfhex_mg_level(mfhex_op op, int level, int32_t *p, int64_t *n_nodes, double 
  * with the default, for the rounding of the factors on ill-conditioned
  * elements), time the others in three interleaved rounds of ten
  * applies, keep the one with the smallest median for this handle and append
- * "<arch> kind quad p nvec prec variant depth" to the text cache
+ * "<key> kind quad p nvec prec variant depth" to the text cache
  * at cache_path (NULL: no file); handles created later read the file named by
- * the environment variable MFHEX_TUNE_CACHE.  scratch_dev: caller-owned
+ * the environment variable MFHEX_TUNE_CACHE and take the lines whose key is
+ * theirs: the architecture, the version of the variant numbers (lines of
+ * another one, or without it, are ignored), the OTF, deterministic and
+ * coefficient options, the row length nex to an eighth of an octave and the
+ * octave of the element count.  scratch_dev: caller-owned
  * device buffer of at least MFHEX_TUNE_SCRATCH(n_nodes * nvec) bytes
  * (256-byte aligned).  Synchronizes `stream`. */
 #define MFHEX_TUNE_SCRATCH(len) (3 * ((((size_t)(len)) * 8 + 255) & ~(size_t)255) + 32768)

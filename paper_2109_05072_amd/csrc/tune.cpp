@@ -14,8 +14,9 @@
 // against the default to 1e-8 (a wrong launch is off by the result's own size),
 // and the rest of that source against it.  Those that agree are timed with HIP
 // events over repeated applies.  The winner is kept on the handle and appended to a
-// text cache "<arch> kind quad p nvec prec variant depth", which later
-// handles read from the file named by MFHEX_TUNE_CACHE.  This plays the role of the
+// text cache "<key> kind quad p nvec prec variant depth", which later
+// handles read from the file named by MFHEX_TUNE_CACHE (cache_key: what else a
+// choice depends on).  This plays the role of the
 // offline benchmark sweeps that select kernel variants per problem shape
 // (Sec. 2, the MAGMA batched kernels chosen from tuning tables).
 #include <algorithm>
@@ -42,6 +43,23 @@ std::string arch_name(int device)
     return c == std::string::npos ? a : a.substr(0, c);
 }
 
+// First field of a cache line, one word: the architecture; the meaning of the variant numbers (raised when a number
+// comes to stand for another kernel); whether the operator evaluates its factors (a number is another kernel then), is
+// deterministic or has a coefficient; the row length, to an eighth of an octave, on which the idle lanes of a group
+// depend; and the octave of the element count, on which the best depth does.
+constexpr int kVariantNumbers = 2;
+std::string cache_key(const mfhex_op_s &op)
+{
+    int octave = 0, size = 0;
+    while (op.d.nex >> octave > 15) ++octave;
+    while (op.E >> size > 1) ++size;
+    char key[64];
+    std::snprintf(key, sizeof key, ":v%d:%s%s%s:x%d:e%d", kVariantNumbers, op.d.flags & MFHEX_FLAG_OTF ? "o" : "-",
+                  op.d.flags & MFHEX_FLAG_DETERMINISTIC ? "d" : "-", op.d.variable_kappa ? "k" : "-",
+                  op.d.nex >> octave << octave, size);
+    return arch_name(op.device) + key;
+}
+
 }  // namespace
 
 void load_tune_cache(mfhex_op op)
@@ -50,13 +68,13 @@ void load_tune_cache(mfhex_op op)
     if (!path || !*path) return;
     FILE *f = std::fopen(path, "r");
     if (!f) return;
-    const std::string arch = arch_name(op->device);
+    const std::string key = cache_key(*op);
     char line[256], a[64];
     while (std::fgets(line, sizeof line, f)) {
         int kind, quad, p, nvec, prec, epb, depth;
         if (std::sscanf(line, "%63s %d %d %d %d %d %d %d", a, &kind, &quad, &p, &nvec, &prec, &epb, &depth) != 8)
             continue;
-        if (arch != a || kind != op->d.kind || quad != op->d.quad || p != op->d.p || !valid_variant(*op, prec, epb))
+        if (key != a || kind != op->d.kind || quad != op->d.quad || p != op->d.p || !valid_variant(*op, prec, epb))
             continue;
         if (depth < 1 || depth > kMaxChain || (depth > 1 && mode_of(*op) != kMass)) continue;
         LaunchCfg c;
@@ -163,7 +181,7 @@ int tune(mfhex_op op, int prec, int nrhs, void *scratch, const char *cache_path,
     if (cache_path && *cache_path) {
         FILE *f = std::fopen(cache_path, "a");
         if (f) {
-            std::fprintf(f, "%s %d %d %d %d %d %d %d\n", arch_name(op->device).c_str(), op->d.kind, op->d.quad, op->d.p,
+            std::fprintf(f, "%s %d %d %d %d %d %d %d\n", cache_key(*op).c_str(), op->d.kind, op->d.quad, op->d.p,
                          nvec, prec, best.variant, pipeline_depth(*op, nvec, best));
             std::fclose(f);
         }

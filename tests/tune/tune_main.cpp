@@ -159,10 +159,52 @@ static void checks_results_by_factor_source()
             }
 }
 
+// A cached choice reaches the operators it was measured for: same options, row length and size (a bucket each), same
+// meaning of the variant numbers.
+static void cache_lines_reach_their_operators()
+{
+    const char *path = "tune_cache.txt";
+    g_valid = [](const Run &r) { return r.variant < 5 || (r.variant >= 9 && r.variant <= 14); };
+    g_default = 9;
+    g_time = [](const Run &r) { return r.variant == 3 ? 0.5 : 1.0; };
+    auto found = [](mfhex_op_s op) {
+        load_tune_cache(&op);
+        return op.config.count({MFHEX_F64, 1}) == 1 && op.config.at({MFHEX_F64, 1}).variant == 3;
+    };
+    auto diff = [](int nex, int ney, int nez, uint32_t flags = 0, int vark = 0) {
+        mfhex_op_s op = make(MFHEX_DIFFUSION, MFHEX_GAUSS, 3, nex, ney, nez, flags);
+        op.d.variable_kappa = vark;
+        return op;
+    };
+    setenv("MFHEX_TUNE_CACHE", path, 1);
+    const uint32_t none = 0, otf = MFHEX_FLAG_OTF, det = MFHEX_FLAG_DETERMINISTIC;
+    for (uint32_t flags : {none, otf, det}) {
+        std::remove(path);
+        mfhex_op_s op = diff(53, 40, 40, flags);
+        tuned(op, path);
+        for (uint32_t other : {none, otf, det})
+            CHECK(found(diff(53, 40, 40, other)) == (other == flags), "flags %u tuned, %u created", flags, other);
+    }
+    std::remove(path);
+    mfhex_op_s op = diff(53, 40, 40);
+    tuned(op, path);
+    CHECK(found(diff(54, 41, 40)), "a mesh of much the same size");
+    CHECK(!found(diff(1, 40, 53 * 40)), "rows of one element");
+    CHECK(!found(diff(53, 4, 4)), "a small mesh");
+    CHECK(!found(diff(53, 40, 40, 0, 1)), "a coefficient");
+    // a line of the earlier format: its variant 3 was another kernel
+    FILE *f = std::fopen(path, "w");
+    std::fprintf(f, "gfx950 %d %d 3 1 %d 3 1\n", MFHEX_DIFFUSION, MFHEX_GAUSS, MFHEX_F64);
+    std::fclose(f);
+    CHECK(!found(diff(53, 40, 40)), "a line without a version");
+    std::remove(path);
+}
+
 int main(int argc, char **argv)
 {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "default") keeps_the_default();
+    else if (what == "cache") cache_lines_reach_their_operators();
     else if (what == "source") checks_results_by_factor_source();
     else return std::fprintf(stderr, "unknown check %s\n", what.c_str()), 2;
     if (fails) return 1;
