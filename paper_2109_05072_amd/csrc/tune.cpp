@@ -114,8 +114,16 @@ int tune(mfhex_op op, int prec, int nrhs, void *scratch, const char *cache_path,
     // the default launch first: it stays unless another is faster; then every variant with the automatic depth and
     // (mass) the others, each launch once
     std::vector<LaunchCfg> cand{LaunchCfg{def, 0}};
+    const auto in_kernel = [&](int v) {
+        return line_variant(mode_of(*op), op->basis.colloc, (op->d.flags & MFHEX_FLAG_OTF) != 0, v);
+    };
+    const auto same_launch = [&](int v, int w) {  // slots of the line-fused kernel with one group size
+        return in_kernel(v) && in_kernel(w) && kLineG[op->Q - 2][line_slot(v)] == kLineG[op->Q - 2][line_slot(w)];
+    };
     for (int e = 0; e < kNumVariants; ++e) {
         if (!valid_variant(*op, prec, e)) continue;
+        if (e != def && std::any_of(cand.begin(), cand.end(), [&](const LaunchCfg &k) { return same_launch(e, k.variant); }))
+            continue;
         if (e != def) cand.push_back(LaunchCfg{e, 0});
         if (mode_of(*op) != kMass) continue;
         for (int d : {1, 2, 4})
@@ -129,9 +137,6 @@ int tune(mfhex_op op, int prec, int nrhs, void *scratch, const char *cache_path,
     // of each other change order from round to round)
     const int reps = 10, rounds = 3;
     const double tol = prec == MFHEX_F32 ? 1e-5 : 1e-13, tol_source = prec == MFHEX_F32 ? 1e-5 : 1e-8;
-    const auto in_kernel = [&](int v) {
-        return line_variant(mode_of(*op), op->basis.colloc, (op->d.flags & MFHEX_FLAG_OTF) != 0, v);
-    };
     std::vector<LaunchCfg> ok;
     for (const bool source : {in_kernel(def), !in_kernel(def)}) {
         bool reference = source == in_kernel(def);  // yref holds a result with factors of this source

@@ -21,7 +21,7 @@ def tuner(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("what", ["default", "source", "cache"])
+@pytest.mark.parametrize("what", ["default", "source", "cache", "once"])
 def test_tuner(tuner, tmp_path, what):
     r = subprocess.run([tuner, what], capture_output=True, text=True, cwd=tmp_path, timeout=60,
                        env={k: v for k, v in os.environ.items() if k != "MFHEX_TUNE_CACHE"})

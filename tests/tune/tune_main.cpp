@@ -200,11 +200,36 @@ static void cache_lines_reach_their_operators()
     std::remove(path);
 }
 
+// The slots of the line-fused kernel at q = 8 hold the group sizes 2, 1, 4, 3, 1, and variant 14 is variant 9: four launches.
+static void times_a_launch_once()
+{
+    mfhex_op_s op = make(MFHEX_DIFFUSION, MFHEX_GAUSS, 6, 30, 30, 30);
+    g_valid = [](const Run &r) { return r.variant < 5 || (r.variant >= 9 && r.variant <= 14); };
+    for (int d = 9; d <= 14; ++d) {
+        g_default = d;
+        tuned(op);
+        std::map<int, int> by_size;
+        int line = 0;
+        for (const auto &t : g_timed)
+            if (t.first.variant >= 9) ++by_size[kLineG[6][line_slot(t.first.variant)]], ++line;
+        CHECK(line == 4 && by_size.size() == 4 && g_timed.size() == 9, "default %d: %d line-fused of %d timed", d, line,
+              (int)g_timed.size());
+        CHECK(g_timed.count({d, 0}) == 1, "default %d not timed", d);
+    }
+    // mass, same q: every slot's depths
+    mfhex_op_s mass = make(MFHEX_MASS, MFHEX_GAUSS, 6, 30, 30, 30);
+    g_valid = [](const Run &r) { return r.variant < 5; };
+    g_default = 4;
+    tuned(mass);
+    CHECK(g_timed.size() == 16, "mass: %d launches timed", (int)g_timed.size());
+}
+
 int main(int argc, char **argv)
 {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "default") keeps_the_default();
     else if (what == "cache") cache_lines_reach_their_operators();
+    else if (what == "once") times_a_launch_once();
     else if (what == "source") checks_results_by_factor_source();
     else return std::fprintf(stderr, "unknown check %s\n", what.c_str()), 2;
     if (fails) return 1;
