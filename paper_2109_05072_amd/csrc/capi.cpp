@@ -181,17 +181,17 @@ int default_variant(const mfhex_op_s &op, int prec, int nvec)
             const int v = kDefVariantMassColl[op.Q - 2];
             return valid_variant(op, prec, v) ? v : 0;
         }
-        int slot = 0;
-        if (prec == MFHEX_F32 && mode == kDiff) {
-            slot = (coll ? kLineSlot32Coll : kLineSlot32Gauss)[op.Q - 2];
-        } else {
-            const int *cost = (mode == kMass ? kLineCostMass : coll ? kLineCostColl : kLineCostDiff)[op.Q - 2];
-            int64_t best = INT64_MAX;
-            for (int i = 0; i < 5; ++i) {
-                const int G = kLineG[op.Q - 2][i];
-                const int64_t t = (int64_t)cost[i] * ((op.d.nex + G - 1) / G) * G;
-                if (t < best) best = t, slot = i;
-            }
+        const bool f32 = prec == MFHEX_F32 && mode == kDiff, few = f32 && op.E <= kFewElements;
+        const auto &table = mode == kMass ? kLineCostMass
+                            : coll        ? (f32 ? kLineCost32Coll : kLineCostColl)
+                                          : (f32 ? kLineCost32Diff : kLineCostDiff);
+        int slot = few ? (coll ? kLineSlot32Coll : kLineSlot32Gauss)[op.Q - 2] : 0;
+        int64_t best = INT64_MAX;
+        for (int i = 0; i < 5 && !few; ++i) {
+            const int G = kLineG[op.Q - 2][i];
+            const int64_t idle = (int64_t)(op.d.nex + G - 1) / G * G - op.d.nex;
+            const int64_t t = table[op.Q - 2][i] * (100 * (int64_t)op.d.nex + (f32 ? kIdle32Percent : 100) * idle);
+            if (t < best) best = t, slot = i;
         }
         return line_variant(mode, coll, otf, slot) ? slot : 9 + slot;
     }

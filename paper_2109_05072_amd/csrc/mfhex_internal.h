@@ -266,8 +266,21 @@ constexpr int kLineCostColl[9][5] = {{102, 102, 137, 100, 245}, {100, 107, 105, 
 constexpr int kLineCostMass[9][5] = {{107, 101, 100, 157, 277}, {107, 101, 100, 157, 277}, {114, 103, 100, 178, 308},
                                      {112, 100, 167, 124, 255}, {100, 126, 106, 198, 138}, {100, 175, 133, 105, 106},
                                      {120, 152, 100, 111, 152}, {100, 146, 113, 146, 100}, {129, 100, 101, 129, 101}};
-// FP32: the measured best slot, Gauss and collocated (p = 1..8, 1e7 nodes: 1583 -> 1079, 384 -> 342, 287 -> 223,
-// 213 -> 182, 193 -> 155, 168 -> 130, 165 -> 128, 169 -> 155 us against the stored-factor kernel).
+// FP32 diffusion (p = 1..8, 1e7 nodes, Gauss: 1583 -> 1079, 384 -> 342, 287 -> 223, 213 -> 182, 193 -> 155, 168 -> 130,
+// 165 -> 128, 169 -> 155 us against the stored-factor kernel): medians over boxes of 1e6 to 1e7 nodes.  An idle element
+// counts 0.4 of a used one (its lanes skip the loads and atomics), which keeps the choice within 20% of the fastest slot
+// for rows of 1 to 25 elements at 2e5 and 2e6 nodes; counted in full it was up to 39% off.  One slot for every row length
+// took up to twice as long on short rows: collocated p = 2, rows of 1 .. 7 at 2e6 nodes 214 .. 64 us with groups of 14,
+// 119 .. 43 with the row's own; Gauss p = 7, rows of one 64, 40.
+constexpr int kIdle32Percent = 40;
+constexpr int kLineCost32Diff[9][5] = {{103, 100, 102, 156, 276}, {103, 100, 102, 156, 276}, {117, 103, 100, 171, 323},
+                                       {102, 100, 117, 118, 200}, {100, 108, 101, 147, 139}, {100, 132, 115, 110, 116},
+                                       {111, 140, 100, 104, 140}, {100, 141, 115, 141, 100}, {113, 159, 100, 113, 100}};
+constexpr int kLineCost32Coll[9][5] = {{106, 100, 130, 102, 223}, {102, 100, 100, 135, 226}, {113, 100, 112, 150, 258},
+                                       {107, 100, 142, 116, 234}, {100, 114, 107, 220, 158}, {100, 183, 139, 113, 121},
+                                       {127, 157, 100, 107, 157}, {100, 136, 107, 136, 100}, {113, 159, 100, 113, 100}};
+// FP32 diffusion on meshes of at most one element a compute unit, which take a launch's time (12 us) in any slot.
+constexpr int64_t kFewElements = 256;
 constexpr int kLineSlot32Gauss[9] = {0, 0, 0, 0, 0, 0, 0, 0, 2};
 constexpr int kLineSlot32Coll[9] = {0, 1, 0, 1, 0, 3, 2, 2, 2};
 // Mass, k_line: largest automatic pipeline depth (elements a group marches through).
