@@ -165,8 +165,9 @@ bool valid_variant(const mfhex_op_s &op, int prec, int variant)
     if (variant_gf(variant) && (mode_of(op) != kDiff || op.basis.colloc || otf)) return false;
     // the matrix-core gradient: collocated FP64 diffusion with stored factors
     if (variant_mx(variant) && (mode_of(op) != kDiff || !op.basis.colloc || otf || prec != MFHEX_F64)) return false;
-    if (line_variant(mode_of(op), op.basis.colloc, otf, variant)) return true;
-    return apply_lds(op.P, op.Q, mode_of(op), prec == MFHEX_F32 ? 4 : 8, variant) <= kMaxLds;
+    if (line_variant(op.Q, mode_of(op), op.basis.colloc, otf, variant)) return true;
+    const int shape = elem_shape(op.Q, mode_of(op), op.basis.colloc, otf, variant);
+    return apply_lds(op.P, op.Q, mode_of(op), prec == MFHEX_F32 ? 4 : 8, shape) <= kMaxLds;
 }
 
 int default_variant(const mfhex_op_s &op, int prec, int nvec)
@@ -185,15 +186,23 @@ int default_variant(const mfhex_op_s &op, int prec, int nvec)
         const auto &table = mode == kMass ? kLineCostMass
                             : coll        ? (f32 ? kLineCost32Coll : kLineCostColl)
                                           : (f32 ? kLineCost32Diff : kLineCostDiff);
+        const int elem = elem_slot(op.Q, mode, coll, otf);
+        if (mode == kDiff && !otf && !few) {
+            const ElemRange r = coll ? (f32 ? kElemColl32 : kElemColl)[op.Q - 2] : f32 ? kElemGauss32[op.Q - 2] : ElemRange{};
+            const int v = coll ? elem : kElemGauss32Variant[op.Q - 2];
+            const int64_t bytes = op.NQ * kQdDiff * (f32 ? 4 : 8);
+            if ((op.d.nex <= r.rows || bytes <= ((int64_t)r.mb << 20)) && valid_variant(op, prec, v)) return v;
+        }
         int slot = few ? (coll ? kLineSlot32Coll : kLineSlot32Gauss)[op.Q - 2] : 0;
         int64_t best = INT64_MAX;
         for (int i = 0; i < 5 && !few; ++i) {
+            if (i == elem) continue;
             const int G = kLineG[op.Q - 2][i];
             const int64_t idle = (int64_t)(op.d.nex + G - 1) / G * G - op.d.nex;
             const int64_t t = table[op.Q - 2][i] * (100 * (int64_t)op.d.nex + (f32 ? kIdle32Percent : 100) * idle);
             if (t < best) best = t, slot = i;
         }
-        return line_variant(mode, coll, otf, slot) ? slot : 9 + slot;
+        return mode == kMass || coll || otf ? slot : 9 + slot;
     }
     const int eb = prec == MFHEX_F32 ? 4 : 8;
     if (!op.ebuf && !op.d.variable_kappa) {
@@ -230,7 +239,7 @@ int pipeline_depth(const mfhex_op_s &op, int nvec, const LaunchCfg &c)
 {
     if (mode_of(op) != kMass) return 1;
     if (c.chain > 0) return c.chain;
-    if (!line_variant(kMass, op.basis.colloc, false, c.variant)) return kDefChainMass[op.Q - 2];
+    if (!line_variant(op.Q, kMass, op.basis.colloc, false, c.variant)) return kDefChainMass[op.Q - 2];
     const int G = kLineG[op.Q - 2][line_slot(c.variant)];
     const int64_t columns = (int64_t)((op.d.nex + G - 1) / G) * op.d.nez * nvec;
     return line_march(kDefChainLineMass[op.Q - 2], op.d.ney, columns, line_nt(op.Q, G));
@@ -646,17 +655,18 @@ int mfhex_get_config(mfhex_op op, int prec, int nrhs, int32_t *variant, int32_t 
     if (!op || nrhs < 1) return fail(MFHEX_ERR_ARG, "bad argument");
     const LaunchCfg c = config_for(*op, prec, nrhs * op->d.ncomp);
     if (variant) *variant = c.variant;
-    const bool line = line_variant(mode_of(*op), op->basis.colloc, (op->d.flags & MFHEX_FLAG_OTF) != 0, c.variant);
+    const bool line = line_variant(op->Q, mode_of(*op), op->basis.colloc, (op->d.flags & MFHEX_FLAG_OTF) != 0, c.variant);
+    const int shape = elem_shape(op->Q, mode_of(*op), op->basis.colloc, (op->d.flags & MFHEX_FLAG_OTF) != 0, c.variant);
     const bool mline = !op->ebuf && mline_serves(op->P, op->Q, mode_of(*op), op->basis.colloc, prec == MFHEX_F32 ? 4 : 8,
                                                  c.variant, nrhs * op->d.ncomp);
     const int g = line    ? kLineG[op->Q - 2][line_slot(c.variant)]
                   : mline ? mline_g(op->Q, c.variant)
-                          : variant_g(op->Q, c.variant, mode_of(*op));
+                          : variant_g(op->Q, shape, mode_of(*op));
     if (elems_per_group) *elems_per_group = g;
     if (threads_per_group)
         *threads_per_group = line    ? line_nt(op->Q, g)
                              : mline ? mline_nt(op->Q, c.variant)
-                                     : variant_nt(op->Q, c.variant);
+                                     : variant_nt(op->Q, shape);
     if (groups_per_block) *groups_per_block = pipeline_depth(*op, nrhs * op->d.ncomp, c);
     return MFHEX_OK;
 }
