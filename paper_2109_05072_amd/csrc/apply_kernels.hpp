@@ -1075,7 +1075,7 @@ static hipError_t launch_apply_v(const ApplyLaunch &a)
     else if constexpr (variant_gf(V) || OTF) return hipErrorInvalidValue;
     else {
         if constexpr (!DET && !VARK && mline_variant(MODE, COLLOC, V) && apply_lds(P, Q, MODE, sizeof(T), V) <= kMaxLds)
-            if (mline_serves(P, Q, MODE, COLLOC, sizeof(T), V, a.nvec)) return launch_mline_v<Q, T, V>(a);
+            if (mline_serves(P, Q, MODE, COLLOC, sizeof(T), V, a.nvec, a.v.nex, a.v.nelem)) return launch_mline_v<Q, T, V>(a);
         return launch_element_v<P, Q, COLLOC, MODE, VARK, T, elem_shape(Q, MODE, COLLOC, OTF, V), DET>(a);
     }
 }

@@ -207,17 +207,20 @@ int default_variant(const mfhex_op_s &op, int prec, int nvec)
     const int eb = prec == MFHEX_F32 ? 4 : 8;
     if (!op.ebuf && !op.d.variable_kappa) {
         // Collocated diffusion: k_mline where it serves the launch (mline_serves), in 8s from five vectors on (3e6 nodes,
-        // FP64, p = 3, 6: 5 vectors 238, 218 us in an 8 and 300, 296 in 4s; 4 vectors 239, 200 and 148, 139).  Two FP64
-        // vectors from q = 5 on are faster as a pair (p = 4, 5, 7: 127, 114, 98 against 142, 141, 116), FP32 ones at
-        // q = 9 (74 against 82); at q = 9 in FP64, where 4 is the largest chunk, so are more than 4 (24 vectors of 2e6
-        // nodes: 901 against 992).
+        // FP64, p = 3, 6: 5 vectors 238, 218 us in an 8 and 300, 296 in 4s; 4 vectors 239, 200 and 148, 139), in 4s where
+        // an 8 does not fit.  Two vectors are faster as a pair: FP64 from q = 5 on (p = 4, 5, 7: 127, 114, 98 against 142,
+        // 141, 116) and at q = 4 where the row leaves more than a quarter of the groups of four idle (rows of 5, 6 18.5,
+        // 18.7 against 22.4, 20.4); FP32 at q = 9 (74 against 82) and where cached_factors says.  At q = 9 in
+        // FP64, where 4 is the largest chunk, so are more than 4 (24 vectors of 2e6 nodes: 901 against 992).
         const bool f32 = prec == MFHEX_F32;
-        const bool pair = (nvec == 2 && op.Q >= (f32 ? 9 : 5)) || (nvec > 4 && op.Q == 9 && !f32);
+        const bool pair2 = f32 ? op.Q >= 9 || cached_factors(op.Q, eb, op.E)
+                               : op.Q >= 5 || (op.Q == 4 && 4 * ((op.d.nex + 3) / 4 * 4) > 5 * (int64_t)op.d.nex);
+        const bool pair = (nvec == 2 && pair2) || (nvec > 4 && op.Q == 9 && !f32);
         const auto served = [&](int v) {
-            return valid_variant(op, prec, v) && mline_serves(op.P, op.Q, mode_of(op), op.basis.colloc, eb, v, nvec);
+            return valid_variant(op, prec, v) && mline_serves(op.P, op.Q, mode_of(op), op.basis.colloc, eb, v, nvec, op.d.nex, op.E);
         };
         if (!pair && nvec > 4 && served(7)) return 7;
-        if (!pair && (nvec <= 4 || !f32) && served(6)) return 6;
+        if (!pair && (nvec <= 4 || (!f32 && !valid_variant(op, prec, 7))) && served(6)) return 6;
     }
     // (with the scatter staging that several chunks need, the chunk must still leave room for two
     // thread groups per compute unit)
@@ -658,7 +661,7 @@ int mfhex_get_config(mfhex_op op, int prec, int nrhs, int32_t *variant, int32_t 
     const bool line = line_variant(op->Q, mode_of(*op), op->basis.colloc, (op->d.flags & MFHEX_FLAG_OTF) != 0, c.variant);
     const int shape = elem_shape(op->Q, mode_of(*op), op->basis.colloc, (op->d.flags & MFHEX_FLAG_OTF) != 0, c.variant);
     const bool mline = !op->ebuf && mline_serves(op->P, op->Q, mode_of(*op), op->basis.colloc, prec == MFHEX_F32 ? 4 : 8,
-                                                 c.variant, nrhs * op->d.ncomp);
+                                                 c.variant, nrhs * op->d.ncomp, op->d.nex, op->E);
     const int g = line    ? kLineG[op->Q - 2][line_slot(c.variant)]
                   : mline ? mline_g(op->Q, c.variant)
                           : variant_g(op->Q, shape, mode_of(*op));

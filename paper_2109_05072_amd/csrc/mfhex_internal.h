@@ -249,18 +249,54 @@ constexpr size_t apply_lds(int P, int Q, int mode, int elem_bytes, int v, bool s
 // and 16-vector chunks at q = 6 while still leaving room for a second group on the CU.
 constexpr size_t kMaxLds = 98304;
 constexpr size_t kLdsTwoGroups = 81920;  // at most this much LDS leaves room for two thread groups per CU
-// Whether k_mline takes a launch of nvec vectors in chunks of variant v (else k_apply): chunks of less than 64 bytes a
-// node update half a line at a time, which k_apply's staged runs avoid where two of its groups fit a CU.  Then k_mline
-// wins with one chunk, or with three of which the last is at least half full (k_apply would fill its last run no better):
-// p = 7, FP64, 12 vectors 459 against 517 us, but 9 582 against 543; 24 of 2e6 nodes 794 against 685, 48 of 1e6 747
-// against 641.  FP32, 24 vectors: 340, 310, 289, 270, 287, 249 at p = 2 .. 7 against 520, 399, 345, 297, 472, 307 and 18
-// 518, 415, 404 at p = 2, 6, 7 against 786, 615, 419 (p = 5 437 against 425), 48 392, 365 at p = 2, 6 against 363, 342.
-constexpr bool mline_serves(int P, int Q, int mode, bool colloc, int elem_bytes, int v, int nvec)
+// Rows (index q - 2) from which k_mline's groups are faster than k_apply's single elements, in chunks of 4 with 2 or 4
+// vectors and with 3 (k_apply has no chunk of three), and in chunks of 8; us of 3e5 nodes, k_apply and k_mline:
+//   FP64, chunks of 4, 2 vectors: p = 1 rows of 1, 2, 3 52 95, 75 97, 0.91; p = 2 rows of 1, 2, 3, 4 18 39, 20 32, 22 25,
+//     0.99; p = 3 rows of 1, 2, 3 12 25, 16 20, 0.99; 4 vectors: p = 4 rows of 1, 2 17 19, 0.89; 3 vectors: p = 2, 3 rows of
+//     one 30 40, 20 26
+//   FP64, chunks of 8, 8 vectors: p = 2 rows of 1, 2 41 48, 0.85; p = 3 29 32, 0.83; p = 4 rows of 1, 2, 3, 4 26 38, 31 34,
+//     35 42, 35 39 (5 vectors 1.21, 0.90, 1.10, 0.94)
+//   FP32, chunks of 8, 8 vectors: p = 1 rows of 1, 2, 3 52 76, 71 83, 0.88; p = 4 rows of 1, 2 17 22, 0.95
+constexpr int kMlineRows4[9] = {3, 4, 3, 2, 1, 1, 1, 1, 1};
+constexpr int kMlineRows3[9] = {2, 2, 2, 1, 1, 1, 1, 1, 1};
+constexpr int kMlineRows8[9] = {2, 2, 2, 4, 1, 1, 1, 1, 1};
+constexpr int kMlineRows8f32[9] = {3, 2, 1, 2, 1, 1, 1, 1, 1};
+// Sizes whose stored factors come from the Infinity Cache, where k_apply's single elements are ahead of k_mline's groups
+// (MB): p = 4, 8 .. 12 FP64 vectors, 16^3 elements (25 MB) 34 and 68 us against 36 and 74, 21^3 (56 MB), 12 vectors 0.82;
+// p = 5, 2 FP32 vectors, 17^3 and 21^3 (48 MB) 23 and 39 against 26 and 43, 29^3 (126 MB) 0.95; p = 6, 2 and 4, 11^3 (11 MB)
+// 14 and 17 against 15 and 18, 14^3 (23 MB) 25 against 22.
+constexpr int cached_factors_mb(int Q, int elem_bytes) { return elem_bytes == 8 ? (Q == 5 ? 32 : 0) : Q == 6 ? 64 : Q == 7 ? 16 : 0; }
+constexpr bool cached_factors(int Q, int elem_bytes, int64_t nelem)
+{
+    return nelem * (Q * Q * Q * kQdDiff * elem_bytes) <= (int64_t)cached_factors_mb(Q, elem_bytes) << 20;
+}
+constexpr int64_t kFewElements = 256;  // at most an element a compute unit
+// Whether k_mline takes a launch of nvec vectors in chunks of variant v (else k_apply), by the row length, the size of the
+// stored factors and the chunks:
+// - rows as above (with more than 14 vectors in 8s from rows of one on, at p = 4 of two), and sizes;
+// - k_apply works through the chunks of an element in turn, k_mline's are groups of their own: with few elements they fill
+//   the chip (p = 7, 64 elements, 12 vectors 22 us, 12);
+// - chunks of less than 64 bytes a node update half a line at a time, which k_apply avoids by staging two chunks where two
+//   of its groups fit a CU.  Several such chunks stay with k_mline in FP32 where its stages are that much shorter (p = 1
+//   and p >= 6, 9 to 48 vectors: 0.35 to 1.0 of k_apply's time; p = 2: 0.6 to 0.98, but 16, 32, 48 up to 1.17 at 3e4 nodes),
+//   and at p = 3 .. 5 where their number is odd, so that k_apply's last run is half empty, and the last is full (24 and 40
+//   vectors 0.80 to 0.98; 16, 32 and 48 1.05 to 1.37, 9 to 12 up to 1.29, 22 up to 1.19).  In FP64 (p = 7, 8) they leave:
+//   12 vectors gained 10% at 1.2e6 nodes and lost up to 15% below, the other counts lose everywhere.
+constexpr bool mline_serves(int P, int Q, int mode, bool colloc, int elem_bytes, int v, int nvec, int nex, int64_t nelem)
 {
     if (!mline_variant(mode, colloc, v)) return false;
-    const int vc = variant_vc(v), chunks = (nvec + vc - 1) / vc, last = nvec - (chunks - 1) * vc;
-    if (vc * elem_bytes >= 64 || chunks == 1 || apply_lds(P, Q, mode, elem_bytes, v, true) > kLdsTwoGroups) return true;
-    return chunks == 3 && (2 * last >= vc || (elem_bytes == 4 && (Q < 4 || Q > 6)));
+    const int vc = variant_vc(v), chunks = (nvec + vc - 1) / vc;
+    const bool f32 = elem_bytes == 4;
+    const int rows = v == 6                ? (nvec == 3 ? kMlineRows3 : kMlineRows4)[Q - 2]
+                     : nvec > 14 && Q >= 4 ? (Q == 5 ? 2 : 1)
+                                           : (f32 ? kMlineRows8f32 : kMlineRows8)[Q - 2];
+    if (nex < rows) return false;
+    if (chunks == 1 && (!cached_factors(Q, elem_bytes, nelem) || (f32 ? nvec != 4 : v != 7 || nvec < 8))) return true;
+    if (vc * elem_bytes >= 64) return nvec > 12 || !cached_factors(Q, elem_bytes, nelem);
+    if (chunks == 1) return false;
+    if (nelem <= kFewElements) return true;
+    if (f32) return Q == 2 || Q > 6 || (Q == 3 ? nvec % 16 != 0 : nvec % 16 == 8);
+    return apply_lds(P, Q, mode, elem_bytes, v, true) > kLdsTwoGroups;
 }
 
 // Single-vector launch defaults of the line-fused kernel per q (index q-2).  Measured time of every
@@ -290,8 +326,7 @@ constexpr int kLineCost32Diff[9][5] = {{103, 100, 102, 156, 276}, {103, 100, 102
 constexpr int kLineCost32Coll[9][5] = {{106, 100, 130, 102, 223}, {102, 100, 100, 135, 226}, {113, 100, 112, 150, 258},
                                        {107, 100, 142, 116, 234}, {100, 114, 107, 220, 158}, {100, 183, 139, 113, 121},
                                        {127, 157, 100, 107, 157}, {100, 136, 107, 136, 100}, {113, 159, 100, 113, 100}};
-// FP32 diffusion on meshes of at most one element a compute unit, which take a launch's time (12 us) in any slot.
-constexpr int64_t kFewElements = 256;
+// FP32 diffusion on meshes of at most kFewElements, which take a launch's time (12 us) in any slot.
 constexpr int kLineSlot32Gauss[9] = {0, 0, 0, 0, 0, 0, 0, 0, 2};
 constexpr int kLineSlot32Coll[9] = {0, 1, 0, 1, 0, 3, 2, 2, 2};
 // One-vector diffusion where the stored-factor kernel (k_apply) is faster than k_line: rows of at most `rows` elements,
