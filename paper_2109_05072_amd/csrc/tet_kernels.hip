@@ -107,10 +107,11 @@ __global__ void k_tet_factors(int nex, int ney, int64_t nelem, const double *__r
     for (int f = 0; f < 6; ++f) fac[6 * e + f] = M[f];
 }
 
-// Node slot i of the box: coordinates (bx, by, bz) in [0, 8p] x [0, p] x [0, p].
-template <int p>
+// Node slot i of the box: coordinates (bx, by, bz) in [0, 8p] x [0, p] x [0, p], or (ALONG_Y: its hexahedra consecutive in
+// y, for rows that would fill a quarter of it at most) [0, p] x [0, 8p] x [0, p].
+template <int p, bool ALONG_Y>
 struct Box {
-    static constexpr int BX = kCubes * p + 1, BY = p + 1, NB = BX * BY * BY;
+    static constexpr int L = kCubes * p + 1, BX = ALONG_Y ? p + 1 : L, BY = ALONG_Y ? L : p + 1, NB = BX * BY * (p + 1);
     __device__ static __forceinline__ void coords(int i, int &bx, int &by, int &bz)
     {
         bx = i % BX;
@@ -120,7 +121,7 @@ struct Box {
 };
 
 // Box position of basis function n of column j (tetrahedron j % 6 of hexahedron j / 6).
-template <int p>
+template <int p, bool ALONG_Y>
 __device__ __forceinline__ int box_node(int j, const int32_t *__restrict__ lattice, int n)
 {
     int a0, a1, a2;
@@ -131,16 +132,18 @@ __device__ __forceinline__ int box_node(int j, const int32_t *__restrict__ latti
     int a[3] = {n3, n3, n3};
     a[a0] += n1 + n2;
     a[a1] += n2;
-    return (j / 6) * p + a[0] + Box<p>::BX * (a[1] + Box<p>::BY * a[2]);
+    a[ALONG_Y ? 1 : 0] += (j / 6) * p;
+    using B = Box<p, ALONG_Y>;
+    return a[0] + B::BX * (a[1] + B::BY * a[2]);
 }
 
-template <int p>
+template <int p, bool ALONG_Y>
 __global__ void __launch_bounds__(set_threads * tet_sets(p))
 k_tet_apply(const int ngx, const int nex, const int ney, const int nez, const int dirichlet, const int per,
             const int32_t *__restrict__ lattice, const double *__restrict__ frag, const double *__restrict__ fac,
             const double *__restrict__ x, double *__restrict__ y)
 {
-    using B = Box<p>;
+    using B = Box<p, ALONG_Y>;
     constexpr int P = n_basis(p), T = tet_tiles(p), NS = round_up(P, 4) / 4, NT = round_up(P, 16) / 16;
     constexpr int FT = tet_tile_doubles(p), SETS = tet_sets(p), NTH = set_threads * SETS;
     constexpr bool STREAM = tet_stream(p);
@@ -160,14 +163,14 @@ k_tet_apply(const int ngx, const int nex, const int ney, const int nez, const in
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
         const int n = 4 * s + kq;
-        const uint32_t v = n < P ? (uint32_t)box_node<p>(16 * wave + el, lattice, n) : 65535u;
+        const uint32_t v = n < P ? (uint32_t)box_node<p, ALONG_Y>(16 * wave + el, lattice, n) : 65535u;
         if (s & 1) xa[s / 2] |= v << 16;
         else xa[s / 2] = v;
     }
 #pragma unroll
     for (int i = 0; i < NT * 4; ++i) {
         const int n = 16 * (i / 4) + el, j = 16 * wave + 4 * (i % 4) + kq;
-        const uint32_t v = n < P ? (uint32_t)box_node<p>(j, lattice, n) : 65535u;
+        const uint32_t v = n < P ? (uint32_t)box_node<p, ALONG_Y>(j, lattice, n) : 65535u;
         if (i & 1) ya[i / 2] |= v << 16;
         else ya[i / 2] = v;
     }
@@ -177,7 +180,8 @@ k_tet_apply(const int ngx, const int nex, const int ney, const int nez, const in
     };
 
     const int nx = p * nex + 1, ny = p * ney + 1, nz = p * nez + 1;
-    const int64_t nsteps = (int64_t)ngx * ney * nez;
+    const int ngy = ALONG_Y ? (ney + kCubes - 1) / kCubes : ney;
+    const int64_t nsteps = (int64_t)ngx * ngy * nez;
     // contiguous runs of steps, y fastest (neighbours in y share the largest faces)
     const int64_t first = (xcd_remap(blockIdx.x, gridDim.x) * SETS + set) * per;
     struct Step {
@@ -190,16 +194,17 @@ k_tet_apply(const int ngx, const int nex, const int ney, const int nez, const in
         const int64_t s = first + i;
         q.on = i < per && s < nsteps;
         const unsigned u = (unsigned)(q.on ? s : 0);
-        q.ey = (int)(u % (unsigned)ney);
-        const unsigned v = u / (unsigned)ney;
+        const int gy = (int)(u % (unsigned)ngy);
+        const unsigned v = u / (unsigned)ngy;
         const int gx = (int)(v % (unsigned)ngx);
         q.ez = (int)(v / (unsigned)ngx);
-        q.cx = gx * kCubes;
-        const int nc = nex - q.cx < kCubes ? nex - q.cx : kCubes;
+        q.cx = ALONG_Y ? gx : gx * kCubes;
+        q.ey = ALONG_Y ? gy * kCubes : gy;
+        const int left = ALONG_Y ? ney - q.ey : nex - q.cx, nc = left < kCubes ? left : kCubes;
         q.ncols = 6 * nc;
         q.node = (int64_t)p * (q.cx + (int64_t)nx * (q.ey + (int64_t)ny * q.ez));
         q.elem = 6 * (q.cx + (int64_t)nex * (q.ey + (int64_t)ney * q.ez));
-        q.edge = nc < kCubes || (dirichlet && (gx == 0 || gx == ngx - 1 || q.ey == 0 || q.ey == ney - 1 || q.ez == 0 ||
+        q.edge = nc < kCubes || (dirichlet && (gx == 0 || gx == ngx - 1 || gy == 0 || gy == ngy - 1 || q.ez == 0 ||
                                                q.ez == nez - 1));
         return q;
     };
@@ -223,7 +228,7 @@ k_tet_apply(const int ngx, const int nex, const int ney, const int nez, const in
             asm volatile("" : "+v"(i));
             B::coords(i, bx, by, bz);
             const int I = p * q.cx + bx, J = p * q.ey + by, K = p * q.ez + bz;
-            ok = ok && I < nx && !(dirichlet && (I == 0 || I == nx - 1 || J == 0 || J == ny - 1 || K == 0 || K == nz - 1));
+            ok = ok && (ALONG_Y ? J < ny : I < nx) && !(dirichlet && (I == 0 || I == nx - 1 || J == 0 || J == ny - 1 || K == 0 || K == nz - 1));
         }
         return ok;
     };
@@ -236,7 +241,7 @@ k_tet_apply(const int ngx, const int nex, const int ney, const int nez, const in
             xs[r] = slot(q, r, off) ? (x + q.node)[off] : 0.0;
         }
         // factors of the set's columns (none past the row's end: those columns' results are dropped)
-        if (q.on && t3 < 3 * q.ncols) fd = reinterpret_cast<const d2 *>(fac + 6 * q.elem)[t3];
+        if (q.on && t3 < 3 * q.ncols) fd = reinterpret_cast<const d2 *>(fac + 6 * q.elem)[ALONG_Y ? t3 / 18 * (int64_t)(18 * nex) + t3 % 18 : t3];
     };
 
     constexpr int RF = (FT + NTH - 1) / NTH;  // streamed fragments: a tile's share of one lane
@@ -350,20 +355,20 @@ k_tet_apply(const int ngx, const int nex, const int ney, const int nez, const in
     }
 }
 
-template <int p>
-hipError_t apply_p(const TetLaunch &a)
+template <int p, bool ALONG_Y>
+hipError_t apply_box(const TetLaunch &a)
 {
     constexpr size_t lds = tet_lds(p);
     static_assert(lds <= 163840, "LDS of a thread group");
-    auto kern = k_tet_apply<p>;
+    auto kern = k_tet_apply<p, ALONG_Y>;
     if (lds > 65536) {
         const hipError_t e =
             hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
     // one resident round of thread groups, each with a contiguous share of the steps
-    const int ngx = (a.nex + kCubes - 1) / kCubes;
-    const int64_t nsteps = (int64_t)ngx * a.ney * a.nez;
+    const int ngx = ALONG_Y ? a.nex : (a.nex + kCubes - 1) / kCubes, ngy = ALONG_Y ? (a.ney + kCubes - 1) / kCubes : a.ney;
+    const int64_t nsteps = (int64_t)ngx * ngy * a.nez;
     static const int resident = [&] {
         int n = 0;
         return hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kern, set_threads * tet_sets(p), lds) == hipSuccess && n > 0
@@ -376,6 +381,15 @@ hipError_t apply_p(const TetLaunch &a)
     hipLaunchKernelGGL(kern, dim3((unsigned)nblk), dim3(set_threads * tet_sets(p)), lds, a.stream, ngx, a.nex, a.ney,
                        a.nez, a.dirichlet, (int)per, a.lattice, a.frag, a.fac, a.x, a.y);
     return hipGetLastError();
+}
+
+// Boxes along x, whose rows of nodes are long, unless the row fills a quarter of one at most and a column of elements
+// fills more: 2e6 nodes, p = 1, 4, 5, 6, rows of one 1346, 459, 491, 628 us along x, of two 1029, 263, 306, 398.
+template <int p>
+hipError_t apply_p(const TetLaunch &a)
+{
+    const int64_t pad = (a.ney + kCubes - 1) / kCubes * kCubes;
+    return 4 * a.nex <= kCubes && pad * a.nex < (int64_t)kCubes * a.ney ? apply_box<p, true>(a) : apply_box<p, false>(a);
 }
 
 }  // namespace
