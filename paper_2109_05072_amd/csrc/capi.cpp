@@ -170,7 +170,7 @@ bool valid_variant(const mfhex_op_s &op, int prec, int variant)
     return apply_lds(op.P, op.Q, mode_of(op), prec == MFHEX_F32 ? 4 : 8, shape) <= kMaxLds;
 }
 
-int default_variant(const mfhex_op_s &op, int prec, int nvec)
+int default_variant(const mfhex_op_s &op, int prec, int nvec, bool det)
 {
     // one vector: the measured single-vector best for this operator and q;
     // several: for the chunks of k_apply and k_mass the largest that fits the
@@ -205,7 +205,7 @@ int default_variant(const mfhex_op_s &op, int prec, int nvec)
         return mode == kMass || coll || otf ? slot : 9 + slot;
     }
     const int eb = prec == MFHEX_F32 ? 4 : 8;
-    if (!op.ebuf && !op.d.variable_kappa) {
+    if (!det && !op.d.variable_kappa) {
         // Collocated diffusion: k_mline where it serves the launch (mline_serves), in 8s from five vectors on (3e6 nodes,
         // FP64, p = 3, 6: 5 vectors 238, 218 us in an 8 and 300, 296 in 4s; 4 vectors 239, 200 and 148, 139), in 4s where
         // an 8 does not fit.  Two vectors are faster as a pair: FP64 from q = 5 on (p = 4, 5, 7: 127, 114, 98 against 142,
@@ -248,12 +248,12 @@ int pipeline_depth(const mfhex_op_s &op, int nvec, const LaunchCfg &c)
     return line_march(kDefChainLineMass[op.Q - 2], op.d.ney, columns, line_nt(op.Q, G));
 }
 
-LaunchCfg config_for(const mfhex_op_s &op, int prec, int nvec)
+LaunchCfg config_for(const mfhex_op_s &op, int prec, int nvec, bool det)
 {
     auto it = op.config.find({prec, nvec});
     if (it != op.config.end()) return it->second;
     LaunchCfg c;
-    c.variant = default_variant(op, prec, nvec);
+    c.variant = default_variant(op, prec, nvec, det);
     return c;
 }
 
@@ -337,7 +337,7 @@ int apply_impl(mfhex_op op, int prec, int nrhs, const void *x, void *y, hipStrea
     void *const ebuf = ebuf_in ? ebuf_in : op->ebuf;
     if (ebuf && nrhs != 1)
         return set_error(op, MFHEX_ERR_UNSUPPORTED, "deterministic operators apply one right-hand side at a time");
-    const LaunchCfg cfg = variant >= 0 ? LaunchCfg{variant, chain} : config_for(*op, prec, nvec);
+    const LaunchCfg cfg = variant >= 0 ? LaunchCfg{variant, chain} : config_for(*op, prec, nvec, ebuf != nullptr);
     if (!valid_variant(*op, prec, cfg.variant)) return set_error(op, MFHEX_ERR_ARG, "invalid launch variant");
     if (cfg.chain < 0 || cfg.chain > kMaxChain || (cfg.chain > 1 && mode_of(*op) != kMass))
         return set_error(op, MFHEX_ERR_ARG, "invalid pipeline depth");
@@ -656,7 +656,7 @@ int mfhex_get_config(mfhex_op op, int prec, int nrhs, int32_t *variant, int32_t 
                      int32_t *threads_per_group, int32_t *groups_per_block)
 {
     if (!op || nrhs < 1) return fail(MFHEX_ERR_ARG, "bad argument");
-    const LaunchCfg c = config_for(*op, prec, nrhs * op->d.ncomp);
+    const LaunchCfg c = config_for(*op, prec, nrhs * op->d.ncomp, op->ebuf != nullptr);
     if (variant) *variant = c.variant;
     const bool line = line_variant(op->Q, mode_of(*op), op->basis.colloc, (op->d.flags & MFHEX_FLAG_OTF) != 0, c.variant);
     const int shape = elem_shape(op->Q, mode_of(*op), op->basis.colloc, (op->d.flags & MFHEX_FLAG_OTF) != 0, c.variant);

@@ -61,9 +61,9 @@ int check_hip(mfhex_op op, hipError_t e, const char *what);
 // then summed per node in a fixed order), in place of the operator's own.
 int apply_impl(mfhex_op op, int prec, int nrhs, const void *x, void *y, hipStream_t s, bool zero, int variant = -1,
                int chain = 0, void *ebuf = nullptr);
-int default_variant(const mfhex_op_s &op, int prec, int nvec);
+int default_variant(const mfhex_op_s &op, int prec, int nvec, bool det);  // det: element values into a buffer
 bool valid_variant(const mfhex_op_s &op, int prec, int variant);
-LaunchCfg config_for(const mfhex_op_s &op, int prec, int nvec);
+LaunchCfg config_for(const mfhex_op_s &op, int prec, int nvec, bool det);
 // diag(M A M) (FP64, masked nodes 0) into d [N].
 int diagonal_impl(mfhex_op op, double *d, hipStream_t s);
 int pipeline_depth(const mfhex_op_s &op, int nvec, const LaunchCfg &c);

@@ -109,7 +109,7 @@ int tune(mfhex_op op, int prec, int nrhs, void *scratch, const char *cache_path,
         if ((c = check_hip(op, launch_copy(x64, MFHEX_F64, ytest, MFHEX_F32, len, s), "copy kernel"))) return cleanup(c);
         if ((c = check_hip(op, hipMemcpyAsync(x64, ytest, len * es, hipMemcpyDeviceToDevice, s), "copy"))) return cleanup(c);
     }
-    const int def = default_variant(*op, prec, nvec);
+    const int def = default_variant(*op, prec, nvec, op->ebuf != nullptr);
     if ((c = apply_impl(op, prec, nrhs, x, yref, s, true, def, 0))) return cleanup(c);
     // the default launch first: it stays unless another is faster; then every variant with the automatic depth and
     // (mass) the others, each launch once

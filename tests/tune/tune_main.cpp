@@ -34,7 +34,7 @@ int set_error(mfhex_op, int code, const std::string &) { return code; }
 int check_hip(mfhex_op, hipError_t e, const char *) { return e == hipSuccess ? MFHEX_OK : MFHEX_ERR_HIP; }
 int mode_of(const mfhex_op_s &op) { return op.d.kind == MFHEX_DIFFUSION ? kDiff : kMass; }
 bool valid_variant(const mfhex_op_s &, int, int v) { return v >= 0 && v < kNumVariants && g_valid({v, 0}); }
-int default_variant(const mfhex_op_s &, int, int) { return g_default; }
+int default_variant(const mfhex_op_s &, int, int, bool) { return g_default; }
 int pipeline_depth(const mfhex_op_s &op, int, const LaunchCfg &c) { return mode_of(op) != kMass ? 1 : c.chain > 0 ? c.chain : 8; }
 hipError_t launch_fill_uniform(double *, int64_t, uint64_t, hipStream_t) { return hipSuccess; }
 hipError_t launch_copy(const void *, int, void *, int, int64_t, hipStream_t) { return hipSuccess; }
