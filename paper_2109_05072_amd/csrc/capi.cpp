@@ -193,11 +193,15 @@ int default_variant(const mfhex_op_s &op, int prec, int nvec, bool det)
             const int64_t bytes = op.NQ * kQdDiff * (f32 ? 4 : 8);
             if ((op.d.nex <= r.rows || bytes <= ((int64_t)r.mb << 20)) && valid_variant(op, prec, v)) return v;
         }
+        // few elements, each more lines than a wavefront has lanes (q >= 9): groups of one, the shortest chain of stages
+        // (p = 8, 2^3 to 6^3 elements 13.0 .. 13.9 us in groups of two, 12.2 .. 13.4 in groups of one)
+        const bool alone = mode == kDiff && !f32 && op.Q >= 9 && op.E <= kFewElements;
         int slot = few ? (coll ? kLineSlot32Coll : kLineSlot32Gauss)[op.Q - 2] : 0;
         int64_t best = INT64_MAX;
         for (int i = 0; i < 5 && !few; ++i) {
             if (i == elem) continue;
             const int G = kLineG[op.Q - 2][i];
+            if (alone && G > 1) continue;
             const int64_t idle = (int64_t)(op.d.nex + G - 1) / G * G - op.d.nex;
             const int64_t t = table[op.Q - 2][i] * (100 * (int64_t)op.d.nex + (f32 ? kIdle32Percent : 100) * idle);
             if (t < best) best = t, slot = i;

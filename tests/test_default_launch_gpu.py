@@ -64,3 +64,17 @@ def test_factors_in_the_kernel_elsewhere(gpu_lib, p, quad, dtype, ne):
     v = op.get_config(dtype)[0]
     print(p, quad, dtype, ne, op.get_config(dtype), flush=True)
     assert 9 <= v <= 13 if quad == "gauss" else v < 5 and v != {1: 3, 3: 2, 8: 4}[p]
+
+
+@pytest.mark.parametrize("p,option", [(8, ""), (8, "vark"), (8, "otf"), (8, "det"), (7, "det")])
+@pytest.mark.parametrize("ne", [(2, 2, 2), (4, 4, 4), (6, 6, 7)])
+def test_few_large_elements_run_alone(gpu_lib, p, option, ne):
+    # at most 256 elements of 81 or 100 lines: groups of one element
+    op, pr = build(gpu_lib, *ne, p, "diffusion", "gauss", True, vark=option == "vark", otf=option == "otf", det=option == "det")
+    print(p, option, ne, op.get_config(), flush=True)
+    assert op.get_config()[1] == 1
+    if option == "vark":
+        op.set_kappa(torch.ones(op.n_elem, op.q ** 3, dtype=torch.float64, device="cuda"))
+    x = synth.uniform_vector(pr.n_nodes)
+    if max(ne) < 5:
+        assert relerr(host(op.apply(dev(x))), oracle.apply(pr, x)) <= TOL64
