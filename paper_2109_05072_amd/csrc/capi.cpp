@@ -187,11 +187,9 @@ int default_variant(const mfhex_op_s &op, int prec, int nvec, bool det)
                             : coll        ? (f32 ? kLineCost32Coll : kLineCostColl)
                                           : (f32 ? kLineCost32Diff : kLineCostDiff);
         const int elem = elem_slot(op.Q, mode, coll, otf);
-        if (mode == kDiff && !otf && !few) {
-            const ElemRange r = coll ? (f32 ? kElemColl32 : kElemColl)[op.Q - 2] : f32 ? kElemGauss32[op.Q - 2] : ElemRange{};
-            const int v = coll ? elem : kElemGauss32Variant[op.Q - 2];
-            const int64_t bytes = op.NQ * kQdDiff * (f32 ? 4 : 8);
-            if ((op.d.nex <= r.rows || bytes <= ((int64_t)r.mb << 20)) && valid_variant(op, prec, v)) return v;
+        if (elem >= 0 && !f32) {
+            const ElemRange r = kElemColl[op.Q - 2];
+            if (op.d.nex <= r.rows || op.NQ * kQdDiff * 8 <= (int64_t)r.mb << 20) return elem;
         }
         // few elements, each more lines than a wavefront has lanes (q >= 9): groups of one, the shortest chain of stages
         // (p = 8, 2^3 to 6^3 elements 13.0 .. 13.9 us in groups of two, 12.2 .. 13.4 in groups of one)

@@ -179,7 +179,7 @@ constexpr int line_march(int most, int ney, int64_t columns, int nt)
 constexpr int line_slot(int v) { return v < 5 ? v : v == 14 ? 0 : v - 9; }
 // Collocated diffusion, of the numbers 0 .. 4 the one that is the element-at-a-time kernel with stored factors instead
 // (k_apply, in the shape of kElemShape; elem_slot, -1: none), at the q where it is the faster one somewhere (kElemColl).
-constexpr int kElemSlotColl[9] = {3, -1, 2, -1, -1, -1, -1, 4, -1};
+constexpr int kElemSlotColl[9] = {3, -1, -1, -1, -1, -1, -1, 4, -1};
 constexpr int kElemShape[9] = {0, 0, 0, 4, 4, 4, 0, 4, 3};
 constexpr int elem_slot(int Q, int mode, bool colloc, bool otf) { return mode == 1 && colloc && !otf ? kElemSlotColl[Q - 2] : -1; }
 // The variant whose group shape (variant_g, variant_nt below) an element-at-a-time launch takes.
@@ -329,23 +329,18 @@ constexpr int kLineCost32Coll[9][5] = {{106, 100, 130, 102, 223}, {102, 100, 100
 // FP32 diffusion on meshes of at most kFewElements, which take a launch's time (12 us) in any slot.
 constexpr int kLineSlot32Gauss[9] = {0, 0, 0, 0, 0, 0, 0, 0, 2};
 constexpr int kLineSlot32Coll[9] = {0, 1, 0, 1, 0, 3, 2, 2, 2};
-// One-vector diffusion where the stored-factor kernel (k_apply) is faster than k_line: rows of at most `rows` elements,
-// which waste the lanes of its groups least, and meshes whose stored factors take at most mb MB, which the 256 MB Infinity
-// Cache (all or most of them) feeds.  us of k_apply and of k_line's best slot:
-//   collocated p = 1: FP32, rows of 1, 4, 9, 13 at 2e6 nodes 332 447, 161 239, 134 169, 132 151 (17: 218 189), 66^3 elements
-//     (55 MB) 24 32, 99^3 72 79, 214^3 692 658; FP64, rows of 1, 4, 9, 13 509 572, 260 298, 180 187, 172 168, 66^3 30 33,
-//     99^3 93 88, 214^3 948 747
-//   collocated p = 3, FP32: rows of 1 .. 4 55 58, 37 48, 31 40, 29 36 (5: 38 39); 48^3 54 45
-//   collocated p = 8, rows of one: FP32 25 34, FP64 with a coefficient 42 45, without 40 40 (rows of two 48 35)
-//   Gauss, FP32: p = 2, rows of 1, 2, 4 148 165, 99 109, 66 77, 33^3 elements (55 MB) 15 19, 49^3 41 46, 72^3 (573 MB) 121
-//     118, 107^3 401 353; p = 7 and 8, rows of one 31 40 and 32 42 (two 34 36, 37 37)
+// One-vector collocated diffusion in FP64 where the stored-factor kernel (k_apply) is faster than k_line: rows of at most
+// `rows` elements, which waste the lanes of its groups least, and meshes whose stored factors take at most mb MB, which the
+// 256 MB Infinity Cache feeds.  us of k_apply and of k_line's best slot: p = 1, rows of 1, 4, 9, 13 at 2e6 nodes 509 572,
+// 260 298, 180 187, 172 168, 66^3 elements (110 MB) 30 33, 99^3 (373 MB) 93 88, 214^3 948 747; p = 8, rows of one with a
+// coefficient 42 45, without 40 40 (rows of two 48 35).
+// FP32 launches evaluate their factors in FP64 everywhere, for half the error (1.6e-7 against 2.9e-7 at p = 3), also where
+// factors stored in FP32 would be faster: collocated p = 1, 66^3 elements 32 us against 24, rows of 4 239 against 161; p = 3,
+// rows of 4 36, 29; Gauss p = 2, 33^3 and 72^3 19, 118 against 15, 121; p = 7, rows of one 40, 31.
 struct ElemRange {
     int rows, mb;
 };
 constexpr ElemRange kElemColl[9] = {{9, 256}, {}, {}, {}, {}, {}, {}, {1, 0}, {}};
-constexpr ElemRange kElemColl32[9] = {{13, 256}, {}, {4, 0}, {}, {}, {}, {}, {1, 0}, {}};
-constexpr ElemRange kElemGauss32[9] = {{}, {}, {4, 512}, {}, {}, {}, {}, {1, 0}, {1, 0}};
-constexpr int kElemGauss32Variant[9] = {0, 0, 0, 0, 0, 0, 0, 3, 3};
 // Mass, k_line: largest automatic pipeline depth (elements a group marches through).
 constexpr int kDefChainLineMass[9] = {8, 8, 8, 8, 4, 2, 4, 4, 2};
 // k_mass (collocated, and several vectors with Gauss points): the collocated one-vector variant, and the depth.  With

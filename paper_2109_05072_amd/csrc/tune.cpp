@@ -47,7 +47,7 @@ std::string arch_name(int device)
 // comes to stand for another kernel); whether the operator evaluates its factors (a number is another kernel then), is
 // deterministic or has a coefficient; the row length, to an eighth of an octave, on which the idle lanes of a group
 // depend; and the octave of the element count, on which the best depth does.
-constexpr int kVariantNumbers = 4;
+constexpr int kVariantNumbers = 5;
 std::string cache_key(const mfhex_op_s &op)
 {
     int octave = 0, size = 0;
