@@ -501,12 +501,11 @@ int mfhex_create(const mfhex_desc *d, void *workspace_dev, size_t workspace_byte
             h[basis_wq(P, Q) + a] = b.wq[a];
         }
         {
-            // the basis derivative at the points, G[a][i] = l_i'(x_a), and its transpose, folded
-            std::vector<double> g(Q * P), gt(P * Q);
+            // the basis derivative at the points, G[a][i] = l_i'(x_a), folded
+            std::vector<double> g(Q * P);
             for (int a = 0; a < Q; ++a)
-                for (int i = 0; i < P; ++i) g[a * P + i] = gt[i * Q + a] = b.Gn[a * P + i];
+                for (int i = 0; i < P; ++i) g[a * P + i] = b.Gn[a * P + i];
             fold(g.data(), Q, P, &h[basis_gf(P, Q)]);
-            fold(gt.data(), P, Q, &h[basis_gtf(P, Q)]);
         }
         for (size_t i = 0; i < h.size(); ++i) h32[i] = (float)h[i];
         if ((c = check_hip(op, hipMemcpy(op->basis64, h.data(), h.size() * sizeof(double), hipMemcpyHostToDevice),
@@ -580,7 +579,7 @@ int mfhex_kappa_grad(mfhex_op op, const double *u_dev, const double *r_dev, doub
     if (!op) return fail(MFHEX_ERR_ARG, "null handle");
     if (op->d.kind != MFHEX_DIFFUSION) return set_error(op, MFHEX_ERR_STATE, "coefficient gradient needs a diffusion operator");
     if (op->d.ncomp != 1) return set_error(op, MFHEX_ERR_UNSUPPORTED, "coefficient gradient needs ncomp = 1");
-    if (!op->q64) return set_error(op, MFHEX_ERR_UNSUPPORTED, "coefficient gradient needs stored geometric factors");
+    if (!op->q64) return set_error(op, MFHEX_ERR_UNSUPPORTED, "coefficient gradient is not available with MFHEX_FLAG_OTF");
     if (!u_dev || !r_dev || !g_dev) return set_error(op, MFHEX_ERR_ARG, "null vector");
     KgradLaunch a{};
     a.v = view_of(*op, MFHEX_F64);

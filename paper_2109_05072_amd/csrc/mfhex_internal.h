@@ -117,10 +117,11 @@ constexpr bool split_stages(int Q, int mode, int G, int NT, int VC)
 
 // Launch variants of the fused kernels for q points per direction: G elements per thread group of NT
 // threads.  Which kernel a number stands for depends on the operator (line_variant below): the line-fused
-// kernel takes 9 .. 14 of diffusion with Gauss points, and 0 .. 4 of collocated or in-kernel-factor
+// kernel takes 9 .. 14 of diffusion with Gauss points, and 0 .. 4 of collocated (but elem_slot) or in-kernel-factor
 // diffusion and of mass with Gauss points.  Variants 0 .. 4 of the other operators carry one vector at a
 // time through the element with stored factors (rows: Q = 2 .. 10); 5 .. 8 carry a chunk of VC = 2, 4, 8,
-// 16 vectors of a multi-vector together (one element per group), sharing the geometric factors and reading
+// 16 vectors of a multi-vector together (one element per group; 6 and 7 of collocated diffusion in k_mline where
+// mline_serves says so), sharing the geometric factors and reading
 // / writing each node's chunk as one contiguous run; 15 and 16 are chunks of 4 and 8 vectors whose
 // collocated gradient contractions run on the FP64 matrix cores.
 constexpr int kNumVariants = 17;
@@ -362,10 +363,10 @@ constexpr int basis_df(int P, int Q) { return basis_btf(P, Q) + half_up(P) * Q; 
 constexpr int basis_dtf(int P, int Q) { return basis_df(P, Q) + half_up(Q) * Q; }
 constexpr int basis_xq(int P, int Q) { return basis_dtf(P, Q) + half_up(Q) * Q; }  // quadrature points [Q]
 constexpr int basis_wq(int P, int Q) { return basis_xq(P, Q) + Q; }                  // quadrature weights [Q]
-// folded G [Q][P] (G[a][i] = l_i'(x_a), the basis derivative at the points) and folded G^T [P][Q]
+// folded G [Q][P] (G[a][i] = l_i'(x_a), the basis derivative at the points); the block ends in half_up(P) * Q elements
+// that nothing uses, which keep the workspace sizes that callers have been told
 constexpr int basis_gf(int P, int Q) { return basis_wq(P, Q) + Q; }
-constexpr int basis_gtf(int P, int Q) { return basis_gf(P, Q) + half_up(Q) * P; }
-constexpr int basis_len(int P, int Q) { return basis_gtf(P, Q) + half_up(P) * Q; }
+constexpr int basis_len(int P, int Q) { return basis_gf(P, Q) + half_up(Q) * P + half_up(P) * Q; }
 
 // Per-order dispatch (one translation unit per order, apply_p<N>.hip).
 hipError_t launch_apply(const ApplyLaunch &a);
