@@ -94,10 +94,12 @@ enum { MFHEX_PRECOND_NONE = 0, MFHEX_PRECOND_JACOBI = 1, MFHEX_PRECOND_MG = 2 };
  *   coordinates, x fastest; each hexahedron is the trilinear image of
  *   [-1,1]^3 through its 8 vertices.  Copied into the workspace by create.
  * Unless MFHEX_FLAG_OTF drops it, create stores the six factors per point;
- * the multi-vector launches, the coefficient gradient, the diagonal and the
- * stored-factor launch variants read them.  The default single-vector launch
- * evaluates the factors from the trilinear map instead (equal up to
- * rounding; mfhex_set_config). */
+ * the multi-vector launches, the diagonal, the stored-factor launch variants
+ * and, with Gauss-Lobatto points in FP64, the default single-vector launch of
+ * p = 1 (rows of at most 9 elements, or at most 256 MB of factors) and of
+ * p = 8 (rows of one) read them.  The other single-vector defaults and the
+ * coefficient gradient evaluate the factors from the trilinear map, in FP64
+ * (equal up to rounding; mfhex_set_config). */
 typedef struct {
     int32_t nex, ney, nez;
     int32_t p, q, quad, kind, ncomp, dirichlet, variable_kappa;
@@ -188,8 +190,8 @@ size_t mfhex_apply_static_max_bytes(void);
  * Sec. 2, s is linear in each kappa_pt, and its derivative is the pointwise
  * product below): g[e][pt] = (Dhat M r)_pt^T G0_pt (Dhat M u)_pt, G0 the
  * kappa-free geometric factors.  u, r: device FP64 [n_nodes] (ncomp = 1);
- * g: device FP64 [n_elem][q^3], overwritten.  Diffusion operators with
- * stored geometric factors only (MFHEX_ERR_UNSUPPORTED with MFHEX_FLAG_OTF).
+ * g: device FP64 [n_elem][q^3], overwritten.  Diffusion operators
+ * without MFHEX_FLAG_OTF only (MFHEX_ERR_UNSUPPORTED with it).
  * For a loss L(y), r = dL/dy gives dL/dkappa.  Asynchronous. */
 int mfhex_kappa_grad(mfhex_op op, const double *u_dev, const double *r_dev, double *g_dev, void *stream);
 
@@ -334,11 +336,14 @@ int mfhex_get_config(mfhex_op op, int prec, int nrhs, int32_t *variant, int32_t 
                      int32_t *threads_per_group, int32_t *groups_per_block);
 
 /* Force the launch configuration for (prec, nrhs): variant 0 .. 16 (5 .. 8
- * carry 2, 4, 8, 16 vectors of a multi-vector together; 9 .. 14 for diffusion
+ * carry 2, 4, 8, 16 vectors of a multi-vector together, 6 and 7 of collocated
+ * diffusion in the line-fused multi-vector kernel where it is the faster one
+ * for the mesh and the vectors; 9 .. 14 for diffusion
  * with Gauss points, and 0 .. 4 for collocated or OTF diffusion and for mass
  * with Gauss points, are the line-fused kernel, which evaluates the factors
- * from the element's trilinear map; 0 .. 4 of diffusion with Gauss points
- * read the stored factors; 15 and 16 carry 4 and 8 vectors with the gradient
+ * from the element's trilinear map; 0 .. 4 of diffusion with Gauss points,
+ * and 3 (p = 1) and 4 (p = 8) of the collocated one without OTF, read the
+ * stored factors; 15 and 16 carry 4 and 8 vectors with the gradient
  * contractions on the FP64 matrix cores, collocated FP64 diffusion only) and
  * pipeline depth
  * groups_per_block (0: the operator's default, which for mass is measured per
@@ -365,9 +370,11 @@ int mfhex_basis_1d(int p, int q, int quad, double *nodes, double *xq, double *wq
  * is applied through its full matrices, the gradient matrix of one element
  * (all quadrature points by all basis functions) times one column per
  * element, i.e. one matrix product for all elements (batched along the
- * elements).  Here 16 elements at a time go through the FP64 matrix cores,
- * with the pointwise 3x3 factor applied to the products in registers and
- * the transposed product back to the nodes in the same kernel.
+ * elements).  Here the 48 tetrahedra of 8 hexahedra go through the FP64
+ * matrix cores together (three tiles of 16 columns), their gradients as
+ * coefficients in an orthonormal basis of P_{p-1}, with the 3x3 factor of the
+ * affine element applied to the products in registers and the transposed
+ * product back to the nodes in the same kernel.
  *
  * Mesh: the structured box of mfhex_desc (same vertex array, x fastest),
  * every hexahedron split into the 6 Kuhn tetrahedra around its main
@@ -398,7 +405,7 @@ typedef struct {
 int mfhex_tet_query(const mfhex_tet_desc *d, mfhex_tet_sizes *out);
 
 /* Build the operator in the caller's workspace (basis-gradient fragments,
- * element restriction, per-point factors w |det J| J^-1 J^-T).  Synchronizes
+ * per-element factors |det J| J^-1 J^-T).  Synchronizes
  * `stream`; ERR_MESH for a degenerate tetrahedron.  The workspace must
  * outlive the handle; the library owns only host metadata. */
 int mfhex_tet_create(const mfhex_tet_desc *d, void *workspace_dev, size_t workspace_bytes, void *stream,

@@ -32,7 +32,7 @@
 // interpolate back.
 //
 // These are the kernels of what the line-fused ones (line_kernels.hpp) don't take: the stored-factor variants of
-// diffusion with Gauss points, multi-vector chunks of collocated diffusion that mline_serves leaves here (or where the
+// diffusion with Gauss points and of collocated diffusion (elem_slot), multi-vector chunks of collocated diffusion that mline_serves leaves here (or where the
 // deterministic scatter is asked for), the matrix-core gradient, collocated mass and the load vector.
 #pragma once
 
@@ -935,7 +935,6 @@ static hipError_t prepare_lds(K kernel, size_t lds)
     return hipSuccess;
 }
 
-// The line-fused kernel.
 // Thread groups of a line-fused kernel: launches of fewer than 2^32 lanes each, the limit of a grid's extent (several
 // vectors of a large mesh exceed it: a chunk has its own groups).
 template <typename K, typename A>

@@ -12,8 +12,8 @@
 //        nodes leave Y^T in registers, straight into the scatter
 // With Gauss-Lobatto points at the nodes B is the identity: Y forms d/ds, X
 // d/dr, Z d/dt, then the same way back.  The mass operator carries one array
-// through the same stages.  Four barriers an element instead of thirteen and
-// 15-17 LDS accesses a point instead of about 26 (Gauss).
+// through the same stages.  Four barriers an element, and a fifth before the next one
+// of a march, instead of thirteen, and 15-17 LDS accesses a point instead of about 26 (Gauss).
 //
 // Pointwise stage: no stored factors.  The map is trilinear, so along a z-line (r, s fixed) the
 // Jacobian columns are j_r, j_s linear in t and j_t constant: a lane forms them
@@ -29,12 +29,12 @@
 // the position in the structured mesh, so no restriction offsets are read.
 //
 // Measured on MI355X, about 1e7 nodes, FP64, us an apply with its output fill, stored-factor kernel
-// (k_apply / k_mass, the best variant) -> this kernel: BP3 p = 1..8 2610 -> 1636, 720 -> 457, 474 -> 285,
-// 383 -> 248, 334 -> 228, 287 -> 194, 294 -> 191, 270 -> 203; BP1 p = 3..8 198 -> 138, 200 -> 122,
-// 152 -> 127, 168 -> 115, 166 -> 119, 160 -> 126.  HBM traffic is within 1.45 of x and y (p = 3: 90 MB
-// read, 135 MB written); the FP64 pipes are busy 61% of the time (p = 3) and bound it: about 109 FP64
+// (k_apply / k_mass, the best variant) -> this kernel: BP3 p = 1..8 2610 -> 1725, 720 -> 446, 474 -> 258,
+// 383 -> 232, 334 -> 208, 287 -> 178, 294 -> 183, 270 -> 198; BP1 p = 3..8 198 -> 143, 200 -> 127,
+// 152 -> 127, 168 -> 118, 166 -> 124, 160 -> 129.  HBM traffic is within 1.45 of x and y (p = 3: 90 MB
+// read, 135 MB written); the vector units are busy 63% of the time (p = 3) and bound it: about 109 FP64
 // operations a point at p = 3, 55 of them geometry.  (Coefficients read from a table of 168 bytes an
-// element instead of formed from the vertices: 253 us at p = 3; not kept, the workspace has no room.)
+// element instead of formed from the vertices gained nothing: 253 us at p = 3.)
 #pragma once
 
 #include <type_traits>
@@ -704,7 +704,7 @@ k_line(const LineArgs<T> a)
 // nodes 280 -> 193.  The LDS of two groups of 7 wavefronts fills a CU at p = 6:
 // 883 us become 694 without the atomics, 577 without the loads as well, and 521
 // without barriers, so that memory and the stages' latency share the time; the
-// vector units are busy for 31% of it.
+// vector units are busy for 35% of it.
 // ---------------------------------------------------------------------------
 
 // The value of lane K of each group of VC lanes (VC = 4: a quad; 8: half a row of 16).
@@ -990,8 +990,8 @@ k_mline(const LineArgs<T> a)
 // p = 6, 327 against 314 at p = 4, 1e7 nodes).
 // Before, one element per wavefront with six LDS arrays and stored factors, and
 // now: Gauss, 1e7 nodes, p = 4 510 -> 314 us, p = 6 434 -> 219; 3e6 nodes,
-// p = 2 370 -> 191, p = 8 154 -> 69.  p = 4 moves 0.43 GB (90 us); the FP64
-// issue is about 190 us of its 314, the rest is the latency of three stages.
+// p = 2 370 -> 191, p = 8 154 -> 69.  p = 4 moves 0.56 GB (107 us); the vector
+// units are busy 56% of the time, the rest is the latency of three stages.
 // ---------------------------------------------------------------------------
 struct KgradArgs {
     const double *bas, *vert, *u, *r;

@@ -4,8 +4,9 @@
 // matrices: the interpolation / gradient matrix of one element (all points by
 // all basis functions) times the element values of every element, one matrix
 // product C = A B with A the basis matrix and B one column per element.  Here
-// the gradient matrices G_d (d = 1..3) multiply 16 elements at a time on the
-// FP64 matrix cores, the pointwise 3x3 factor acts on the products in
+// the matrix of the gradients in an orthonormal basis of P_{p-1} multiplies the
+// 48 tetrahedra of 8 hexahedra (three tiles of 16 columns) on the FP64 matrix
+// cores, the 3x3 factor of the affine element acts on the products in
 // registers, and the transposed products go back to the nodes.
 //
 // Mesh: every hexahedron of the structured box is split into the 6 Kuhn

@@ -70,9 +70,13 @@ def _short(name: str) -> str:
         P, Q, colloc, T, G, NT, VC, det = m.groups()
         vc = f" VC={VC}" if VC != "1" else ""
         return f"k_mass p={int(P) - 1} q={Q} {T} G={G} NT={NT}{vc}{' det' if det == 'true' else ''}"
-    m = re.match(r"void mfhex::tet::\(anonymous namespace\)::k_tet_apply<(\d+)>", name)
+    m = re.match(r"void mfhex::k_kgrad<(\d+), (\d+), (\w+), (\d+), (\d+), (true|false)>", name)
     if m:
-        return f"k_tet_apply p={m.group(1)}"
+        P, Q, colloc, G, NT, stack = m.groups()
+        return f"k_kgrad p={int(P) - 1} q={Q} double G={G} NT={NT}{' stacked' if stack == 'true' else ''}"
+    m = re.match(r"void mfhex::tet::\(anonymous namespace\)::k_tet_apply<(\d+)(?:, (true|false))?>", name)
+    if m:
+        return f"k_tet_apply p={m.group(1)}{' along y' if m.group(2) == 'true' else ''}"
     name = name.replace("(anonymous namespace)::", "").replace("void ", "")
     return name.split("(")[0].split("<")[0].split("::")[-1][:60]
 
