@@ -342,7 +342,7 @@ int mfhex_get_config(mfhex_op op, int prec, int nrhs, int32_t *variant, int32_t 
  * with Gauss points, and 0 .. 4 for collocated or OTF diffusion and for mass
  * with Gauss points, are the line-fused kernel, which evaluates the factors
  * from the element's trilinear map; 0 .. 4 of diffusion with Gauss points,
- * and 3 (p = 1) and 4 (p = 8) of the collocated one without OTF, read the
+ * and 3 (p = 1) and 4 (p = 8) of the collocated one in FP64 without OTF, read the
  * stored factors; 15 and 16 carry 4 and 8 vectors with the gradient
  * contractions on the FP64 matrix cores, collocated FP64 diffusion only) and
  * pipeline depth

@@ -1070,12 +1070,12 @@ static hipError_t launch_element_v(const ApplyLaunch &a)
 template <int P, int Q, bool COLLOC, int MODE, bool VARK, typename T, int V, bool OTF, bool DET>
 static hipError_t launch_apply_v(const ApplyLaunch &a)
 {
-    if constexpr (line_variant(Q, MODE, COLLOC, OTF, V)) return launch_line_v<P, Q, COLLOC, MODE, VARK, T, V, DET>(a);
+    if constexpr (line_variant(Q, MODE, COLLOC, OTF, sizeof(T) == 4, V)) return launch_line_v<P, Q, COLLOC, MODE, VARK, T, V, DET>(a);
     else if constexpr (variant_gf(V) || OTF) return hipErrorInvalidValue;
     else {
         if constexpr (!DET && !VARK && mline_variant(MODE, COLLOC, V) && apply_lds(P, Q, MODE, sizeof(T), V) <= kMaxLds)
             if (mline_serves(P, Q, MODE, COLLOC, sizeof(T), V, a.nvec, a.v.nex, a.v.nelem)) return launch_mline_v<Q, T, V>(a);
-        return launch_element_v<P, Q, COLLOC, MODE, VARK, T, elem_shape(Q, MODE, COLLOC, OTF, V), DET>(a);
+        return launch_element_v<P, Q, COLLOC, MODE, VARK, T, elem_shape(Q, MODE, COLLOC, OTF, sizeof(T) == 4, V), DET>(a);
     }
 }
 

@@ -165,9 +165,10 @@ bool valid_variant(const mfhex_op_s &op, int prec, int variant)
     if (variant_gf(variant) && (mode_of(op) != kDiff || op.basis.colloc || otf)) return false;
     // the matrix-core gradient: collocated FP64 diffusion with stored factors
     if (variant_mx(variant) && (mode_of(op) != kDiff || !op.basis.colloc || otf || prec != MFHEX_F64)) return false;
-    if (line_variant(op.Q, mode_of(op), op.basis.colloc, otf, variant)) return true;
-    const int shape = elem_shape(op.Q, mode_of(op), op.basis.colloc, otf, variant);
-    return apply_lds(op.P, op.Q, mode_of(op), prec == MFHEX_F32 ? 4 : 8, shape) <= kMaxLds;
+    const bool f32 = prec == MFHEX_F32;
+    if (line_variant(op.Q, mode_of(op), op.basis.colloc, otf, f32, variant)) return true;
+    const int shape = elem_shape(op.Q, mode_of(op), op.basis.colloc, otf, f32, variant);
+    return apply_lds(op.P, op.Q, mode_of(op), f32 ? 4 : 8, shape) <= kMaxLds;
 }
 
 int default_variant(const mfhex_op_s &op, int prec, int nvec, bool det)
@@ -186,8 +187,8 @@ int default_variant(const mfhex_op_s &op, int prec, int nvec, bool det)
         const auto &table = mode == kMass ? kLineCostMass
                             : coll        ? (f32 ? kLineCost32Coll : kLineCostColl)
                                           : (f32 ? kLineCost32Diff : kLineCostDiff);
-        const int elem = elem_slot(op.Q, mode, coll, otf);
-        if (elem >= 0 && !f32) {
+        const int elem = elem_slot(op.Q, mode, coll, otf, prec == MFHEX_F32);
+        if (elem >= 0) {
             const ElemRange r = kElemColl[op.Q - 2];
             if (op.d.nex <= r.rows || op.NQ * kQdDiff * 8 <= (int64_t)r.mb << 20) return elem;
         }
@@ -244,7 +245,7 @@ int pipeline_depth(const mfhex_op_s &op, int nvec, const LaunchCfg &c)
 {
     if (mode_of(op) != kMass) return 1;
     if (c.chain > 0) return c.chain;
-    if (!line_variant(op.Q, kMass, op.basis.colloc, false, c.variant)) return kDefChainMass[op.Q - 2];
+    if (!line_variant(op.Q, kMass, op.basis.colloc, false, false, c.variant)) return kDefChainMass[op.Q - 2];
     const int G = kLineG[op.Q - 2][line_slot(c.variant)];
     const int64_t columns = (int64_t)((op.d.nex + G - 1) / G) * op.d.nez * nvec;
     return line_march(kDefChainLineMass[op.Q - 2], op.d.ney, columns, line_nt(op.Q, G));
@@ -659,9 +660,10 @@ int mfhex_get_config(mfhex_op op, int prec, int nrhs, int32_t *variant, int32_t 
     if (!op || nrhs < 1) return fail(MFHEX_ERR_ARG, "bad argument");
     const LaunchCfg c = config_for(*op, prec, nrhs * op->d.ncomp, op->ebuf != nullptr);
     if (variant) *variant = c.variant;
-    const bool line = line_variant(op->Q, mode_of(*op), op->basis.colloc, (op->d.flags & MFHEX_FLAG_OTF) != 0, c.variant);
-    const int shape = elem_shape(op->Q, mode_of(*op), op->basis.colloc, (op->d.flags & MFHEX_FLAG_OTF) != 0, c.variant);
-    const bool mline = !op->ebuf && mline_serves(op->P, op->Q, mode_of(*op), op->basis.colloc, prec == MFHEX_F32 ? 4 : 8,
+    const bool otf = (op->d.flags & MFHEX_FLAG_OTF) != 0, f32 = prec == MFHEX_F32;
+    const bool line = line_variant(op->Q, mode_of(*op), op->basis.colloc, otf, f32, c.variant);
+    const int shape = elem_shape(op->Q, mode_of(*op), op->basis.colloc, otf, f32, c.variant);
+    const bool mline = !op->ebuf && mline_serves(op->P, op->Q, mode_of(*op), op->basis.colloc, f32 ? 4 : 8,
                                                  c.variant, nrhs * op->d.ncomp, op->d.nex, op->E);
     const int g = line    ? kLineG[op->Q - 2][line_slot(c.variant)]
                   : mline ? mline_g(op->Q, c.variant)

@@ -178,20 +178,23 @@ constexpr int line_march(int most, int ney, int64_t columns, int nt)
     return (int)(m < 1 ? 1 : m < cap ? m : cap);
 }
 constexpr int line_slot(int v) { return v < 5 ? v : v == 14 ? 0 : v - 9; }
-// Collocated diffusion, of the numbers 0 .. 4 the one that is the element-at-a-time kernel with stored factors instead
+// Collocated diffusion in FP64, of the numbers 0 .. 4 the one that is the element-at-a-time kernel with stored factors instead
 // (k_apply, in the shape of kElemShape; elem_slot, -1: none), at the q where it is the faster one somewhere (kElemColl).
 constexpr int kElemSlotColl[9] = {3, -1, -1, -1, -1, -1, -1, 4, -1};
 constexpr int kElemShape[9] = {0, 0, 0, 4, 4, 4, 0, 4, 3};
-constexpr int elem_slot(int Q, int mode, bool colloc, bool otf) { return mode == 1 && colloc && !otf ? kElemSlotColl[Q - 2] : -1; }
-// The variant whose group shape (variant_g, variant_nt below) an element-at-a-time launch takes.
-constexpr int elem_shape(int Q, int mode, bool colloc, bool otf, int v)
+constexpr int elem_slot(int Q, int mode, bool colloc, bool otf, bool f32)
 {
-    return v == elem_slot(Q, mode, colloc, otf) ? kElemShape[Q - 2] : v;
+    return mode == 1 && colloc && !otf && !f32 ? kElemSlotColl[Q - 2] : -1;
 }
-constexpr bool line_variant(int Q, int mode, bool colloc, bool otf, int v)
+// The variant whose group shape (variant_g, variant_nt below) an element-at-a-time launch takes.
+constexpr int elem_shape(int Q, int mode, bool colloc, bool otf, bool f32, int v)
+{
+    return v == elem_slot(Q, mode, colloc, otf, f32) ? kElemShape[Q - 2] : v;
+}
+constexpr bool line_variant(int Q, int mode, bool colloc, bool otf, bool f32, int v)
 {
     if (mode == 0) return v < 5 && !colloc;
-    return mode == 1 && v != elem_slot(Q, mode, colloc, otf) && (colloc || otf ? v < 5 : v >= 9 && v <= 14);
+    return mode == 1 && v != elem_slot(Q, mode, colloc, otf, f32) && (colloc || otf ? v < 5 : v >= 9 && v <= 14);
 }
 // Collocated diffusion, several vectors: variants 6 and 7 are the line-fused multi-vector kernel (k_mline) with chunks
 // of 4 and 8 vectors; G q^2 VC lanes.  G fills the last wavefront (q <= 5) while two groups fit a CU's LDS.

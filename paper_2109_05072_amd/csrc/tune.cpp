@@ -47,7 +47,7 @@ std::string arch_name(int device)
 // comes to stand for another kernel); whether the operator evaluates its factors (a number is another kernel then), is
 // deterministic or has a coefficient; the row length, to an eighth of an octave, on which the idle lanes of a group
 // depend; and the octave of the element count, on which the best depth does.
-constexpr int kVariantNumbers = 5;
+constexpr int kVariantNumbers = 6;
 std::string cache_key(const mfhex_op_s &op)
 {
     int octave = 0, size = 0;
@@ -115,7 +115,7 @@ int tune(mfhex_op op, int prec, int nrhs, void *scratch, const char *cache_path,
     // (mass) the others, each launch once
     std::vector<LaunchCfg> cand{LaunchCfg{def, 0}};
     const auto in_kernel = [&](int v) {
-        return line_variant(op->Q, mode_of(*op), op->basis.colloc, (op->d.flags & MFHEX_FLAG_OTF) != 0, v);
+        return line_variant(op->Q, mode_of(*op), op->basis.colloc, (op->d.flags & MFHEX_FLAG_OTF) != 0, prec == MFHEX_F32, v);
     };
     const auto same_launch = [&](int v, int w) {  // slots of the line-fused kernel with one group size
         return in_kernel(v) && in_kernel(w) && kLineG[op->Q - 2][line_slot(v)] == kLineG[op->Q - 2][line_slot(w)];

@@ -59,6 +59,22 @@ def test_factors_in_the_kernel_elsewhere(gpu_lib, p, quad, dtype, ne):
     assert 9 <= v <= 13 if quad == "gauss" else v < 5 and v != {1: 3, 3: -1, 8: 4}[p]
 
 
+@pytest.mark.parametrize("p,variant,elem,line", [(1, 3, 16, 64), (8, 4, 1, 3)])
+def test_stored_factor_number_is_fp64_only(gpu_lib, p, variant, elem, line):
+    # the number of the stored-factor kernel is a group of the line kernel in FP32 and with in-kernel factors
+    op, pr = build(gpu_lib, 3, 2, 2, p, "diffusion", "gll", True, f32=True)
+    x = synth.uniform_vector(pr.n_nodes)
+    yo = oracle.apply(pr, x)
+    for dtype, g, tol in ((F64, elem, TOL64), (F32, line, TOL32)):
+        op.set_config(variant, dtype)
+        assert op.get_config(dtype)[:2] == (variant, g)
+        assert relerr(host(op.apply(dev(x, dtype))), yo) <= tol
+    otf, _ = build(gpu_lib, 3, 2, 2, p, "diffusion", "gll", True, otf=True)
+    otf.set_config(variant)
+    assert otf.get_config()[:2] == (variant, line)
+    assert relerr(host(otf.apply(dev(x))), yo) <= TOL64
+
+
 @pytest.mark.parametrize("p,option", [(8, ""), (8, "vark"), (8, "otf"), (8, "det"), (7, "det")])
 @pytest.mark.parametrize("ne", [(2, 2, 2), (4, 4, 4), (6, 6, 7)])
 def test_few_large_elements_run_alone(gpu_lib, p, option, ne):
